@@ -27,6 +27,8 @@
 // split-BF16 products (v_mfma_f32_16x16x16_bf16) in the split mode.
 #include "device.hpp"
 
+#include <type_traits>
+
 namespace spx {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
@@ -512,137 +514,152 @@ __device__ __forceinline__ double recip_nr(double d)
 // (each item begins with a cache invalidation) on the elimination chain.
 constexpr int kThrSlot = 3 * kNB;   // offset from bc
 
+// acc[i] += m * (lane i's value of b within each row of 16 lanes), i = I0 ..
+// I0 + N - 1: FP64 multiply-adds that take one operand from a fixed lane
+// (DPP row_newbcast; 4.5 cycles each, measured, where a readlane pair and
+// a multiply-add took 23 and a broadcast read of LDS 10 plus the
+// multiply-add).  b comes from LDS, not from a vector instruction; the
+// s_nop keeps the distance a DPP read needs even if a register copy
+// precedes it.
+template <int I0, int N, int NV>
+__device__ __forceinline__ void fmac_rows(double (&acc)[NV], int at, double b, double m)
+{
+#define SPX_FM(q, k) "v_fmac_f64_dpp %" #q ", %[b], %[m] row_newbcast:%[" #k "] row_mask:0xf bank_mask:0xf\n"
+    if constexpr (N >= 4) {
+        asm("s_nop 1\n" SPX_FM(0, k0) SPX_FM(1, k1) SPX_FM(2, k2) SPX_FM(3, k3)
+            : "+v"(acc[at]), "+v"(acc[at + 1]), "+v"(acc[at + 2]), "+v"(acc[at + 3])
+            : [b] "v"(b), [m] "v"(m), [k0] "n"(I0), [k1] "n"(I0 + 1), [k2] "n"(I0 + 2), [k3] "n"(I0 + 3));
+        fmac_rows<I0 + 4, N - 4>(acc, at + 4, b, m);
+    } else if constexpr (N >= 1) {
+        asm("s_nop 1\n" SPX_FM(0, k0) : "+v"(acc[at]) : [b] "v"(b), [m] "v"(m), [k0] "n"(I0));
+        fmac_rows<I0 + 1, N - 1>(acc, at + 1, b, m);
+    }
+#undef SPX_FM
+}
+
 // Cholesky factor and inverse of one 32x32 diagonal tile, in FP64, by one
 // wave.  Lt (column-major, ld 33) holds the lower triangle of the tile; rows
 // and columns >= jb hold the identity.  Lane r < 32 keeps row r of the tile,
 // lane 32 + q keeps column q of X = L^{-1}, starting from the unit vector
-// e_q.  One right-looking loop over the columns c serves both halves: the
+// e_q.  One right-looking pass over the columns c serves both halves: the
 // pivot l_cc is broadcast by readlane, column c is scaled by 1/l_cc (the
-// pivot itself becomes sqrt of it), its entries l_ic go to LDS (bc), and every
-// lane updates v[i] -= v[c] * l_ic for i > c.  For a row of the tile that is
-// the Cholesky update of its remaining columns; for a column of X it is the
-// forward substitution step x_iq -= l_ic x_cq after x_cq was divided by
-// l_cc.  Entries above the diagonal of the tile rows are not meaningful and
-// never read.  A pivot that is not > 0 records its column with atomicMin
-// (NaN propagates).  Out: L in Lt (upper triangle zero), X in Dt.  NC (8,
-// 16 or 32, >= jb) bounds the columns stepped through: the leading NC x NC
-// part of Lt and Dt is written, the rest of the identity-padded tile is
-// left as it is.
+// pivot itself becomes sqrt of it), its entries l_ic go through LDS (bc) into
+// every row of 16 lanes, and every lane updates v[i] -= v[c] * l_ic for
+// i > c (fmac_rows).  For a row of the tile that is the Cholesky update of
+// its remaining columns; for a column of X it is the forward substitution
+// step x_iq -= l_ic x_cq after x_cq was divided by l_cc.  A pivot that is not
+// > 0 records its column with atomicMin (NaN propagates).  Column c goes out
+// as soon as it is final, by out(c, lane, x, d): in the lower half of the
+// wave x = l_rc of row r = lane (r < c: an undefined value; L D L^T: 1 for
+// r = c, and d is the pivot), in the upper half x = x_cr of column
+// r = lane - 32 (r > c: zero).  Columns 0 .. jb - 1, rounded up to a
+// multiple of 8, go out; NC (8, 16 or 32, >= jb) bounds them.
 //
-// LDL = true: the L D L^T form of the same loop (unit L): the pivot d is
-// not square-rooted (a breakdown is a zero or non-finite d, found from the
-// diagonal after the loop), a row keeps the
-// unscaled value t of column c for its update (a_ri -= t l_ic) and stores
+// What bounds it is the chain from one pivot to the next: 94 cycles a
+// column (readlane, estimate, one third-order step, scaling, readlane,
+// multiply-add), with the updates of the later columns in its gaps.  The
+// next column is updated by a readlane of l_{c+1,c}, so that its pivot does
+// not wait for the LDS round trip of the others.  A tile alone on the chip
+// takes 12,000 cycles; a form that read l_ic from LDS for every update and
+// branched around each load of Lt took 38,400.
+//
+// LDL = true: the L D L^T form of the same pass (unit L): the pivot d is
+// not square-rooted (a breakdown is a zero or non-finite d), a row keeps the
+// unscaled value t of column c for its update (a_ri -= t l_ic) and puts out
 // t / d (d itself on the diagonal); on the identity rows the same steps give
-// Y = D^{-1} L^{-1}.  Out: L (unit, d on the diagonal) in Lt, Y in Dt.
-//
-// Static pivoting (L D L^T): the common form (PIV false) only tracks the
-// smallest |d| (one min per column, beside the dependency chain) and
-// returns false before writing anything when it is below the threshold;
-// the tile, still intact in Lt, is then factored again by the form with the
-// replacement (PIV true).  With the test and replacement in every step, the
-// scalar registers of the loop spill and each step waits longer.
-template <class T, int NC, bool LDL, bool PIV>
-__device__ __noinline__ bool tile_chol_inv_k(double* Lt, double* bc, T* Dt, int jb, int col0, int32_t* status)
-{
-    static_assert(NC == 8 || NC == 16 || NC == 32, "tile width");
-    const double thr = LDL ? readlane_d(bc[kThrSlot], 0) : 0.0;
-    double dmin = __builtin_inf();
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 31;
-    const bool upper = lane >= 32;
+// Y = D^{-1} L^{-1}.  Static pivoting: a pivot with |d| below the threshold
+// is replaced by +-threshold (a select beside the reciprocal) and counted.
+template <int NC, bool LDL, class Out>
+struct TileChol {
     double v[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        const double l = Lt[r + c * 33];
-        v[c] = upper ? (c == r ? 1.0 : 0.0) : l;
-    }
-    // pivot of column c: inv = 1/sqrt(l_cc) from the hardware estimate and
-    // two Newton-Raphson steps y <- y (3 - d y^2) / 2, s = d inv (a short
-    // dependency chain; within a few ulps of the rounded values)
-    int fail = 32;
-    int nrep = 0;   // (L D L^T) pivots replaced by the static pivoting threshold thr
-    auto pivot = [&](int c, double& s, double& inv) {
-        double d = readlane_d(v[c], c);
+    double inv, d, y, thr;   // 1/l_cc (1/d) of the current column; the pivot d in work and its estimate
+    int lane, jb, fail, nrep;
+    __attribute__((address_space(3))) double* bc;
+    Out out;
+
+    // d and the hardware estimate y of 1/sqrt(d) (1/d) from column c
+    __device__ __forceinline__ void estimate(int c, double x)
+    {
+        d = readlane_d(x, c);
         if constexpr (LDL) {
-            if constexpr (PIV) {
-                if (c < jb && fabs(d) < thr) {   // static pivoting (a uniform branch)
-                    d = d < 0.0 ? -thr : thr;
-                    ++nrep;
-                }
-            } else {
-                dmin = fmin(dmin, fabs(d));   // (identity padding: pivots 1)
-            }
-            const double y = recip_nr(d);
-            inv = y;
-            s = d;
+            const bool rep = c < jb && fabs(d) < thr;
+            d = rep ? (d < 0.0 ? -thr : thr) : d;
+            nrep += rep ? 1 : 0;
+            fail = (c < jb && !(d != 0.0 && d - d == 0.0) && fail == 32) ? c : fail;
+            y = __builtin_amdgcn_rcp(d);
         } else {
             fail = (c < jb && !(d > 0.0) && fail == 32) ? c : fail;
-            double y = __builtin_amdgcn_rsq(d);
-            y = y * __builtin_fma(-0.5 * d, y * y, 1.5);
-            y = y * __builtin_fma(-0.5 * d, y * y, 1.5);
-            inv = y;
-            s = d * y;
+            y = __builtin_amdgcn_rsq(d);
         }
-    };
-    double s, inv;
-    pivot(0, s, inv);
+    }
+    __device__ __forceinline__ void finish()
+    {
+        if constexpr (LDL) {
+            const double e = __builtin_fma(-d, y, 1.0);
+            inv = __builtin_fma(y, __builtin_fma(e, e, e), y);
+        } else {
+            const double e = __builtin_fma(-(d * y), y, 1.0);
+            inv = __builtin_fma(e * y, __builtin_fma(e, 0.375, 0.5), y);
+        }
+    }
+    template <int C>
+    __device__ __forceinline__ void columns()
+    {
+        const double t = v[C];
+        const double x = t * inv;          // lane C: l_cc = d / sqrt(d) (L D L^T: 1)
+        const double m = LDL ? -t : -x;    // minus the factor of this column's update
+        const double dc = d;
+        if constexpr (C + 1 < NC) {
+            if constexpr (C + 2 < NC) bc[lane] = x;
+            v[C + 1] = __builtin_fma(m, readlane_d(x, C + 1), v[C + 1]);
+            double b0 = 0.0, b1 = 0.0;
+            if constexpr (C + 2 < NC) {   // LDS operations of one wave complete in order: the reads see column C
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if constexpr (C + 2 < 16) b0 = bc[lane & 15];
+                if constexpr (NC > 16) b1 = bc[16 + (lane & 15)];
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            }
+            estimate(C + 1, v[C + 1]);
+            out(C, lane, x, dc);
+            finish();
+            if constexpr (C + 2 < 16) fmac_rows<C + 2, (NC < 16 ? NC : 16) - (C + 2)>(v, C + 2, b0, m);
+            if constexpr (NC > 16) {
+                constexpr int i = C + 2 > 16 ? C + 2 : 16;
+                fmac_rows<i - 16, NC - i>(v, i, b1, m);
+            }
+            if constexpr ((C & 7) == 7) {
+                if (jb <= C + 1) return;
+            }
+            columns<C + 1>();
+        } else {
+            out(C, lane, x, dc);
+        }
+    }
+};
+
+template <int NC, bool LDL, class Out>
+__device__ __forceinline__ void tile_chol_inv(double* Lt_g, double* bc_g, int jb, int col0, int32_t* status, Out out)
+{
+    static_assert(NC == 8 || NC == 16 || NC == 32, "tile width");
+    auto Lt = lds(Lt_g);
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // (keeps the lane masks of the columns from being formed ahead and held)
+    const int r = lane & 31;
+    TileChol<NC, LDL, Out> tc{{}, 0.0, 0.0, 0.0, LDL ? readlane_d(lds(bc_g)[kThrSlot], 0) : 0.0, lane, jb, 32, 0, lds(bc_g), out};
+#pragma unroll
+    for (int c = 0; c < NC; ++c) tc.v[c] = Lt[r + c * 33];
+    // (all loads issued before the selects: a conditional load is a branch each)
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
-        // L D L^T: every row is scaled by 1/d_c but updated with its unscaled
-        // value, so the factor rows hold unit L (d_c on the diagonal) and the
-        // identity rows end as rows of L^{-T} D^{-1}
-        const double t = v[c];
-        v[c] = lane == c ? s : t * inv;
-        const double tu = LDL ? t : v[c];   // the factor of this column's update
-        if (c < NC - 1) {
-            // column c to bc[0..31] (the upper half writes the unused
-            // bc[32..63]); LDS operations of one wave complete in order, so
-            // the reads below see it (compiler barrier only)
-            bc[lane] = v[c];
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            // column c+1 first: its pivot overlaps the rest of the update
-            v[c + 1] -= tu * bc[c + 1];
-            double sn, invn;
-            pivot(c + 1, sn, invn);
-#pragma unroll
-            for (int i = c + 2; i < NC; ++i) v[i] -= tu * bc[i];
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            s = sn;
-            inv = invn;
-        }
-        // keep the scheduler from interleaving column steps (register pressure)
-        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("" : "+v"(tc.v[c]));
+        tc.v[c] = lane >= 32 ? (c == r ? 1.0 : 0.0) : tc.v[c];
     }
-    if constexpr (LDL && !PIV) {
-        if (dmin < thr) return false;   // a pivot to replace: the caller runs the PIV form
-    }
-    if constexpr (LDL) {   // breakdown: a zero or non-finite pivot among the first jb
-        double dd = 0.0;
-#pragma unroll
-        for (int c = 0; c < NC; ++c) dd = lane == c ? v[c] : dd;
-        const bool bad = !upper && r < jb && !(dd != 0.0 && dd - dd == 0.0);
-        const uint64_t m = __ballot(bad);
-        fail = m ? __builtin_ctzll(m) : 32;
-    }
-    if (lane == 0 && fail < jb) atomicMin(status, col0 + fail);
-    if (LDL && lane == 0 && nrep > 0) atomicAdd(status + kStReplaced, nrep);
-    if (r < NC && !upper) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) Lt[r + c * 33] = c <= r ? v[c] : 0.0;
-    }
-    if (r < NC && upper) {
-#pragma unroll
-        for (int c = 0; c < NC; ++c) Dt[c + r * 33] = c >= r ? (T)v[c] : T(0);
-    }
-    return true;
-}
-
-template <class T, int NC = 32, bool LDL = false>
-__device__ __forceinline__ void tile_chol_inv(double* Lt, double* bc, T* Dt, int jb, int col0, int32_t* status)
-{
-    if (!tile_chol_inv_k<T, NC, LDL, false>(Lt, bc, Dt, jb, col0, status))
-        tile_chol_inv_k<T, NC, LDL, true>(Lt, bc, Dt, jb, col0, status);
+    tc.estimate(0, tc.v[0]);
+    tc.finish();
+    tc.template columns<0>();
+    if (lane == 0 && tc.fail < jb) atomicMin(status, col0 + tc.fail);
+    if (LDL && lane == 0 && tc.nrep > 0) atomicAdd(status + kStReplaced, tc.nrep);
 }
 
 // Small product of the diagonal-block factorization: acc += X Y^T with
@@ -724,171 +741,375 @@ __device__ __forceinline__ void wave_mm_rmw(LX ldx, LY ldy, int mv, int nv, cons
 }
 
 constexpr int kPbLd = 228;   // leading dimension of the LDS copy of the rows below a tile (<= 224 rows)
+constexpr int kTSz = kNB * 33;                 // a 32x32 tile in LDS, column-major, ld 33
+constexpr int kTiles = 256 / kNB;              // tiles of the widest block: the LDS buffer of every item but FACT's own
+static_assert((kTiles - 1) * kTSz >= kPbLd * kNB + 32, "row buffer");
+
+// A 32x32 block held by one wave, in the form of the matrix cores' results:
+// b[h][q][v] of lane l holds M(16 q + l%16, 16 h + drow(v, l/16)).  As the
+// inner index of a product may be taken in any order, provided both operands
+// take the same one, this is also the form of an operand whose inner index
+// is its column: results feed the next product without a pass through LDS.
+template <class T>
+struct Blk {
+    typename MM<T>::acc b[2][2];
+};
+
+template <class T>
+__device__ __forceinline__ void blk_zero(Blk<T>& m)
+{
+    zero_acc(m.b);
+}
+
+// rows row0.., columns col0.. of g's array; half h only if given
+template <class T>
+__device__ __forceinline__ void blk_load_half(T (&m)[2][4], const GOp& g, int row0, int col0, int h)
+{
+    const int lane = threadIdx.x & 63;
+    const int vo = (lane & 15) * g.si + MM<T>::drow(0, lane >> 4) * g.sk;
+#pragma unroll
+    for (int q = 0; q < 2; ++q)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            m[q][v] = gload_s(g, vo, uni(g.off + (row0 + 16 * q) * g.si + (col0 + 16 * h + MM<T>::drow(v, 0)) * g.sk), T(0));
+}
+
+template <class T>
+__device__ __forceinline__ void blk_load(Blk<T>& m, const GOp& g, int row0, int col0)
+{
+    T x[2][2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) blk_load_half<T>(x[h], g, row0, col0, h);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) m.b[h][q][v] = x[h][q][v];
+}
+
+// C += X Y^T of two blocks; LOW: the blocks of C on and below the diagonal
+// only; YTRI: Y is lower triangular (its upper right quarter is zero)
+template <class T, bool LOW, bool YTRI>
+__device__ __forceinline__ void blk_mul(Blk<T>& C, const Blk<T>& X, const Blk<T>& Y)
+{
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (LOW && h == 1 && q == 0) continue;
+                    if (YTRI && h == 0 && p == 1) continue;
+                    C.b[h][q] = MM<T>::mfma(Y.b[p][h][v], X.b[p][q][v], C.b[h][q]);
+                }
+}
+
+// a tile in LDS (column-major, ld 33) as a block, M(c, p) = tile[c + 33 p]
+template <class T>
+__device__ __forceinline__ void blk_from_lds(Blk<T>& m, const double* tile_g)
+{
+    auto tile = lds(tile_g);
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) m.b[h][q][v] = (T)tile[16 * q + li + 33 * (16 * h + MM<T>::drow(v, lk))];
+}
+
+// the block's columns times d[0..31] (LDS, FP64)
+template <class T>
+__device__ __forceinline__ void blk_scale(Blk<T>& m, const double* d_g)
+{
+    auto d = lds(d_g);
+    const int lk = (threadIdx.x & 63) >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const T dv = (T)d[16 * h + MM<T>::drow(v, lk)];
+#pragma unroll
+            for (int q = 0; q < 2; ++q) m.b[h][q][v] *= dv;
+        }
+}
+
+// C += X Y^T over nblk 32-wide inner blocks: X(r, p) at row xr, inner index
+// xp + p of gx (row = the array's row index), Y(c, p) likewise; SWAP: the
+// result transposed in the lanes, C.b[h][q][v] = C(16 h + drow(v, l/16),
+// 16 q + l%16), the operand form of a block whose inner index is its row.
+// d: X's columns scaled by d[p] (LDS, indexed from inner index 0).  The
+// next half block (16 inner indices) is in flight while the current one is
+// multiplied.
+template <class T, bool SWAP, bool DS>
+__device__ __forceinline__ void blk_gemm(Blk<T>& C, const GOp& gx, int xr, int xp, const GOp& gy, int yr, int yp, int nblk,
+                                         const double* d_g)
+{
+    if (nblk <= 0) return;
+    const int lk = (threadIdx.x & 63) >> 4;
+    T xa[2][4], ya[2][4], xb[2][4], yb[2][4];
+    auto load = [&](T (&x)[2][4], T (&y)[2][4], int ch) {
+        blk_load_half<T>(x, gx, xr, xp + 16 * ch, 0);
+        blk_load_half<T>(y, gy, yr, yp + 16 * ch, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto mma = [&](T (&x)[2][4], T (&y)[2][4], int ch) {
+        if constexpr (DS) {
+            auto d = lds(d_g);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const T dv = (T)d[16 * ch + MM<T>::drow(v, lk)];
+#pragma unroll
+                for (int q = 0; q < 2; ++q) x[q][v] *= dv;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+                    C.b[h][q] = SWAP ? MM<T>::mfma(x[h][v], y[q][v], C.b[h][q]) : MM<T>::mfma(y[h][v], x[q][v], C.b[h][q]);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(xa, ya, 0);
+    for (int ch = 0; ch < 2 * nblk; ch += 2) {
+        load(xb, yb, ch + 1);
+        mma(xa, ya, ch);
+        load(xa, ya, min(ch + 2, 2 * nblk - 1));   // (the last one repeats and is not used)
+        mma(xb, yb, ch + 1);
+    }
+}
+
+// Progress words of the row blocks of a diagonal block, in LDS: a wave waits
+// until another one has published what it reads.  Every wait ends: row
+// block i waits for row blocks < i only, and row block 0 for none.
+__device__ __forceinline__ void wait_for(const int* flag_g, int value)
+{
+    auto flag = lds(flag_g);
+    while (__hip_atomic_load(flag, __ATOMIC_ACQUIRE, __HIP_MEMORY_SCOPE_WORKGROUP) < value) __builtin_amdgcn_s_sleep(1);
+}
+// (all lanes store the same value; release: the wave's stores are visible
+// to the workgroup first)
+__device__ __forceinline__ void publish(int* flag_g, int value)
+{
+    __hip_atomic_store(lds(flag_g), value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+// the same for data in LDS alone (stores to memory may still be on their way)
+__device__ __forceinline__ void publish_lds(int* flag_g, int value)
+{
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    __hip_atomic_store(lds(flag_g), value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
 
 // Cholesky factorization of the w x w diagonal block (w <= 256) of panel k
-// and the inverse D = L_kk^{-1}, by one workgroup, right-looking over 32
-// columns at a time.  The running inverse uses the block form of L D = I:
-// block row I of D is D_II (E_I - sum_{K<I} L_IK D_K), accumulated as the
-// columns of L become final.  Step J (tile columns J .. J+jb):
-//   1. the tile, fully updated, is factored and inverted by wave 0
-//      (tile_chol_inv): L_JJ -> panel, D_JJ -> D;
-//   2. the rows below: P = A[J+jb:w, J:J+jb] D_JJ^T -> panel and LDS (Pb);
-//      block row J of D: D_J[:, 0:J] = D_JJ X_J[:, 0:J], in place;
-//   3. trailing updates, 64x32 tiles dealt to the four waves:
-//      A[J+jb:, J+jb:] -= P P^T (lower triangle) and
-//      X[J+jb:, 0:J+jb] -= P D_J (columns J .. J+jb written for the first time).
-// Products run on the matrix cores; P and D_JJ are read from LDS.
+// and the inverse D = L_kk^{-1}, by one workgroup.  The block is cut into
+// row blocks of 32; wave v owns the row blocks v, v + 4, ...  Row block i is
+// a forward substitution against the finished row blocks above it,
+//   L_iJ = (A_iJ - sum_{K<J} L_iK L_JK^T) D_JJ^T,   J = 0 .. i-1,
+// then its diagonal tile A_ii - sum_K L_iK L_iK^T is factored and inverted
+// (tile_chol_inv).  Nothing is updated in memory: a block is read once,
+// collected on the matrix cores and written once.  The waves run as a
+// pipeline without barriers: row block i takes L_J* as soon as row block J
+// has published it (s_x) and D_JJ as soon as tile J is factored (s_d), so a
+// step of the chain is one tile factorization, one 32x32 product with D_JJ
+// and one with L_i,i-1; the long sums over K are formed ahead of it by waves
+// that wait for D_JJ.  -D_JJ stays in LDS for the whole item, L_iJ in
+// registers between the product that makes it and the ones that use it.
+// The rest of the inverse follows by block columns,
+//   D_Jc = -D_JJ sum_{c<=K<J} L_JK D_Kc,
+// dealt to the waves as they run out of row blocks (the longest columns to
+// the wave that is free first); a chain block (inv_item) leaves it to its
+// INV item.  Bound: the chain of 32-column tile factorizations.
+// The right-looking form before it (trailing blocks read, updated and
+// written in memory at every 32-column step, two barriers per step) took
+// 294 us at w = 256 in FP64 and 252 us without the inverse's off-diagonal
+// blocks, in a kernel of its own on an idle MI355X; this one 123 and 83 us
+// (FP32 233 and 206 us before, 101 and 67 us now).
 //
 // LDL = true: L D L^T of the diagonal block (unit L with D on its diagonal,
 // and Y = D^{-1} L^{-1} as the stored inverse, so that the panel solve and
-// the rows below stay one product A_rows Y^T): the tile step is the L D L^T
-// form of tile_chol_inv, the trailing update is A -= L (D L^T) and the rows
-// of the running inverse take (L D) Y_J.
+// the rows below stay one product A_rows Y^T): the same with d between the
+// factors of every product of two L's, and -Y_JJ in place of -D_JJ.
 template <class T, bool LDL = false>
-__device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, T* Dt, T* Pb)
+__device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, double* tiles)
 {
-    typedef typename MM<T>::acc acc_t;
     const DevPlan& pl = a.pl;
-    const int f = pl.fcol[k];
-    const int w = pl.lcol[k] - f + 1;
+    const int f = uni(pl.fcol[k]);
+    const int w = uni(pl.lcol[k]) - f + 1;
     const int64_t ld = pl.stride[k];
     T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
     T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
-    const int64_t nA = ld * w, nD = (int64_t)w * w;
-    const GOp gA = make_gop(A, nA, 0, 1, ld);   // A(i, p) at i + p*ld
-    const GOp gD = make_gop(D, nD, 0, 1, w);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const GOp gA = make_gop(A, ld * w, 0, 1, ld);           // A(i, p) at i + p*ld
+    const GOp gDt = make_gop(D, (int64_t)w * w, 0, w, 1);   // D^T(i, p) = D(p, i)
+    const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     double* bc = Lt + kNB * 33;
-    __shared__ int s_next;   // next trailing tile to deal
-    __shared__ double dcur[kNB];   // (L D L^T) this step's pivots
-    bool ready = false;      // Lt/Dt already hold this step's factored tile
-    // the off-diagonal tiles of the inverse here, or (a chain block with an
-    // INV item) only its diagonal tiles, D_JJ
-    const bool full = LDL || a.inv_item == nullptr || a.inv_item[k] < 0;
-    for (int J = 0; J < w; J += kNB) {
-        const int jb = min(kNB, w - J);
-        const int R = w - J - jb;   // rows below the tile inside the block
-        // 1. tile (identity padded) -> Lt; factor and invert (done ahead,
-        // during the previous step's trailing updates, from the second step on)
-        if (!ready) {
-            for (int idx = tid; idx < kNB * kNB; idx += kThreads) {
-                const int r = idx & 31, c = idx >> 5;
-                Lt[r + c * 33] = (r < jb && c < jb) ? (c <= r ? (double)A[(J + r) + (int64_t)(J + c) * ld] : 0.0)
-                                                    : (r == c ? 1.0 : 0.0);
+    __shared__ int s_x[8], s_d;      // blocks of row block i published (i + 1: D_ii too); tiles factored
+    __shared__ double dd[LDL ? 256 : 1];   // (L D L^T) the pivots
+    const bool full = a.inv_item == nullptr || uni(a.inv_item[k]) < 0;
+    const int nb = (w + kNB - 1) / kNB;
+    if (tid < 8) s_x[tid] = 0;
+    if (tid == 8) s_d = 0;
+    __syncthreads();
+    for (int i = wave; i < nb; i += kThreads / 64) {
+        const int i0 = kNB * i, jb = min(kNB, w - i0);
+        // (entries past w are read from the rows below or as zeros and only
+        // reach rows and columns past jb; the sums are collected from zero
+        // and subtracted once: fewer roundings than from A downwards)
+        Blk<T> S, X;
+        blk_zero<T>(S);
+        for (int J = 0; J < i; ++J) {
+            Blk<T> B, C;
+            blk_load<T>(B, gA, i0, kNB * J);
+            blk_zero<T>(C);
+            if (J > 0) {
+                wait_for(&s_x[J], J - 1);
+                blk_gemm<T, false, LDL>(C, gA, i0, 0, gA, kNB * J, 0, J - 1, dd);
+                wait_for(&s_x[J], J);
+                Blk<T> Y;
+                blk_load<T>(Y, gA, kNB * J, kNB * (J - 1));
+                if (LDL) blk_scale<T>(X, dd + kNB * (J - 1));
+                blk_mul<T, false, false>(C, X, Y);
             }
-            __syncthreads();
-            if (wave == 0) tile_chol_inv<T, 32, LDL>(Lt, bc, Dt, jb, f + J, a.status);
-        }
-        if (tid == 0) s_next = 0;
-        __syncthreads();
-        for (int idx = tid; idx < kNB * kNB; idx += kThreads) {
-            const int r = idx & 31, c = idx >> 5;
-            if (r < jb && c <= r) {
-                A[(J + r) + (int64_t)(J + c) * ld] = (T)Lt[r + c * 33];
-                D[(J + r) + (int64_t)(J + c) * w] = Dt[r + c * 33];
-            }
-        }
-        if (LDL && tid < kNB) dcur[tid] = Lt[tid + tid * 33];
-        // 2a. rows below: P = A_rows D_JJ^T (wave v: rows 64v ..)
-        const int r0 = 64 * wave;
-        if (r0 < R) {
-            acc_t acc[2][4];
-            zero_acc(acc);
-            const int gbase = gA.off + (J + jb + r0) * gA.si + J * gA.sk;
-            // (R > 0 implies jb = 32: full inner range)
-            wave_mm<2, T>(acc, [&](int i, int p) { return gload<T>(gA, gbase + i * gA.si + p * gA.sk); },
-                          [&](int c, int p) { return Dt[c + p * 33]; });
-            wave_store<T>(acc, min(64, R - r0), jb, [&](int r, int c, T v) {
-                Pb[(r0 + r) + c * kPbLd] = v;
-                A[(J + jb + r0 + r) + (int64_t)(J + c) * ld] = v;
-            });
-        }
-        // 2b. block row J of D for columns < J (transposed: rows c of the
-        // product are columns of D), each wave a 64-column slice, in place
-        for (int c0 = 64 * wave; full && c0 < J; c0 += 64 * (kThreads / 64)) {
-            acc_t acc[2][4];
-            zero_acc(acc);
-            // with jb < 32 (last step) the inner indices p >= jb read entries
-            // of D below row w (finite: the top of the next column, or zero
-            // past the array) that meet D_JJ[r][p] = 0 for r < jb
-            wave_mm<2, T>(acc, [&](int i, int p) { return gload<T>(gD, gD.off + (J + p) * gD.si + (c0 + i) * gD.sk); },
-                          [&](int c, int p) { return Dt[c + p * 33]; });
-            wave_store<T>(acc, min(64, J - c0), jb,
-                          [&](int r, int c, T v) { D[(J + c) + (int64_t)(c0 + r) * w] = v; });
-        }
-        __syncthreads();
-        if (R == 0) break;
-        // 3. trailing updates: syrk tiles (rt, ct) with ct*32 < rt*64 + 64,
-        // then inverse tiles (rt, ct), ct*32 < J + jb, dealt to the waves one
-        // at a time.  Tile 0 holds the whole next diagonal tile: the wave that
-        // takes it also writes the tile's new lower entries (identity padded)
-        // to Lt and then factors and inverts it, while the other waves go on
-        // with the remaining tiles.
-        const int nrt = (R + 63) >> 6, ncs = (R + 31) >> 5, nci = (J + jb + 31) >> 5;
-        int nsyrk = 0;
-        for (int rt = 0; rt < nrt; ++rt) nsyrk += min(ncs, 2 * rt + 2);
-        const int ntiles = nsyrk + (full ? nrt * nci : 0);
-        const int jn = min(kNB, R);   // width of the next tile
-        for (;;) {
-            int t = 0;
-            if (lane == 0) t = atomicAdd(&s_next, 1);
-            t = __shfl(t, 0);
-            if (t >= ntiles) break;
-            int rt = 0, ct = t;
-            const bool syrk = t < nsyrk;
-            if (syrk) {
-                while (ct >= min(ncs, 2 * rt + 2)) { ct -= min(ncs, 2 * rt + 2); ++rt; }
+            wait_for(&s_d, J + 1);
+            Blk<T> Y;
+            blk_from_lds<T>(Y, tiles + J * kTSz);
+            blk_zero<T>(X);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) C.b[h][q] -= B.b[h][q];
+            blk_mul<T, false, true>(X, C, Y);   // (sum - A) (-D)^T
+            auto out = glob(A);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (16 * q + li < jb)
+                            out[(i0 + 16 * q + li) + (int64_t)(kNB * J + 16 * h + MM<T>::drow(v, lk)) * ld] = X.b[h][q][v];
+            if (LDL) {
+                Blk<T> Xd = X;
+                blk_scale<T>(Xd, dd + kNB * J);
+                blk_mul<T, true, false>(S, Xd, X);
             } else {
-                rt = (t - nsyrk) / nci;
-                ct = (t - nsyrk) - rt * nci;
+                blk_mul<T, true, false>(S, X, X);
             }
-            const int i0 = 64 * rt, c0 = 32 * ct;
-            const int mv = min(64, R - i0);
-            // rows i >= mv (and columns c >= nv below) only reach results
-            // that are not stored; Pb is padded for their indices
-            auto ldx = [&](int i, int p) { return Pb[(i0 + i) + p * kPbLd]; };
-            // (L D L^T) the facing rows of the syrk tiles and the rows of the
-            // inverse tiles carry D
-            auto ldxd = [&](int i, int p) { return LDL ? (T)(Pb[(i0 + i) + p * kPbLd] * dcur[p]) : Pb[(i0 + i) + p * kPbLd]; };
-            auto ldyd = [&](int c, int p) { return LDL ? (T)(Pb[(c0 + c) + p * kPbLd] * dcur[p]) : Pb[(c0 + c) + p * kPbLd]; };
-            auto sub = [](T o, T v) { return o - v; };
-            if (syrk) {
-                const int nv = min(32, R - c0);
-                GOp cA = gA;
-                cA.off = uni(gA.off + (J + jb + i0) * gA.si + (J + jb + c0) * gA.sk);
-                if (t == 0) {
-                    for (int idx = lane; idx < kNB * kNB; idx += 64) {
-                        const int r = idx & 31, c = idx >> 5;
-                        Lt[r + c * 33] = r == c && r >= jn ? 1.0 : 0.0;
+            publish(&s_x[i], J + 1);
+        }
+        // the tile, identity padded, to LDS; row block i-1 is done with Lt (s_d)
+        {
+            Blk<T> B;
+            blk_load<T>(B, gA, i0, i0);
+            auto L = lds(Lt);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int r = 16 * q + li, c = 16 * h + MM<T>::drow(v, lk);
+                        L[r + 33 * c] = (r < jb && c < jb) ? (double)(B.b[h][q][v] - S.b[h][q][v]) : (r == c ? 1.0 : 0.0);
                     }
-                    wave_mm_rmw<2, T>(
-                        ldx, ldyd, mv, nv, cA, [&](int r, int c) { return r >= c; }, sub, [&](int r, int c, T v) {
-                            if (r < jn && c < jn && c <= r) Lt[r + c * 33] = (double)v;
-                        });
-                    tile_chol_inv<T, 32, LDL>(Lt, bc, Dt, jn, f + J + jb, a.status);
-                } else {
-                    wave_mm_rmw<2, T>(
-                        ldx, ldyd, mv, nv, cA, [&](int r, int c) { return i0 + r >= c0 + c; }, sub,
-                        [](int, int, T) {});
-                }
-            } else {
-                const int nv = min(32, J + jb - c0);
-                auto ldy = [&](int c, int p) { return gload<T>(gD, gD.off + (J + p) * gD.si + (c0 + c) * gD.sk); };
-                if (c0 >= J) {   // columns written for the first time
-                    acc_t acc[2][4];
-                    zero_acc(acc);
-                    wave_mm<2, T>(acc, ldxd, ldy);
-                    wave_store<T>(acc, mv, nv,
-                                  [&](int r, int c, T v) { D[(J + jb + i0 + r) + (int64_t)(c0 + c) * w] = -v; });
-                } else {
-                    GOp cD = gD;
-                    cD.off = uni(gD.off + (J + jb + i0) * gD.si + c0 * gD.sk);
-                    wave_mm_rmw<2, T>(ldxd, ldy, mv, nv, cD, [](int, int) { return true; }, sub, [](int, int, T) {});
-                }
-            }
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
         }
-        __syncthreads();
-        ready = true;
+        auto Di = lds(tiles + i * kTSz);
+        // (branch-free: masked rows go past the array, the lower half's
+        // writes of D into the pivot buffer of the small items)
+        const int vL = uni(gA.off + i0 * gA.si + i0 * gA.sk), lim = jb;
+        auto out = [&](int c, int ln, double x, double d) {
+            const double val = (LDL && ln == c) ? d : x;
+            gstore_s(gA, (ln >= c && ln < lim && c < lim) ? ln * gA.si : kOffNone, uni(vL + c * gA.sk), (T)val);
+            (ln >= 32 ? Di + 33 * (ln - 32) : lds(bc) + 64)[c] = -x;
+            if (LDL) lds(dd)[i0 + c] = d;
+        };
+        tile_chol_inv<32, LDL>(Lt, bc, jb, f + i0, a.status, out);
+        publish_lds(&s_d, i + 1);
+        auto oD = glob(D + (int64_t)i0 * (w + 1));
+        for (int idx = lane; idx < kNB * kNB; idx += 64) {
+            const int r = idx & 31, c = idx >> 5;
+            if (r < jb && c <= r) oD[r + (int64_t)c * w] = (T)-Di[r + 33 * c];
+        }
+        publish(&s_x[i], i + 1);
+    }
+    if (!full) return;
+    // block columns of the inverse: wave v takes column v (first the columns
+    // 0 .. 3 with the most blocks; wave 0 runs out of row blocks first), then
+    // the short columns 4 .. 6 go to the waves 3, 2, 1
+    for (int t = 0; t < 2; ++t) {
+        const int c = t == 0 ? wave : 7 - wave;
+        if (c + 1 >= nb) continue;
+        Blk<T> N;   // -D_Kc of the last step, as an operand over its rows
+        for (int J = c + 1; J < nb; ++J) {
+            wait_for(&s_x[J], J);
+            Blk<T> C;
+            blk_zero<T>(C);
+            // sum over K < J - 1 from memory (this wave's own stores)
+            if (J == c + 1) {
+                wait_for(&s_x[c], c + 1);   // (its tile -D_cc in LDS, D_cc in memory)
+                auto tile = lds(tiles + c * kTSz);
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < 2; ++q)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) N.b[h][q][v] = (T)tile[16 * h + MM<T>::drow(v, lk) + 33 * (16 * q + li)];
+            } else {
+                blk_gemm<T, true, LDL>(C, gA, kNB * J, kNB * c, gDt, kNB * c, kNB * c, J - 1 - c, dd + kNB * c);
+            }
+            Blk<T> L;
+            blk_load<T>(L, gA, kNB * J, kNB * (J - 1));
+            if (LDL) blk_scale<T>(L, dd + kNB * (J - 1));
+            // C -= L_J,J-1 N (N holds minus D)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) C.b[h][q] = -C.b[h][q];
+            {
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+#pragma unroll
+                        for (int h = 0; h < 2; ++h)
+#pragma unroll
+                            for (int q = 0; q < 2; ++q) C.b[h][q] = MM<T>::mfma(L.b[p][h][v], N.b[p][q][v], C.b[h][q]);
+            }
+            // now C = -sum L D; N = -D_Jc = D_JJ sum = (-D_JJ) C
+            wait_for(&s_d, J + 1);
+            Blk<T> Dj;
+            blk_from_lds<T>(Dj, tiles + J * kTSz);   // -D_JJ(r, t)
+            blk_zero<T>(N);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+#pragma unroll
+                        for (int q = 0; q < 2; ++q) {
+                            if (h == 0 && p == 1) continue;   // D_JJ is lower triangular
+                            N.b[h][q] = MM<T>::mfma(Dj.b[p][h][v], C.b[p][q][v], N.b[h][q]);
+                        }
+            const int jb = min(kNB, w - kNB * J);
+            auto oD = glob(D + kNB * J + (int64_t)kNB * c * w);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int r = 16 * h + MM<T>::drow(v, lk);
+                        if (r < jb) oD[r + (int64_t)(16 * q + li) * w] = -N.b[h][q][v];
+                    }
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (the wave's later loads of D_Jc follow its stores)
+        }
     }
 }
 
@@ -1542,14 +1763,14 @@ __device__ __forceinline__ void finish_update(const SchedArgs& a, int j)
 // factored tile) between the two rows.
 constexpr int kSLd = kSmallRows + 1;   // leading dimension of the LDS panel copy
 static_assert(kSLd * kNB * sizeof(float) + (kSmallMap + 8 * kSmallMaxUpd) * sizeof(int) +
-                      kSmallMaxUpd * sizeof(int64_t) <= (kPbLd * kNB + 32) * sizeof(float),
+                      kSmallMaxUpd * sizeof(int64_t) <= (kTiles - 1) * kTSz * sizeof(double),
               "small-block tables exceed the LDS row buffer");
 static_assert((kSLd * kNB * sizeof(float) + (kSmallMap + 8 * kSmallMaxUpd) * sizeof(int)) % 8 == 0,
               "misaligned small-block offset table");
 static_assert(kSmallRows * kNB % kThreads == 0, "rows below per thread");
 
 template <class T, bool LDL = false>
-__device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const int4 d1, double* Lt, T* Dt, T* Pb)
+__device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const int4 d1, double* Lt, double* Dt, T* Pb)
 {
     const DevPlan& pl = a.pl;
     const int k = d0.y;
@@ -1590,19 +1811,19 @@ __device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const
     }
     __syncthreads();
     if (wave == 0) {
-        if (w <= 8)
-            tile_chol_inv<T, 8, LDL>(Lt, bc, Dt, w, f, a.status);
-        else if (w <= 16)
-            tile_chol_inv<T, 16, LDL>(Lt, bc, Dt, w, f, a.status);
-        else
-            tile_chol_inv<T, 32, LDL>(Lt, bc, Dt, w, f, a.status);
+        auto out = [&](int c, int ln, double x, double d) {
+            *(ln >= 32 ? lds(Dt) + c + 33 * (ln - 32) : lds(Lt) + ln + 33 * c) = (LDL && ln == c) ? d : x;
+        };
+        if (w <= 8) tile_chol_inv<8, LDL>(Lt, bc, w, f, a.status, out);
+        else if (w <= 16) tile_chol_inv<16, LDL>(Lt, bc, w, f, a.status, out);
+        else tile_chol_inv<32, LDL>(Lt, bc, w, f, a.status, out);
     }
     __syncthreads();
     for (int idx = tid; idx < kNB * kNB; idx += kThreads) {
         const int r = idx & 31, c = idx >> 5;
         if (r < w && c <= r) {
             A[r + (int64_t)c * ld] = (T)Lt[r + c * 33];
-            D[r + (int64_t)c * w] = Dt[r + c * 33];
+            D[r + (int64_t)c * w] = (T)Dt[r + c * 33];
         }
     }
     // rows below: P = A_off D^T, D lower triangular
@@ -1614,7 +1835,7 @@ __device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const
         double acc = 0.0;
         if (idx < R * w) {
             const int i = idx % R, c = idx / R;
-            for (int t = 0; t <= c; ++t) acc += (double)S[(w + i) + t * kSLd] * (double)Dt[c + t * 33];
+            for (int t = 0; t <= c; ++t) acc += (double)S[(w + i) + t * kSLd] * (double)(T)Dt[c + t * 33];
         }
         p[q] = acc;
     }
@@ -1665,8 +1886,11 @@ template <class T, bool LDL = false, bool LU = false>
 __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
 {
     __shared__ double Lt[kNB * 33 + 3 * kNB + 1];   // tile, bc, small-item pivots, pivot threshold
-    __shared__ T Dt[kNB * 33];
-    __shared__ __align__(16) T Pb[kPbLd * kNB + 32];   // + padding: tile row indices up to 255; small-block tables
+    // the tiles of a diagonal block; as elements of T, rows of a block or
+    // tile and the small-block tables, followed by one tile
+    __shared__ __align__(16) double tiles[kTiles * kTSz];
+    T* Pb = reinterpret_cast<T*>(tiles);
+    double* Dt = tiles + (kTiles - 1) * kTSz;
     __shared__ int rpos[256], cpos[128];
     __shared__ int s_item;
     __shared__ int s_push[6];   // {hp first, hp count, hp base, normal first, normal count, normal base}
@@ -1740,8 +1964,8 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
         const bool thin = (d0.x & kThinItem) != 0;
         if (kind == kFact) {
             __builtin_amdgcn_s_setprio(3);
-            if constexpr (LU) task_fact_lu<T>(a, d0.y, Lt, Dt, Pb);
-            else task_fact<T, LDL>(a, d0.y, Lt, Dt, Pb);
+            if constexpr (LU) task_fact_lu<T>(a, d0.y, Lt, reinterpret_cast<T*>(Dt), Pb);
+            else task_fact<T, LDL>(a, d0.y, Lt, tiles);
             __builtin_amdgcn_s_setprio(0);
         } else if (kind == kTrsm) {
             __builtin_amdgcn_s_setprio(2);

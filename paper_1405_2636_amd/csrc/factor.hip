@@ -662,88 +662,113 @@ __device__ __forceinline__ void tile_chol_inv(double* Lt_g, double* bc_g, int jb
     if (LDL && lane == 0 && tc.nrep > 0) atomicAdd(status + kStReplaced, tc.nrep);
 }
 
-// Small product of the diagonal-block factorization: acc += X Y^T with
-// X(i, p), i < 64, and Y(c, p), c < 16*NB, p < 32, given by loader functions
-// that load unconditionally (no masks: callers arrange that entries outside
-// the operands are zeros or only reach results that are not stored).  Fully
-// unrolled in two halves of 16: the operand loads of a half are issued
-// before its products.
-template <int NB, class T, class LX, class LY>
-__device__ __forceinline__ void wave_mm(typename MM<T>::acc (&acc)[NB][4], LX ldx, LY ldy)
-{
-    const int lane = threadIdx.x & 63;
-    const int li = lane & 15, lk = lane >> 4;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        T xs[4][4], ys[4][NB];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int p = 16 * h + 4 * q + lk;
-#pragma unroll
-            for (int b = 0; b < 4; ++b) xs[q][b] = ldx(16 * b + li, p);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) ys[q][b] = ldy(16 * b + li, p);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-#pragma unroll
-            for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = MM<T>::mfma(ys[q][bi], xs[q][bj], acc[bi][bj]);
+// L U factorization without pivoting (the static pivoting of Section III:
+// the elimination order is the analysis' order) of one 32x32 diagonal tile
+// and the two inverses the panel solves use, in FP64, by one wave.  Lt
+// (column-major, ld 33) holds the whole tile; rows and columns >= jb hold
+// the identity.  The tile is kept twice: lane r < 32 holds row r, lane
+// 32 + q holds column q (v); a second set of registers (z) holds column r of
+// X = L^{-1} in lane r and column q of Y = U^{-T} in lane 32 + q, starting
+// from unit vectors.  Step c: the pivot u_cc is broadcast by readlane; the
+// row lanes scale their entry of column c to l_rc = a_rc / u_cc, the column
+// lanes hold u_cq; both sets go to LDS (bc), and every lane updates
+//   row lane r     v_q -= l_rc u_cq,     column lane q  v_p -= u_cq l_pc,
+//   X lane         z_i -= l_ic z_c,      Y lane         z_i -= u_ci z_c (after z_c /= u_cc)
+// for the indices past c (fmac_rows: the operand in l or u from a fixed lane
+// of each row of 16).  Rows and columns up to c go on being updated; nothing
+// reads them.  Out: out(c, lane, x, z) with x = l_rc (rows r > c) or u_cq
+// (columns q >= c) and z = X(c, r) or Y(c, q), columns 0 .. jb - 1 rounded up
+// to a multiple of 8.  Static pivoting and breakdown as in L D L^T.
+// Bound: the multiply-adds (992 of 4.5 cycles) beside the chain of pivots
+// (about 100 cycles a column, the next pivot formed by readlanes).  The form
+// before it (two passes, a broadcast LDS read per multiply-add, the code
+// unrolled with a branch for each replaced pivot's retry) is part of the
+// 490 us of a 256-wide FACT below.
+template <class Out>
+struct TileLu {
+    double v[kNB], z[kNB];
+    double inv, d, y, thr;
+    int lane, jb, fail, nrep;
+    __attribute__((address_space(3))) double* bc;
+    Out out;
+
+    __device__ __forceinline__ void estimate(int c, double x)
+    {
+        d = readlane_d(x, c);
+        const bool rep = c < jb && fabs(d) < thr;
+        d = rep ? (d < 0.0 ? -thr : thr) : d;
+        nrep += rep ? 1 : 0;
+        fail = (c < jb && !(d != 0.0 && d - d == 0.0) && fail == 32) ? c : fail;
+        y = __builtin_amdgcn_rcp(d);
     }
-}
-
-// C(r, c) = f(old C(r, c), (X Y^T)(r, c)) for r < mv, c < nv, keep(r, c),
-// with C(r, c) at byte offset C.off + r*C.si + c*C.sk of C's array; each
-// offset is a per-lane part plus a wave-uniform part (scalar offset).  FP32
-// requests the old values first, so that their latency overlaps the
-// products; FP64 requests them all after the products (held across them, the
-// old values and the accumulators exceed the registers and spill).  The
-// stores are unconditional, masked elements going to an offset past the
-// array where the hardware drops them: with a branch there the compiler
-// sinks the loads of the old values into it, one round trip per element.
-template <int NB, class T, class LX, class LY, class Keep, class F, class Also>
-__device__ __forceinline__ void wave_mm_rmw(LX ldx, LY ldy, int mv, int nv, const GOp& C, Keep keep, F f, Also also)
-{
-    const int lane = threadIdx.x & 63;
-    const int li = lane & 15, lk = lane >> 4;
-    // drow(v, lk) = MM<T>::drow(0, lk) + MM<T>::drow(v, 0)
-    const int vl = C.off + li * C.si + MM<T>::drow(0, lk) * C.sk;
-    auto voff = [&](int bi, int bj, int v) {
-        const int r = 16 * bj + li, c = 16 * bi + MM<T>::drow(v, lk);
-        return (r < mv && c < nv && keep(r, c)) ? vl : kOffNone;
-    };
-    auto soff = [&](int bi, int bj, int v) { return uni(16 * bj * C.si + (16 * bi + MM<T>::drow(v, 0)) * C.sk); };
-    T old[NB][4][4];
-    auto load_old = [&]() {
-#pragma unroll
-        for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 4; ++bj)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) old[bi][bj][v] = gload_s(C, voff(bi, bj, v), soff(bi, bj, v), T(0));
-    };
-    if constexpr (sizeof(T) == 4) load_old();
-    typename MM<T>::acc acc[NB][4];
-    zero_acc(acc);
-    wave_mm<NB, T>(acc, ldx, ldy);
-    if constexpr (sizeof(T) == 8) load_old();
-#pragma unroll
-    for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-        for (int bj = 0; bj < 4; ++bj)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const T nv_ = f(old[bi][bj][v], acc[bi][bj][v]);
-                gstore_s(C, voff(bi, bj, v), soff(bi, bj, v), nv_);
-                also(16 * bj + li, 16 * bi + MM<T>::drow(v, lk), nv_);
+    __device__ __forceinline__ void finish()
+    {
+        const double e = __builtin_fma(-d, y, 1.0);
+        inv = __builtin_fma(y, __builtin_fma(e, e, e), y);
+    }
+    template <int C>
+    __device__ __forceinline__ void columns()
+    {
+        const bool upper = lane >= 32;
+        const double t = v[C];
+        const double x0 = t * inv;
+        double x = upper ? t : x0;
+        const double zc = upper ? z[C] * inv : z[C];
+        const double m = -x, mz = -zc;
+        // (a replaced pivot: u_cc itself)
+        if (lane == 32 + C) x = d;
+        if constexpr (C + 1 < kNB) {
+            bc[lane] = x;
+            const double e = __builtin_fma(-x0, readlane_d(t, 33 + C), v[C + 1]);   // row lane C+1: the next pivot
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            // LDS operations of one wave complete in order: the reads see column C
+            const int o = lane & 15, ow = (upper ? 0 : 32) + o, oz = (upper ? 32 : 0) + o;
+            double w0 = 0.0, u0 = 0.0;
+            if constexpr (C + 1 < 16) { w0 = bc[ow]; u0 = bc[oz]; }
+            const double w1 = bc[ow + 16], u1 = bc[oz + 16];
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+            estimate(C + 1, e);
+            out(C, lane, x, zc);
+            finish();
+            if constexpr (C + 1 < 16) {
+                fmac_rows<C + 1, 15 - C>(v, C + 1, w0, m);
+                fmac_rows<C + 1, 15 - C>(z, C + 1, u0, mz);
             }
+            constexpr int i = C + 1 > 16 ? C + 1 : 16;
+            fmac_rows<i - 16, kNB - i>(v, i, w1, m);
+            fmac_rows<i - 16, kNB - i>(z, i, u1, mz);
+            if constexpr ((C & 7) == 7) {
+                if (jb <= C + 1) return;
+            }
+            columns<C + 1>();
+        } else {
+            out(C, lane, x, zc);
+        }
+    }
+};
+
+template <class Out>
+__device__ __forceinline__ void tile_lu_inv(double* Lt_g, double* bc_g, int jb, int col0, int32_t* status, Out out)
+{
+    auto Lt = lds(Lt_g);
+    int lane = threadIdx.x & 63;
+    asm volatile("" : "+v"(lane));   // (keeps the lane masks of the columns from being formed ahead and held)
+    const int r = lane & 31;
+    TileLu<Out> tc{{}, {}, 0.0, 0.0, 0.0, readlane_d(lds(bc_g)[kThrSlot], 0), lane, jb, 32, 0, lds(bc_g), out};
+    const int base = lane >= 32 ? 33 * r : r, step = lane >= 32 ? 1 : 33;
+#pragma unroll
+    for (int c = 0; c < kNB; ++c) tc.v[c] = Lt[base + c * step];
+#pragma unroll
+    for (int c = 0; c < kNB; ++c) tc.z[c] = c == r ? 1.0 : 0.0;
+    tc.estimate(0, tc.v[0]);
+    tc.finish();
+    tc.template columns<0>();
+    if (lane == 0 && tc.fail < jb) atomicMin(status, col0 + tc.fail);
+    if (lane == 0 && tc.nrep > 0) atomicAdd(status + kStReplaced, tc.nrep);
 }
 
-constexpr int kPbLd = 228;   // leading dimension of the LDS copy of the rows below a tile (<= 224 rows)
 constexpr int kTSz = kNB * 33;                 // a 32x32 tile in LDS, column-major, ld 33
 constexpr int kTiles = 256 / kNB;              // tiles of the widest block: the LDS buffer of every item but FACT's own
-static_assert((kTiles - 1) * kTSz >= kPbLd * kNB + 32, "row buffer");
 
 // A 32x32 block held by one wave, in the form of the matrix cores' results:
 // b[h][q][v] of lane l holds M(16 q + l%16, 16 h + drow(v, l/16)).  As the
@@ -805,6 +830,56 @@ __device__ __forceinline__ void blk_mul(Blk<T>& C, const Blk<T>& X, const Blk<T>
                     if (YTRI && h == 0 && p == 1) continue;
                     C.b[h][q] = MM<T>::mfma(Y.b[p][h][v], X.b[p][q][v], C.b[h][q]);
                 }
+}
+
+// C += X Y with the result and Y transposed in the lanes (b[h][q][v] of lane
+// l: row 16 h + drow(v, l/16), column 16 q + l%16); XTRI: X is lower triangular
+template <class T, bool XTRI>
+__device__ __forceinline__ void blk_mul_t(Blk<T>& C, const Blk<T>& X, const Blk<T>& Y)
+{
+#pragma unroll
+    for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (XTRI && h == 0 && p == 1) continue;
+                    C.b[h][q] = MM<T>::mfma(X.b[p][h][v], Y.b[p][q][v], C.b[h][q]);
+                }
+}
+
+template <class T>
+__device__ __forceinline__ void blk_sub(Blk<T>& m, const Blk<T>& o)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) m.b[h][q] -= o.b[h][q];
+}
+
+template <class T>
+__device__ __forceinline__ void blk_neg(Blk<T>& m)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q) m.b[h][q] = -m.b[h][q];
+}
+
+// the block to memory, rows < mv: M(r, c) at out[r sr + c sc]
+template <class T, class P>
+__device__ __forceinline__ void blk_store(const Blk<T>& m, P out, int64_t sr, int64_t sc, int mv)
+{
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                if (16 * q + li < mv) out[(16 * q + li) * sr + (16 * h + MM<T>::drow(v, lk)) * sc] = m.b[h][q][v];
 }
 
 // a tile in LDS (column-major, ld 33) as a block, M(c, p) = tile[c + 33 p]
@@ -907,6 +982,72 @@ __device__ __forceinline__ void publish_lds(int* flag_g, int value)
     __hip_atomic_store(lds(flag_g), value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
+// Block column c of the inverse D of a lower triangular w x w block L (its
+// blocks below the diagonal at gL), below the tile D_cc:
+//   D_Jc = -D_JJ sum_{c<=K<J} L_JK D_Kc,   J = c+1 .. nb-1,
+// by one wave.  Every product is formed transposed in the lanes, so that its
+// result is the operand of the next one; the last D_Kc stays in registers,
+// the earlier ones are read back (the wave's own stores).  DS: L_JK d_K in
+// place of L_JK (d in LDS).  LDSD: -D_JJ from LDS (tiles); otherwise D_JJ
+// from memory.
+template <class T, bool DS, bool LDSD>
+__device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, int w, int nb, int c, int* s_x, int* s_d,
+                                           const double* tiles, const double* dd)
+{
+    const int lane = threadIdx.x & 63, li = lane & 15, lk = lane >> 4;
+    GOp gDt = gD;   // D^T(i, p) = D(p, i)
+    gDt.si = gD.sk;
+    gDt.sk = gD.si;
+    Blk<T> N;   // -D_Kc of the last step, as an operand over its rows
+    wait_for(&s_x[c], c + 1);   // D_cc in memory (and its tile in LDS)
+    if constexpr (LDSD) {
+        auto tile = lds(tiles + c * kTSz);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) N.b[h][q][v] = (T)tile[16 * h + MM<T>::drow(v, lk) + 33 * (16 * q + li)];
+    } else {
+        blk_load<T>(N, gDt, kNB * c, kNB * c);
+        blk_neg<T>(N);
+    }
+    for (int J = c + 1; J < nb; ++J) {
+        wait_for(&s_x[J], LDSD ? J : J + 1);
+        Blk<T> C, L;
+        blk_zero<T>(C);
+        // minus the sum: K < J - 1 from memory, then K = J - 1
+        blk_gemm<T, true, DS>(C, gL, kNB * J, kNB * c, gDt, kNB * c, kNB * c, J - 1 - c, dd + kNB * c);
+        blk_load<T>(L, gL, kNB * J, kNB * (J - 1));
+        if (DS) blk_scale<T>(L, dd + kNB * (J - 1));
+        blk_neg<T>(C);
+        blk_mul_t<T, false>(C, L, N);
+        // N = -D_Jc = (-D_JJ) (minus the sum)
+        Blk<T> Dj;
+        if constexpr (LDSD) {
+            wait_for(s_d, J + 1);
+            blk_from_lds<T>(Dj, tiles + J * kTSz);
+        } else {
+            blk_load<T>(Dj, gD, kNB * J, kNB * J);
+            blk_neg<T>(Dj);
+        }
+        blk_zero<T>(N);
+        blk_mul_t<T, true>(N, Dj, C);
+        const int jb = min(kNB, w - kNB * J);
+        auto oD = glob(D + kNB * J + (int64_t)kNB * c * w);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < 2; ++q)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int r = 16 * h + MM<T>::drow(v, lk);
+                    if (r < jb) oD[r + (int64_t)(16 * q + li) * w] = -N.b[h][q][v];
+                }
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (the wave's later loads of D_Jc follow its stores)
+    }
+}
+
 // Cholesky factorization of the w x w diagonal block (w <= 256) of panel k
 // and the inverse D = L_kk^{-1}, by one workgroup.  The block is cut into
 // row blocks of 32; wave v owns the row blocks v, v + 4, ...  Row block i is
@@ -946,7 +1087,6 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
     T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
     T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
     const GOp gA = make_gop(A, ld * w, 0, 1, ld);           // A(i, p) at i + p*ld
-    const GOp gDt = make_gop(D, (int64_t)w * w, 0, w, 1);   // D^T(i, p) = D(p, i)
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     double* bc = Lt + kNB * 33;
     __shared__ int s_x[8], s_d;      // blocks of row block i published (i + 1: D_ii too); tiles factored
@@ -980,20 +1120,9 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
             Blk<T> Y;
             blk_from_lds<T>(Y, tiles + J * kTSz);
             blk_zero<T>(X);
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) C.b[h][q] -= B.b[h][q];
+            blk_sub<T>(C, B);
             blk_mul<T, false, true>(X, C, Y);   // (sum - A) (-D)^T
-            auto out = glob(A);
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-                        if (16 * q + li < jb)
-                            out[(i0 + 16 * q + li) + (int64_t)(kNB * J + 16 * h + MM<T>::drow(v, lk)) * ld] = X.b[h][q][v];
+            blk_store<T>(X, glob(A + i0 + (int64_t)kNB * J * ld), 1, ld, jb);
             if (LDL) {
                 Blk<T> Xd = X;
                 blk_scale<T>(Xd, dd + kNB * J);
@@ -1044,72 +1173,7 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
     // the short columns 4 .. 6 go to the waves 3, 2, 1
     for (int t = 0; t < 2; ++t) {
         const int c = t == 0 ? wave : 7 - wave;
-        if (c + 1 >= nb) continue;
-        Blk<T> N;   // -D_Kc of the last step, as an operand over its rows
-        for (int J = c + 1; J < nb; ++J) {
-            wait_for(&s_x[J], J);
-            Blk<T> C;
-            blk_zero<T>(C);
-            // sum over K < J - 1 from memory (this wave's own stores)
-            if (J == c + 1) {
-                wait_for(&s_x[c], c + 1);   // (its tile -D_cc in LDS, D_cc in memory)
-                auto tile = lds(tiles + c * kTSz);
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) N.b[h][q][v] = (T)tile[16 * h + MM<T>::drow(v, lk) + 33 * (16 * q + li)];
-            } else {
-                blk_gemm<T, true, LDL>(C, gA, kNB * J, kNB * c, gDt, kNB * c, kNB * c, J - 1 - c, dd + kNB * c);
-            }
-            Blk<T> L;
-            blk_load<T>(L, gA, kNB * J, kNB * (J - 1));
-            if (LDL) blk_scale<T>(L, dd + kNB * (J - 1));
-            // C -= L_J,J-1 N (N holds minus D)
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int q = 0; q < 2; ++q) C.b[h][q] = -C.b[h][q];
-            {
-#pragma unroll
-                for (int p = 0; p < 2; ++p)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v)
-#pragma unroll
-                        for (int h = 0; h < 2; ++h)
-#pragma unroll
-                            for (int q = 0; q < 2; ++q) C.b[h][q] = MM<T>::mfma(L.b[p][h][v], N.b[p][q][v], C.b[h][q]);
-            }
-            // now C = -sum L D; N = -D_Jc = D_JJ sum = (-D_JJ) C
-            wait_for(&s_d, J + 1);
-            Blk<T> Dj;
-            blk_from_lds<T>(Dj, tiles + J * kTSz);   // -D_JJ(r, t)
-            blk_zero<T>(N);
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-#pragma unroll
-                        for (int q = 0; q < 2; ++q) {
-                            if (h == 0 && p == 1) continue;   // D_JJ is lower triangular
-                            N.b[h][q] = MM<T>::mfma(Dj.b[p][h][v], C.b[p][q][v], N.b[h][q]);
-                        }
-            const int jb = min(kNB, w - kNB * J);
-            auto oD = glob(D + kNB * J + (int64_t)kNB * c * w);
-#pragma unroll
-            for (int h = 0; h < 2; ++h)
-#pragma unroll
-                for (int q = 0; q < 2; ++q)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int r = 16 * h + MM<T>::drow(v, lk);
-                        if (r < jb) oD[r + (int64_t)(16 * q + li) * w] = -N.b[h][q][v];
-                    }
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (the wave's later loads of D_Jc follow its stores)
-        }
+        if (c + 1 < nb) inv_column<T, LDL, true>(gA, make_gop(D, (int64_t)w * w, 0, 1, w), D, w, nb, c, s_x, &s_d, tiles, dd);
     }
 }
 
@@ -1177,295 +1241,135 @@ __device__ __noinline__ void task_inv(const SchedArgs& a, int k, T* Pb)
 }
 
 // ---------------------------------------------------------------- FACT(k), L U
-// L U factorization without pivoting (the static pivoting of Section III:
-// the elimination order is the analysis' order) of one 32x32 diagonal tile
-// and the two inverses the panel solves use, in FP64, by one wave.  Lt
-// (column-major, ld 33) holds the whole tile; rows and columns >= jb hold
-// the identity.  Pass 1 keeps the tile twice: lane r < 32 holds row r, lane
-// 32 + q holds column q.  Step c: the pivot u_cc is broadcast by readlane;
-// the entries of column c below it become l_rc = a_rc / u_cc (in the row
-// lanes, and in column lane c); every lane puts one value in LDS (row lane r
-// its l_rc, column lane q its u_cq), so that row lane r > c updates
-// a_rq -= l_rc u_cq (q > c) with u_cq from LDS and column lane q > c updates
-// a_pq -= l_pc u_cq (p > c) with l_pc from LDS: the same operands in both
-// copies.  Pass 2, from L\U in Lt: lane q < 32 forms column q of
-// X = L^{-1} by forward substitution with the unit L (x_i -= l_ic x_c, i > c),
-// lane 32 + q column q of Y = U^{-T} by forward substitution with U^T
-// (y_c /= u_cc, then y_i -= u_ci y_c, i > c).  Out: L\U in Lt (unit L
-// strictly below the diagonal, U on and above), X in Dt (column-major, ld
-// 33), Y (rounded to T) in Yg[i + q*ldy] for q <= i < jb.  A zero or
-// non-finite pivot among the first jb records its column with atomicMin.
-//
-// Static pivoting as in tile_chol_inv: the common form (PIV false) tracks
-// the smallest |u_cc| and returns false, with Lt intact, when one is below
-// the threshold; the PIV form replaces.
-template <class T, bool PIV>
-__device__ __noinline__ bool tile_lu_inv_k(double* Lt, double* bc, T* Dt, T* Yg, int ldy, int jb, int col0,
-                                           int32_t* status)
-{
-    const double thr = readlane_d(bc[kThrSlot], 0);
-    double dmin = __builtin_inf();
-    const int lane = threadIdx.x & 63;
-    const int r = lane & 31;
-    const bool colh = lane >= 32;
-    double v[32], invp[32];   // invp: the inverse pivots (uniform), for pass 2
-#pragma unroll
-    for (int c = 0; c < 32; ++c) v[c] = colh ? Lt[c + r * 33] : Lt[r + c * 33];
-    // PIV: a replaced pivot only changes 1/u_cc here (the entries u_cc of
-    // lanes r == c are not read again by the loop) and is written to the
-    // tile's diagonal after it (uniform selects: a branch in the body stops
-    // the full unroll and sends the arrays to scratch)
-    const double ithr = PIV ? recip_nr(thr) : 0.0;
-    uint32_t repmask = 0;
-#pragma unroll
-    for (int c = 0; c < 32; ++c) {
-        const double d = readlane_d(v[c], c);   // row lane c: u_cc
-        double y = recip_nr(d);
-        if constexpr (PIV) {
-            const bool rp = c < jb && fabs(d) < thr;
-            y = rp ? (d < 0.0 ? -ithr : ithr) : y;
-            repmask |= rp ? 1u << c : 0u;
-        } else {
-            dmin = fmin(dmin, fabs(d));   // (identity padding: pivots 1)
-        }
-        invp[c] = y;
-        if (!colh && r > c) v[c] *= y;   // l_rc
-        // row lanes: l_rc (meaningful for r > c); column lanes: u_cq
-        bc[lane] = v[c];
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        // column lane c takes its scaled entries l_pc (p > c) from the row
-        // lanes' values, the others update
-        const double own = (r > c) ? v[c] : 0.0;
-        const bool take = colh && r == c;
-        const int bo = colh ? 0 : 32;
-#pragma unroll
-        for (int q = c + 1; q < 32; ++q) {
-            const double b = bc[bo + q];
-            v[q] = take ? b : v[q] - own * b;
-        }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if constexpr (!PIV) {
-        if (dmin < thr) return false;   // a pivot to replace: the caller runs the PIV form
-    }
-    // breakdown: a zero or non-finite pivot among the first jb (after replacement)
-    double dd = 0.0;
-#pragma unroll
-    for (int c = 0; c < 32; ++c) dd = (r == c) ? v[c] : dd;
-    const bool replaced = (repmask >> r) & 1u;
-    if (replaced) dd = dd < 0.0 ? -thr : thr;
-    const bool bad = !colh && r < jb && !(dd != 0.0 && dd - dd == 0.0);
-    const uint64_t m = __ballot(bad);
-    if (lane == 0 && m) atomicMin(status, col0 + (int)__builtin_ctzll(m));
-    if (lane == 0 && repmask) atomicAdd(status + kStReplaced, (int)__builtin_popcount(repmask));
-    if (!colh) {
-#pragma unroll
-        for (int c = 0; c < 32; ++c) Lt[r + c * 33] = v[c];
-        if (replaced) Lt[r + r * 33] = dd;
-    }
-    __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    // pass 2: X (lanes < 32) and Y (lanes >= 32), column r of each
-#pragma unroll
-    for (int i = 0; i < 32; ++i) v[i] = i == r ? 1.0 : 0.0;
-#pragma unroll
-    for (int c = 0; c < 32; ++c) {
-        if (colh) v[c] *= invp[c];
-        const double xc = v[c];
-        // coefficient i: U(c, i) at c + 33 i for the Y lanes, L(i, c) at i + 33 c for the X lanes
-        const int base = colh ? c : 33 * c, step = colh ? 33 : 1;
-#pragma unroll
-        for (int i = c + 1; i < 32; ++i) v[i] -= Lt[base + i * step] * xc;
-        __builtin_amdgcn_sched_barrier(0);
-    }
-    if (!colh) {
-#pragma unroll
-        for (int c = 0; c < 32; ++c) Dt[c + r * 33] = c >= r ? (T)v[c] : T(0);
-    } else if (r < jb) {
-#pragma unroll
-        for (int c = 0; c < 32; ++c)
-            if (c >= r && c < jb) Yg[c + (int64_t)r * ldy] = (T)v[c];
-    }
-    return true;
-}
-
-template <class T>
-__device__ __forceinline__ void tile_lu_inv(double* Lt, double* bc, T* Dt, T* Yg, int ldy, int jb, int col0,
-                                            int32_t* status)
-{
-    if (!tile_lu_inv_k<T, false>(Lt, bc, Dt, Yg, ldy, jb, col0, status))
-        tile_lu_inv_k<T, true>(Lt, bc, Dt, Yg, ldy, jb, col0, status);
-}
-
 // L U factorization of the w x w diagonal block (w <= 256) of panel k, in
 // place in the L panel (unit L below the diagonal, U on and above), with the
 // inverses X = L_kk^{-1} (L inverse array) and Y = U_kk^{-T} (U inverse
-// array), both lower triangular, by one workgroup, right-looking over 32
-// columns at a time.  Step J (tile columns J .. J+jb):
-//   1. the tile, fully updated, is factored and inverted by wave 0
-//      (tile_lu_inv): L\U_JJ -> panel, X_JJ -> X, Y_JJ -> Y;
-//   2. rows below: P = A[J+jb:w, J:J+jb] Y_JJ^T (= L rows) -> panel and LDS;
-//      columns to the right, transposed: Q = A[J:J+jb, J+jb:w]^T X_JJ^T
-//      (= U^T rows) -> the panel's upper part (U_J,right); block rows J of
-//      the inverses: X_J[:, 0:J] = X_JJ X_J[:, 0:J], Y_J[:, 0:J] = Y_JJ Y_J[:, 0:J];
-//   3. trailing updates, 64x32 tiles dealt to the four waves:
-//      A[J+jb:, J+jb:] -= P Q^T (the whole square), X[J+jb:, 0:J+jb] -= P X_J
-//      and Y[J+jb:, 0:J+jb] -= Q Y_J (columns J .. J+jb written for the first
-//      time).  The wave taking tile 0 (which holds the next diagonal tile)
-//      writes it to LDS and factors it while the others go on.
-// P is read from LDS, Q and the inverses' block rows from global memory
-// (written by this workgroup earlier in the step).
+// array), both lower triangular, by one workgroup: the row-block pipeline of
+// task_fact with two sides.  Row block i holds its rows of L and its rows of
+// U^T, Z_iJ = U_Ji^T:
+//   L_iJ = (A_iJ - sum_{K<J} L_iK Z_JK^T) Y_JJ^T
+//   Z_iJ = (A_Ji^T - sum_{K<J} Z_iK L_JK^T) X_JJ^T,   J = 0 .. i-1,
+// then the tile A_ii - sum_K L_iK Z_iK^T is factored and inverted
+// (tile_lu_inv), and after the row blocks the block columns of both
+// inverses follow (inv_column with L, and with U^T).  -X_JJ and -Y_JJ of the
+// last four tiles are kept in LDS; earlier ones are read back from memory:
+// row block J+4 overwrites tile J's after row block J+3 is factored, so only
+// the row blocks up to J+3 take it from LDS.  At w = 256 in FP64 the
+// right-looking form before it took 490 us in a kernel of its own (FP32
+// 410), this one @LU256@.
 template <class T>
-__device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt, T* Dt, T* Pb)
+__device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt, double* tiles)
 {
-    typedef typename MM<T>::acc acc_t;
     const DevPlan& pl = a.pl;
-    const int f = pl.fcol[k];
-    const int w = pl.lcol[k] - f + 1;
+    const int f = uni(pl.fcol[k]);
+    const int w = uni(pl.lcol[k]) - f + 1;
     const int64_t ld = pl.stride[k];
     T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
     T* X = static_cast<T*>(a.dinv) + pl.dinv_off[k];
     T* Y = X + a.uinv;
-    const int64_t nA = ld * w, nD = (int64_t)w * w;
-    const GOp gA = make_gop(A, nA, 0, 1, ld);   // A(i, p) at i + p*ld
-    const GOp gX = make_gop(X, nD, 0, 1, w);
-    const GOp gY = make_gop(Y, nD, 0, 1, w);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const GOp gA = make_gop(A, ld * w, 0, 1, ld);    // A(i, p) at i + p*ld
+    const GOp gAt = make_gop(A, ld * w, 0, ld, 1);   // A^T
+    const GOp gX = make_gop(X, (int64_t)w * w, 0, 1, w), gY = make_gop(Y, (int64_t)w * w, 0, 1, w);
+    const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     double* bc = Lt + kNB * 33;
-    __shared__ int s_next;
-    bool ready = false;
-    for (int J = 0; J < w; J += kNB) {
-        const int jb = min(kNB, w - J);
-        const int R = w - J - jb;
-        if (!ready) {
-            for (int idx = tid; idx < kNB * kNB; idx += kThreads) {
-                const int r = idx & 31, c = idx >> 5;
-                Lt[r + c * 33] = (r < jb && c < jb) ? (double)A[(J + r) + (int64_t)(J + c) * ld] : (r == c ? 1.0 : 0.0);
+    __shared__ int s_x[8], s_d;   // blocks of row block i published (i + 1: its inverse tiles too); tiles factored
+    const int nb = (w + kNB - 1) / kNB;
+    if (tid < 8) s_x[tid] = 0;
+    if (tid == 8) s_d = 0;
+    __syncthreads();
+    for (int i = wave; i < nb; i += kThreads / 64) {
+        const int i0 = kNB * i, jb = min(kNB, w - i0);
+        Blk<T> S, XL, XU;
+        blk_zero<T>(S);
+        for (int J = 0; J < i; ++J) {
+            Blk<T> CL, CU;
+            blk_zero<T>(CL);
+            blk_zero<T>(CU);
+            if (J > 0) {
+                wait_for(&s_x[J], J - 1);
+                blk_gemm<T, false, false>(CL, gA, i0, 0, gAt, kNB * J, 0, J - 1, nullptr);
+                blk_gemm<T, false, false>(CU, gAt, i0, 0, gA, kNB * J, 0, J - 1, nullptr);
+                wait_for(&s_x[J], J);
+                Blk<T> Q;
+                blk_load<T>(Q, gAt, kNB * J, kNB * (J - 1));
+                blk_mul<T, false, false>(CL, XL, Q);
+                blk_load<T>(Q, gA, kNB * J, kNB * (J - 1));
+                blk_mul<T, false, false>(CU, XU, Q);
             }
-            __syncthreads();
-            if (wave == 0) tile_lu_inv<T>(Lt, bc, Dt, Y + J + (int64_t)J * w, w, jb, f + J, a.status);
-        }
-        if (tid == 0) s_next = 0;
-        __syncthreads();
-        for (int idx = tid; idx < kNB * kNB; idx += kThreads) {
-            const int r = idx & 31, c = idx >> 5;
-            if (r < jb && c < jb) {
-                A[(J + r) + (int64_t)(J + c) * ld] = (T)Lt[r + c * 33];
-                if (c <= r) X[(J + r) + (int64_t)(J + c) * w] = Dt[r + c * 33];
-            }
-        }
-        __syncthreads();   // Y_JJ (global, from wave 0) and the tile are in place
-        const int r0 = 64 * wave;
-        if (r0 < R) {
-            // 2a. P = A_rows Y_JJ^T (R > 0 implies jb = 32)
             {
-                acc_t acc[2][4];
-                zero_acc(acc);
-                const int gbase = gA.off + (J + jb + r0) * gA.si + J * gA.sk;
-                wave_mm<2, T>(acc, [&](int i, int p) { return gload<T>(gA, gbase + i * gA.si + p * gA.sk); },
-                              [&](int c, int p) { return gload<T>(gY, gY.off + (J + c) * gY.si + (J + p) * gY.sk); });
-                wave_store<T>(acc, min(64, R - r0), jb, [&](int r, int c, T v) {
-                    Pb[(r0 + r) + c * kPbLd] = v;
-                    A[(J + jb + r0 + r) + (int64_t)(J + c) * ld] = v;
-                });
+                Blk<T> B;
+                blk_load<T>(B, gA, i0, kNB * J);
+                blk_sub<T>(CL, B);
+                blk_load<T>(B, gAt, i0, kNB * J);
+                blk_sub<T>(CU, B);
             }
-            // 2a'. Q = A[J:J+jb, right]^T X_JJ^T, stored as U_J,right
-            {
-                acc_t acc[2][4];
-                zero_acc(acc);
-                wave_mm<2, T>(acc,
-                              [&](int i, int p) { return gload<T>(gA, gA.off + (J + p) * gA.si + (J + jb + r0 + i) * gA.sk); },
-                              [&](int c, int p) { return Dt[c + p * 33]; });
-                // (the upper rows of the inverse tile are zero: products over
-                // p > c vanish)
-                wave_store<T>(acc, min(64, R - r0), jb,
-                              [&](int r, int c, T v) { A[(J + c) + (int64_t)(J + jb + r0 + r) * ld] = v; });
-            }
-        }
-        // 2b. block rows J of X and Y for columns < J, in place; each wave a
-        // 64-column slice of one of them
-        for (int t = wave; t < 2 * ((J + 63) >> 6); t += kThreads / 64) {
-            const bool isY = (t & 1) != 0;
-            const int c0 = 64 * (t >> 1);
-            const GOp& g = isY ? gY : gX;
-            T* Z = isY ? Y : X;
-            acc_t acc[2][4];
-            zero_acc(acc);
-            if (isY)
-                wave_mm<2, T>(acc, [&](int i, int p) { return gload<T>(g, g.off + (J + p) * g.si + (c0 + i) * g.sk); },
-                              [&](int c, int p) { return gload<T>(gY, gY.off + (J + c) * gY.si + (J + p) * gY.sk); });
-            else
-                wave_mm<2, T>(acc, [&](int i, int p) { return gload<T>(g, g.off + (J + p) * g.si + (c0 + i) * g.sk); },
-                              [&](int c, int p) { return Dt[c + p * 33]; });
-            wave_store<T>(acc, min(64, J - c0), jb, [&](int r, int c, T v) { Z[(J + c) + (int64_t)(c0 + r) * w] = v; });
-        }
-        __syncthreads();
-        if (R == 0) break;
-        // 3. trailing updates: A tiles (rt, ct) over the whole R x R square,
-        // then X tiles and Y tiles (rt, ct), ct*32 < J + jb
-        const int nrt = (R + 63) >> 6, ncs = (R + 31) >> 5, nci = (J + jb + 31) >> 5;
-        const int nsq = nrt * ncs, ninv = nrt * nci;
-        const int ntiles = nsq + 2 * ninv;
-        const int jn = min(kNB, R);
-        for (;;) {
-            int t = 0;
-            if (lane == 0) t = atomicAdd(&s_next, 1);
-            t = __shfl(t, 0);
-            if (t >= ntiles) break;
-            auto sub = [](T o, T v) { return o - v; };
-            if (t < nsq) {
-                const int rt = t / ncs, ct = t - rt * ncs;
-                const int i0 = 64 * rt, c0 = 32 * ct;
-                const int mv = min(64, R - i0), nv = min(32, R - c0);
-                auto ldx = [&](int i, int p) { return Pb[(i0 + i) + p * kPbLd]; };
-                auto ldq = [&](int c, int p) {
-                    return gload<T>(gA, gA.off + (J + p) * gA.si + (J + jb + c0 + c) * gA.sk);
-                };
-                GOp cA = gA;
-                cA.off = uni(gA.off + (J + jb + i0) * gA.si + (J + jb + c0) * gA.sk);
-                if (t == 0) {
-                    for (int idx = lane; idx < kNB * kNB; idx += 64) {
-                        const int r = idx & 31, c = idx >> 5;
-                        Lt[r + c * 33] = r == c && r >= jn ? 1.0 : 0.0;
-                    }
-                    wave_mm_rmw<2, T>(
-                        ldx, ldq, mv, nv, cA, [](int, int) { return true; }, sub, [&](int r, int c, T v) {
-                            if (r < jn && c < jn) Lt[r + c * 33] = (double)v;
-                        });
-                    tile_lu_inv<T>(Lt, bc, Dt, Y + (J + jb) + (int64_t)(J + jb) * w, w, jn, f + J + jb, a.status);
-                } else {
-                    wave_mm_rmw<2, T>(ldx, ldq, mv, nv, cA, [](int, int) { return true; }, sub, [](int, int, T) {});
-                }
+            Blk<T> Q;
+            blk_zero<T>(XL);
+            blk_zero<T>(XU);
+            if (J + 3 >= i) {
+                wait_for(&s_d, J + 1);
+                blk_from_lds<T>(Q, tiles + (2 * (J & 3) + 1) * kTSz);
+                blk_mul<T, false, true>(XL, CL, Q);
+                blk_from_lds<T>(Q, tiles + 2 * (J & 3) * kTSz);
+                blk_mul<T, false, true>(XU, CU, Q);
             } else {
-                const bool isY = t >= nsq + ninv;
-                const int u = t - nsq - (isY ? ninv : 0);
-                const int rt = u / nci, ct = u - rt * nci;
-                const int i0 = 64 * rt, c0 = 32 * ct;
-                const int mv = min(64, R - i0), nv = min(32, J + jb - c0);
-                const GOp& g = isY ? gY : gX;
-                T* Z = isY ? Y : X;
-                auto ldy = [&](int c, int p) { return gload<T>(g, g.off + (J + p) * g.si + (c0 + c) * g.sk); };
-                auto ldp = [&](int i, int p) { return Pb[(i0 + i) + p * kPbLd]; };
-                auto ldqr = [&](int i, int p) {
-                    return gload<T>(gA, gA.off + (J + p) * gA.si + (J + jb + i0 + i) * gA.sk);
-                };
-                if (c0 >= J) {   // columns written for the first time
-                    acc_t acc[2][4];
-                    zero_acc(acc);
-                    if (isY) wave_mm<2, T>(acc, ldqr, ldy);
-                    else wave_mm<2, T>(acc, ldp, ldy);
-                    wave_store<T>(acc, mv, nv,
-                                  [&](int r, int c, T v) { Z[(J + jb + i0 + r) + (int64_t)(c0 + c) * w] = -v; });
-                } else {
-                    GOp cZ = g;
-                    cZ.off = uni(g.off + (J + jb + i0) * g.si + c0 * g.sk);
-                    if (isY) wave_mm_rmw<2, T>(ldqr, ldy, mv, nv, cZ, [](int, int) { return true; }, sub, [](int, int, T) {});
-                    else wave_mm_rmw<2, T>(ldp, ldy, mv, nv, cZ, [](int, int) { return true; }, sub, [](int, int, T) {});
-                }
+                wait_for(&s_x[J], J + 1);
+                blk_load<T>(Q, gY, kNB * J, kNB * J);
+                blk_neg<T>(Q);
+                blk_mul<T, false, true>(XL, CL, Q);
+                blk_load<T>(Q, gX, kNB * J, kNB * J);
+                blk_neg<T>(Q);
+                blk_mul<T, false, true>(XU, CU, Q);
+            }
+            blk_store<T>(XL, glob(A + i0 + (int64_t)kNB * J * ld), 1, ld, jb);
+            blk_store<T>(XU, glob(A + kNB * J + (int64_t)i0 * ld), ld, 1, jb);
+            blk_mul<T, false, false>(S, XL, XU);
+            publish(&s_x[i], J + 1);
+        }
+        // the tile, identity padded, to LDS; row block i-1 is done with Lt (s_d)
+        {
+            Blk<T> B;
+            blk_load<T>(B, gA, i0, i0);
+            auto L = lds(Lt);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) {
+                        const int r = 16 * q + li, c = 16 * h + MM<T>::drow(v, lk);
+                        L[r + 33 * c] = (r < jb && c < jb) ? (double)(B.b[h][q][v] - S.b[h][q][v]) : (r == c ? 1.0 : 0.0);
+                    }
+            __atomic_signal_fence(__ATOMIC_SEQ_CST);
+        }
+        auto Ti = lds(tiles + 2 * (i & 3) * kTSz);   // -X_ii, then -Y_ii
+        const int vL = uni(gA.off + i0 * gA.si + i0 * gA.sk), lim = jb;
+        auto out = [&](int c, int ln, double x, double z) {
+            // (masked entries go past the array, where the store is dropped)
+            const int r = ln & 31;
+            const int vo = ln >= 32 ? (r >= c && r < lim && c < lim ? c * gA.si + r * gA.sk : kOffNone)
+                                    : (r > c && r < lim && c < lim ? r * gA.si + c * gA.sk : kOffNone);
+            gstore_s(gA, vo, vL, (T)x);
+            Ti[(ln >= 32 ? kTSz : 0) + 33 * r + c] = -z;
+        };
+        tile_lu_inv(Lt, bc, jb, f + i0, a.status, out);
+        publish_lds(&s_d, i + 1);
+        auto oX = glob(X + (int64_t)i0 * (w + 1)), oY = glob(Y + (int64_t)i0 * (w + 1));
+        for (int idx = lane; idx < kNB * kNB; idx += 64) {
+            const int r = idx & 31, c = idx >> 5;
+            if (r < jb && c <= r) {
+                oX[r + (int64_t)c * w] = (T)-Ti[r + 33 * c];
+                oY[r + (int64_t)c * w] = (T)-Ti[kTSz + r + 33 * c];
             }
         }
-        __syncthreads();
-        ready = true;
+        publish(&s_x[i], i + 1);
+    }
+    // block columns 0 .. nb - 2 of both inverses, dealt as in task_fact
+    for (int t = 0; t < 4; ++t) {
+        const int c = (t & 2) == 0 ? wave : 7 - wave;
+        if (c + 1 >= nb) continue;
+        if ((t & 1) == 0) inv_column<T, false, false>(gA, gX, X, w, nb, c, s_x, &s_d, tiles, nullptr);
+        else inv_column<T, false, false>(gAt, gY, Y, w, nb, c, s_x, &s_d, tiles, nullptr);
     }
 }
 
@@ -1964,7 +1868,7 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
         const bool thin = (d0.x & kThinItem) != 0;
         if (kind == kFact) {
             __builtin_amdgcn_s_setprio(3);
-            if constexpr (LU) task_fact_lu<T>(a, d0.y, Lt, reinterpret_cast<T*>(Dt), Pb);
+            if constexpr (LU) task_fact_lu<T>(a, d0.y, Lt, tiles);
             else task_fact<T, LDL>(a, d0.y, Lt, tiles);
             __builtin_amdgcn_s_setprio(0);
         } else if (kind == kTrsm) {

@@ -150,7 +150,7 @@ struct spx_handle {
     DevBuf<int4> ftab;
     // deterministic mode: update pairs (see SchedArgs)
     int32_t npair = 0, ubase = 0;
-    int32_t ninv = 0;                 // INV items (chain blocks, L L^T)
+    int32_t ninv = 0;                 // INV items (chain blocks)
     DevBuf<int32_t> inv_item;
     DevBuf<int32_t> upair, kpair, pdep0, pdep, pleft;
     DevBuf<int4> pairs;
@@ -319,16 +319,27 @@ void build_tasks(spx_handle* h)
     std::vector<char> chain(nc, 0);
     for (int32_t k = 0; k < nc; ++k)
         chain[k] = per_level[lvl[k]] <= kChainLevel && P.lcol[k] - P.fcol[k] + 1 >= 128;
-    // L L^T blocks of width >= 128 in levels of at most kInvLevel blocks
-    // (high priority): FACT stores L_kk and the diagonal tiles of its inverse
-    // only, the panel solves are block substitutions with those tiles (64
-    // rows, 16 per wave), and an INV item in the normal queue forms the rest
-    // of the inverse (needed by the triangular sweeps only): the chain runs
-    // through about half the FACT products and none of the inverse's
-    constexpr int kInvLevel = 4;
+    // Blocks of width >= 128 in narrow levels (high priority): FACT stores the
+    // factor and the diagonal tiles of its inverse only, the panel solves are
+    // block substitutions with those tiles (16 rows, a workgroup each), and
+    // an INV item in the normal queue forms the rest of the inverse (needed
+    // by the triangular sweeps only): the chain runs through none of the
+    // inverse's products.  A level is narrow if it has at most kInvLevel
+    // blocks and its solves fit two rounds of the workgroups that run at
+    // once: more of them wait for each other, and the product with the whole
+    // inverse is the shorter way.  Scheduler kernel with at most 128, 256,
+    // 512, 1024 solves: 100^3 90.1, 89.6, 89.5, 89.5 ms (92.1 without the
+    // limit), 50x47x49 L U 12.4, 12.0, 12.0, 11.4, 72x70x69 19.6, 19.3, 19.3,
+    // 18.6.
+    constexpr int kInvLevel = 8;
+    constexpr int64_t kInvSolves = 1024;
+    std::vector<int64_t> solves(static_cast<size_t>(nc) + 1, 0);
+    for (int32_t k = 0; k < nc; ++k)
+        if (P.lcol[k] - P.fcol[k] + 1 >= 128)
+            solves[lvl[k]] += (P.stride[k] - (P.lcol[k] - P.fcol[k] + 1) + 15) / 16 * (h->lu() ? 2 : 1);
     std::vector<char> inv(nc, 0);
     for (int32_t k = 0; k < nc; ++k)
-        inv[k] = h->opt.method == SPX_LLT && hp[k] && per_level[lvl[k]] <= kInvLevel && P.lcol[k] - P.fcol[k] + 1 >= 128;
+        inv[k] = hp[k] && per_level[lvl[k]] <= kInvLevel && solves[lvl[k]] <= kInvSolves && P.lcol[k] - P.fcol[k] + 1 >= 128;
     // update tiles of source k into target group [b, b2) (blocks facing one
     // cblk), tr x tcl each
     auto for_tiles = [&](int32_t k, int32_t b, int32_t b2, int32_t tr, int32_t tcl, auto&& fn) {
@@ -410,13 +421,14 @@ void build_tasks(spx_handle* h)
         tf[k] = id;
         // 64 rows per wave tile (chains: 16); panels narrower than 256
         // columns stack 4/ceil(w/64) of them
-        const int32_t trows = inv[k] ? 64 : (chain[k] ? 16 : kTrsmRows) * (4 / ((w + 63) / 64));
+        const int32_t trows = inv[k] ? 16 : (chain[k] ? 16 : kTrsmRows) * (4 / ((w + 63) / 64));
         const int32_t tflag = inv[k] ? kSubstItem : (chain[k] ? kThinItem : 0);
-        for (int32_t r = w; r < ld && !small[k]; r += trows) {
-            desc.push_back(int4{kTrsm | tflag, k, r, std::min(trows, ld - r)});
-            desc.push_back(int4{0, 0, 0, 0});
-            ++id;
-        }
+        for (int32_t r = w; r < ld && !small[k]; r += trows)
+            for (int32_t side = 0; side < (inv[k] && h->lu() ? 2 : 1); ++side) {   // (L U: L rows, U^T rows)
+                desc.push_back(int4{kTrsm | tflag | (side ? kUSideItem : 0), k, r, std::min(trows, ld - r)});
+                desc.push_back(int4{0, 0, 0, 0});
+                ++id;
+            }
         tc[k] = id - tf[k];
     }
     int64_t nhp_upd = 0;

@@ -25,7 +25,8 @@ struct DevPlan {
 // TRSM or update item of an elimination chain: 16-row wave tiles).
 enum ItemKind : int32_t { kFact = 0, kTrsm = 1, kUpdate = 2, kSmall = 3, kInv = 4 };
 constexpr int32_t kThinItem = 1 << 12;
-constexpr int32_t kSubstItem = 1 << 13;   // TRSM of a chain block: substitution with the diagonal tiles of D
+constexpr int32_t kSubstItem = 1 << 13;   // TRSM of a chain block: substitution with the diagonal tiles of D (16 rows)
+constexpr int32_t kUSideItem = 1 << 14;   // (L U) such an item of the U^T rows; else of the L rows
 
 // Two int4 per item: {kind, k, a, b}, {c, d, e, f}
 //   kFact:   k
@@ -71,7 +72,7 @@ struct SchedArgs {
     // Deterministic mode (npair > 0): the update items of one (source,
     // target) pair are released when the source's panel solves are done and
     // the previous pair into the same target (ascending source) has finished.
-    // Blocks of elimination chains (L L^T): FACT leaves the off-diagonal tiles
+    // Blocks of elimination chains: FACT leaves the off-diagonal tiles
     // of the inverse to an INV item, released with the panel solves (which
     // use the diagonal tiles only) and off the chain.
     const int32_t* inv_item;   // INV item of block k, or -1 (FACT computes the whole inverse)

@@ -548,52 +548,159 @@ __device__ __forceinline__ void fmac_rows(double (&acc)[NV], int at, double b, d
 // i > c (fmac_rows).  For a row of the tile that is the Cholesky update of
 // its remaining columns; for a column of X it is the forward substitution
 // step x_iq -= l_ic x_cq after x_cq was divided by l_cc.  A pivot that is not
-// > 0 records its column with atomicMin (NaN propagates).  Column c goes out
-// as soon as it is final, by out(c, lane, x, d): in the lower half of the
-// wave x = l_rc of row r = lane (r < c: an undefined value; L D L^T: 1 for
-// r = c, and d is the pivot), in the upper half x = x_cr of column
-// r = lane - 32 (r > c: zero).  Columns 0 .. jb - 1, rounded up to a
-// multiple of 8, go out; NC (8, 16 or 32, >= jb) bounds them.
+// > 0 records its column with atomicMin (NaN propagates).  Result in
+// registers: v[c] of lane r < 32 is l_rc for r >= c (undefined above the
+// diagonal), of lane 32 + q it is x_cq (zero for q > c), columns 0 .. jb - 1;
+// NC (8, 16 or 32, >= jb) bounds them.
 //
-// What bounds it is the chain from one pivot to the next: 94 cycles a
-// column (readlane, estimate, one third-order step, scaling, readlane,
-// multiply-add), with the updates of the later columns in its gaps.  The
-// next column is updated by a readlane of l_{c+1,c}, so that its pivot does
-// not wait for the LDS round trip of the others.  A tile alone on the chip
-// takes 12,000 cycles; a form that read l_ic from LDS for every update and
-// branched around each load of Lt took 38,400.
+// What bounds it is the chain from one pivot to the next, 94 cycles a column
+// (readlane, multiply-add, readlane, estimate, one third-order step,
+// scaling), and the issue of the multiply-adds.  The next column is updated
+// by a readlane of l_{c+1,c}, so that its pivot does not wait for the LDS
+// round trip of the others, and the updates of the columns after it are put,
+// four at a time, into the gaps of the next column's chain (column() below
+// is in the order of issue, held by scheduling barriers: the compiler puts
+// them behind the chain).  A tile alone on the chip takes 10,300 cycles,
+// 12,000 with the updates behind the chain; a form that read l_ic from LDS
+// for every update and branched around each load of Lt took 38,400.
 //
 // LDL = true: the L D L^T form of the same pass (unit L): the pivot d is
 // not square-rooted (a breakdown is a zero or non-finite d), a row keeps the
-// unscaled value t of column c for its update (a_ri -= t l_ic) and puts out
-// t / d (d itself on the diagonal); on the identity rows the same steps give
-// Y = D^{-1} L^{-1}.  Static pivoting: a pivot with |d| below the threshold
-// is replaced by +-threshold (a select beside the reciprocal) and counted.
-template <int NC, bool LDL, class Out>
+// unscaled value t of column c for its update (a_ri -= t l_ic) and ends as
+// t / d (1 on the diagonal; the pivots go to dg[0..]); on the identity rows
+// the same steps give Y = D^{-1} L^{-1}.  Static pivoting: a pivot with |d|
+// below the threshold is replaced by +-threshold (a select beside the
+// reciprocal) and counted.
+template <int NC, bool LDL>
 struct TileChol {
     double v[NC];
-    double inv, d, y, thr;   // 1/l_cc (1/d) of the current column; the pivot d in work and its estimate
-    int lane, jb, fail, nrep;
-    __attribute__((address_space(3))) double* bc;
-    Out out;
+    double inv, d, y, thr;     // 1/l_cc (1/d) of the current column; the pivot d in work and its estimate
+    double b0, b1, m;          // the last column's entries (rows 0..15, 16..31 in every row of lanes), minus its factor
+    int lane, jb;
+    uint32_t bad, rep;         // columns with a failed (replaced) pivot
+    __attribute__((address_space(3))) double *bc, *dg;
 
-    // d and the hardware estimate y of 1/sqrt(d) (1/d) from column c
-    __device__ __forceinline__ void estimate(int c, double x)
+    // d and the hardware estimate y of 1/sqrt(d) (1/d) of column C
+    template <int C>
+    __device__ __forceinline__ void estimate()
     {
-        d = readlane_d(x, c);
         if constexpr (LDL) {
-            const bool rep = c < jb && fabs(d) < thr;
-            d = rep ? (d < 0.0 ? -thr : thr) : d;
-            nrep += rep ? 1 : 0;
-            fail = (c < jb && !(d != 0.0 && d - d == 0.0) && fail == 32) ? c : fail;
+            const bool small = C < jb && fabs(d) < thr;
+            d = small ? (d < 0.0 ? -thr : thr) : d;
+            rep |= small ? 1u << C : 0u;
             y = __builtin_amdgcn_rcp(d);
         } else {
-            fail = (c < jb && !(d > 0.0) && fail == 32) ? c : fail;
             y = __builtin_amdgcn_rsq(d);
         }
     }
-    __device__ __forceinline__ void finish()
+    template <int C>
+    __device__ __forceinline__ void check()
     {
+        if constexpr (LDL) {
+            bad |= !(d != 0.0 && d - d == 0.0) ? 1u << C : 0u;
+            dg[C] = d;
+        } else {
+            bad |= !(d > 0.0) ? 1u << C : 0u;
+        }
+    }
+    // the last column's updates of v[A .. B - 1]
+    template <int A, int B0>
+    __device__ __forceinline__ void update()
+    {
+        constexpr int B = B0 < NC ? B0 : NC;
+        constexpr int lo = A < 16 ? (B < 16 ? B : 16) : A;
+        if constexpr (A < lo) fmac_rows<A, lo - A>(v, A, b0, m);
+        if constexpr (lo < B && B > 16) fmac_rows<lo - 16, B - lo>(v, lo, b1, m);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    // column C; v[C] is final but for its scaling, the last column's updates
+    // of the columns C + 1 .. are still to be made
+    template <int C>
+    __device__ __forceinline__ void column()
+    {
+        const double t = v[C], x = t * inv;   // lane C: l_cc = d / sqrt(d) (L D L^T: 1)
+        if constexpr (C + 1 >= NC) {
+            v[C] = x;
+            return;
+        } else {
+            if constexpr (C + 2 < NC) bc[lane] = x;
+            const double mc = LDL ? -t : -x;   // minus the factor of this column's updates
+            const double l1 = readlane_d(x, C + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (C > 0) update<C + 1, C + 5>();
+            v[C] = x;
+            v[C + 1] = __builtin_fma(mc, l1, v[C + 1]);
+            __builtin_amdgcn_sched_barrier(0);
+            double n0 = 0.0, n1 = 0.0;
+            if constexpr (C + 2 < NC) {   // LDS operations of one wave complete in order: the reads see column C
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                if constexpr (C + 2 < 16) n0 = bc[lane & 15];
+                if constexpr (NC > 16) n1 = bc[16 + (lane & 15)];
+                __atomic_signal_fence(__ATOMIC_SEQ_CST);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (C > 0) update<C + 5, C + 7>();
+            d = readlane_d(v[C + 1], C + 1);
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (C > 0) update<C + 7, C + 11>();
+            estimate<C + 1>();
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (C > 0) update<C + 11, C + 15>();
+            if constexpr (LDL) {
+                const double e = __builtin_fma(-d, y, 1.0);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (C > 0) update<C + 15, C + 19>();
+                const double q = __builtin_fma(e, e, e);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (C > 0) update<C + 19, C + 23>();
+                inv = __builtin_fma(y, q, y);
+            } else {
+                const double g = d * y;
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (C > 0) update<C + 15, C + 17>();
+                const double e = __builtin_fma(-g, y, 1.0);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (C > 0) update<C + 17, C + 21>();
+                const double q = e * y, p = __builtin_fma(e, 0.375, 0.5);
+                __builtin_amdgcn_sched_barrier(0);
+                if constexpr (C > 0) update<C + 21, C + 23>();
+                inv = __builtin_fma(q, p, y);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+            if constexpr (C > 0) update<C + 23, NC>();
+            check<C + 1>();
+            b0 = n0;
+            b1 = n1;
+            m = mc;
+            if constexpr ((C & 7) == 7) {
+                if (jb <= C + 1) return;
+            }
+            column<C + 1>();
+        }
+    }
+    __device__ __forceinline__ void run(double* Lt_g, double* bc_g, double* dg_g, int jb_, int col0, int32_t* status)
+    {
+        static_assert(NC == 8 || NC == 16 || NC == 32, "tile width");
+        auto Lt = lds(Lt_g);
+        bc = lds(bc_g);
+        dg = lds(dg_g);
+        jb = jb_;
+        bad = rep = 0;
+        thr = LDL ? readlane_d(bc[kThrSlot], 0) : 0.0;
+        lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));   // (keeps the columns' lane masks from being formed ahead and held)
+        const int r = lane & 31;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[c] = Lt[r + c * 33];
+        // (all loads issued before the selects: a conditional load is a branch each)
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            asm volatile("" : "+v"(v[c]));
+            v[c] = lane >= 32 ? (c == r ? 1.0 : 0.0) : v[c];
+        }
+        d = readlane_d(v[0], 0);
+        estimate<0>();
         if constexpr (LDL) {
             const double e = __builtin_fma(-d, y, 1.0);
             inv = __builtin_fma(y, __builtin_fma(e, e, e), y);
@@ -601,66 +708,32 @@ struct TileChol {
             const double e = __builtin_fma(-(d * y), y, 1.0);
             inv = __builtin_fma(e * y, __builtin_fma(e, 0.375, 0.5), y);
         }
+        check<0>();
+        column<0>();
+        const uint32_t in = jb >= 32 ? ~0u : (1u << jb) - 1;
+        if (lane == 0 && (bad & in)) atomicMin(status, col0 + __builtin_ctz(bad & in));
+        if (LDL && lane == 0 && rep) atomicAdd(status + kStReplaced, __builtin_popcount(rep));
     }
-    template <int C>
-    __device__ __forceinline__ void columns()
+    // the inverse times s to an LDS tile: X(c, q) at tile[c + 33 q]
+    __device__ __forceinline__ void put_inverse(double* tile_g, double s)
     {
-        const double t = v[C];
-        const double x = t * inv;          // lane C: l_cc = d / sqrt(d) (L D L^T: 1)
-        const double m = LDL ? -t : -x;    // minus the factor of this column's update
-        const double dc = d;
-        if constexpr (C + 1 < NC) {
-            if constexpr (C + 2 < NC) bc[lane] = x;
-            v[C + 1] = __builtin_fma(m, readlane_d(x, C + 1), v[C + 1]);
-            double b0 = 0.0, b1 = 0.0;
-            if constexpr (C + 2 < NC) {   // LDS operations of one wave complete in order: the reads see column C
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-                if constexpr (C + 2 < 16) b0 = bc[lane & 15];
-                if constexpr (NC > 16) b1 = bc[16 + (lane & 15)];
-                __atomic_signal_fence(__ATOMIC_SEQ_CST);
-            }
-            estimate(C + 1, v[C + 1]);
-            out(C, lane, x, dc);
-            finish();
-            if constexpr (C + 2 < 16) fmac_rows<C + 2, (NC < 16 ? NC : 16) - (C + 2)>(v, C + 2, b0, m);
-            if constexpr (NC > 16) {
-                constexpr int i = C + 2 > 16 ? C + 2 : 16;
-                fmac_rows<i - 16, NC - i>(v, i, b1, m);
-            }
-            if constexpr ((C & 7) == 7) {
-                if (jb <= C + 1) return;
-            }
-            columns<C + 1>();
-        } else {
-            out(C, lane, x, dc);
+        auto o = lds(tile_g) + 33 * (lane & 31);
+        if (lane >= 32) {
+#pragma unroll
+            for (int c = 0; c < NC; ++c) o[c] = s * v[c];
+        }
+    }
+    // put(r, c, l_rc) for every row and column (L D L^T: d on the diagonal)
+    template <class Put>
+    __device__ __forceinline__ void put_rows(Put put)
+    {
+        if (lane < 32) {
+            const double dr = LDL ? dg[lane < NC ? lane : 0] : 0.0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) put(lane, c, LDL && c == lane ? dr : v[c]);
         }
     }
 };
-
-template <int NC, bool LDL, class Out>
-__device__ __forceinline__ void tile_chol_inv(double* Lt_g, double* bc_g, int jb, int col0, int32_t* status, Out out)
-{
-    static_assert(NC == 8 || NC == 16 || NC == 32, "tile width");
-    auto Lt = lds(Lt_g);
-    int lane = threadIdx.x & 63;
-    asm volatile("" : "+v"(lane));   // (keeps the lane masks of the columns from being formed ahead and held)
-    const int r = lane & 31;
-    TileChol<NC, LDL, Out> tc{{}, 0.0, 0.0, 0.0, LDL ? readlane_d(lds(bc_g)[kThrSlot], 0) : 0.0, lane, jb, 32, 0, lds(bc_g), out};
-#pragma unroll
-    for (int c = 0; c < NC; ++c) tc.v[c] = Lt[r + c * 33];
-    // (all loads issued before the selects: a conditional load is a branch each)
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int c = 0; c < NC; ++c) {
-        asm volatile("" : "+v"(tc.v[c]));
-        tc.v[c] = lane >= 32 ? (c == r ? 1.0 : 0.0) : tc.v[c];
-    }
-    tc.estimate(0, tc.v[0]);
-    tc.finish();
-    tc.template columns<0>();
-    if (lane == 0 && tc.fail < jb) atomicMin(status, col0 + tc.fail);
-    if (LDL && lane == 0 && tc.nrep > 0) atomicAdd(status + kStReplaced, tc.nrep);
-}
 
 // L U factorization without pivoting (the static pivoting of Section III:
 // the elimination order is the analysis' order) of one 32x32 diagonal tile
@@ -1022,6 +1095,16 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
         if (DS) blk_scale<T>(L, dd + kNB * (J - 1));
         blk_neg<T>(C);
         blk_mul_t<T, false>(C, L, N);
+        const int jb = min(kNB, w - kNB * J);
+        if (jb < kNB) {   // rows of L past w are the panel's next rows: not to meet the zeros of D_JJ (0 x inf)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 2; ++q)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (16 * h + MM<T>::drow(v, lk) >= jb) C.b[h][q][v] = T(0);
+        }
         // N = -D_Jc = (-D_JJ) (minus the sum)
         Blk<T> Dj;
         if constexpr (LDSD) {
@@ -1033,7 +1116,6 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
         }
         blk_zero<T>(N);
         blk_mul_t<T, true>(N, Dj, C);
-        const int jb = min(kNB, w - kNB * J);
         auto oD = glob(D + kNB * J + (int64_t)kNB * c * w);
 #pragma unroll
         for (int h = 0; h < 2; ++h)
@@ -1050,7 +1132,7 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
 
 // Cholesky factorization of the w x w diagonal block (w <= 256) of panel k
 // and the inverse D = L_kk^{-1}, by one workgroup.  The block is cut into
-// row blocks of 32; wave v owns the row blocks v, v + 4, ...  Row block i is
+// row blocks of 32; wave v owns the row blocks v and v + 4.  Row block i is
 // a forward substitution against the finished row blocks above it,
 //   L_iJ = (A_iJ - sum_{K<J} L_iK L_JK^T) D_JJ^T,   J = 0 .. i-1,
 // then its diagonal tile A_ii - sum_K L_iK L_iK^T is factored and inverted
@@ -1070,8 +1152,10 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
 // The right-looking form before it (trailing blocks read, updated and
 // written in memory at every 32-column step, two barriers per step) took
 // 294 us at w = 256 in FP64 and 252 us without the inverse's off-diagonal
-// blocks, in a kernel of its own on an idle MI355X; this one 123 and 83 us
-// (FP32 233 and 206 us before, 101 and 67 us now).
+// blocks, in a kernel of its own on an idle MI355X; this one 109 and 71 us
+// (FP32 233 and 206 us before, 89 and 57 us now).  With a wave's second row
+// block begun after its first was finished it took 123 and 83 us: the sums
+// of the last row blocks came late.
 //
 // LDL = true: L D L^T of the diagonal block (unit L with D on its diagonal,
 // and Y = D^{-1} L^{-1} as the stored inverse, so that the panel solve and
@@ -1087,6 +1171,7 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
     T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
     T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
     const GOp gA = make_gop(A, ld * w, 0, 1, ld);           // A(i, p) at i + p*ld
+    const GOp gD = make_gop(D, (int64_t)w * w, 0, 1, w);    // D(i, p) at i + p*w
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     double* bc = Lt + kNB * 33;
     __shared__ int s_x[8], s_d;      // blocks of row block i published (i + 1: D_ii too); tiles factored
@@ -1096,46 +1181,41 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
     if (tid < 8) s_x[tid] = 0;
     if (tid == 8) s_d = 0;
     __syncthreads();
-    for (int i = wave; i < nb; i += kThreads / 64) {
-        const int i0 = kNB * i, jb = min(kNB, w - i0);
-        // (entries past w are read from the rows below or as zeros and only
-        // reach rows and columns past jb; the sums are collected from zero
-        // and subtracted once: fewer roundings than from A downwards)
-        Blk<T> S, X;
-        blk_zero<T>(S);
-        for (int J = 0; J < i; ++J) {
-            Blk<T> B, C;
-            blk_load<T>(B, gA, i0, kNB * J);
-            blk_zero<T>(C);
-            if (J > 0) {
-                wait_for(&s_x[J], J - 1);
-                blk_gemm<T, false, LDL>(C, gA, i0, 0, gA, kNB * J, 0, J - 1, dd);
-                wait_for(&s_x[J], J);
-                Blk<T> Y;
-                blk_load<T>(Y, gA, kNB * J, kNB * (J - 1));
-                if (LDL) blk_scale<T>(X, dd + kNB * (J - 1));
-                blk_mul<T, false, false>(C, X, Y);
-            }
-            wait_for(&s_d, J + 1);
-            Blk<T> Y;
-            blk_from_lds<T>(Y, tiles + J * kTSz);
-            blk_zero<T>(X);
-            blk_sub<T>(C, B);
-            blk_mul<T, false, true>(X, C, Y);   // (sum - A) (-D)^T
-            blk_store<T>(X, glob(A + i0 + (int64_t)kNB * J * ld), 1, ld, jb);
-            if (LDL) {
-                Blk<T> Xd = X;
-                blk_scale<T>(Xd, dd + kNB * J);
-                blk_mul<T, true, false>(S, Xd, X);
-            } else {
-                blk_mul<T, true, false>(S, X, X);
-            }
-            publish(&s_x[i], J + 1);
+    // block J of row block i into the panel, and into the sum S of its tile.
+    // (Entries past w are read from the rows below or as zeros and only
+    // reach rows and columns past w; the sums are collected from zero and
+    // subtracted once: fewer roundings than from A downwards.)
+    auto step = [&](int i, int J, Blk<T>& S) {
+        const int i0 = kNB * i;
+        Blk<T> B, C, X;
+        blk_load<T>(B, gA, i0, kNB * J);
+        blk_zero<T>(C);
+        if (J > 0) {
+            wait_for(&s_x[J], J - 1);
+            blk_gemm<T, false, LDL>(C, gA, i0, 0, gA, kNB * J, 0, J - 1, dd);
+            wait_for(&s_x[J], J);
+            blk_gemm<T, false, LDL>(C, gA, i0, kNB * (J - 1), gA, kNB * J, kNB * (J - 1), 1, dd + kNB * (J - 1));
         }
-        // the tile, identity padded, to LDS; row block i-1 is done with Lt (s_d)
+        blk_sub<T>(C, B);
+        wait_for(&s_d, J + 1);
+        blk_from_lds<T>(B, tiles + J * kTSz);
+        blk_zero<T>(X);
+        blk_mul<T, false, true>(X, C, B);   // (sum - A) (-D)^T
+        blk_store<T>(X, glob(A + i0 + (int64_t)kNB * J * ld), 1, ld, min(kNB, w - i0));
+        if (LDL) {
+            Blk<T> Xd = X;
+            blk_scale<T>(Xd, dd + kNB * J);
+            blk_mul<T, true, false>(S, Xd, X);
+        } else {
+            blk_mul<T, true, false>(S, X, X);
+        }
+        publish(&s_x[i], J + 1);
+    };
+    // tile i: A_ii - S factored and inverted
+    auto tile = [&](int i, const Blk<T>& S, const Blk<T>& B) {
+        const int i0 = kNB * i, jb = min(kNB, w - i0);
+        // identity padded, to LDS; row block i-1 is done with Lt (s_d)
         {
-            Blk<T> B;
-            blk_load<T>(B, gA, i0, i0);
             auto L = lds(Lt);
 #pragma unroll
             for (int h = 0; h < 2; ++h)
@@ -1148,24 +1228,43 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
                     }
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
         }
-        auto Di = lds(tiles + i * kTSz);
-        // (branch-free: masked rows go past the array, the lower half's
-        // writes of D into the pivot buffer of the small items)
-        const int vL = uni(gA.off + i0 * gA.si + i0 * gA.sk), lim = jb;
-        auto out = [&](int c, int ln, double x, double d) {
-            const double val = (LDL && ln == c) ? d : x;
-            gstore_s(gA, (ln >= c && ln < lim && c < lim) ? ln * gA.si : kOffNone, uni(vL + c * gA.sk), (T)val);
-            (ln >= 32 ? Di + 33 * (ln - 32) : lds(bc) + 64)[c] = -x;
-            if (LDL) lds(dd)[i0 + c] = d;
-        };
-        tile_chol_inv<32, LDL>(Lt, bc, jb, f + i0, a.status, out);
+        TileChol<kNB, LDL> tc;
+        tc.run(Lt, bc, LDL ? dd + i0 : bc, jb, f + i0, a.status);
+        tc.put_inverse(tiles + i * kTSz, -1.0);
         publish_lds(&s_d, i + 1);
-        auto oD = glob(D + (int64_t)i0 * (w + 1));
-        for (int idx = lane; idx < kNB * kNB; idx += 64) {
-            const int r = idx & 31, c = idx >> 5;
-            if (r < jb && c <= r) oD[r + (int64_t)c * w] = (T)-Di[r + 33 * c];
+        // (masked entries go past the arrays, where the stores are dropped)
+        const int vL = uni(gA.off + i0 * (gA.si + gA.sk)), vD = uni(gD.off + i0 * (gD.si + gD.sk));
+        tc.put_rows([&](int r, int c, double x) { gstore_s(gA, r >= c && r < jb ? r * gA.si : kOffNone, uni(vL + c * gA.sk), (T)x); });
+        auto Di = lds(tiles + i * kTSz);
+        const int r = lane & 31;
+#pragma unroll
+        for (int cb = 0; cb < kNB; cb += 2) {
+            const int c = cb + (lane >> 5);
+            gstore_s(gD, r >= c && r < jb ? r * gD.si + c * gD.sk : kOffNone, vD, (T)-Di[r + 33 * c]);
         }
         publish(&s_x[i], i + 1);
+    };
+    // a wave's row blocks v and v + 4 go on side by side: block J of both as
+    // soon as tile J is there, the first row block's, which is nearer in the
+    // chain, ahead
+    const int i1 = wave, i2 = wave + kThreads / 64;
+    Blk<T> S1, S2, B;
+    blk_zero<T>(S1);
+    blk_zero<T>(S2);
+    if (i1 < nb) {
+        for (int J = 0; J + 1 < i1; ++J) {
+            step(i1, J, S1);
+            if (i2 < nb) step(i2, J, S2);
+        }
+        blk_load<T>(B, gA, kNB * i1, kNB * i1);   // (requested ahead of the last wait)
+        if (i1 > 0) step(i1, i1 - 1, S1);
+        tile(i1, S1, B);
+    }
+    if (i2 < nb) {
+        for (int J = max(0, i1 - 1); J + 1 < i2; ++J) step(i2, J, S2);
+        blk_load<T>(B, gA, kNB * i2, kNB * i2);
+        step(i2, i2 - 1, S2);
+        tile(i2, S2, B);
     }
     if (!full) return;
     // block columns of the inverse: wave v takes column v (first the columns
@@ -1173,70 +1272,7 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
     // the short columns 4 .. 6 go to the waves 3, 2, 1
     for (int t = 0; t < 2; ++t) {
         const int c = t == 0 ? wave : 7 - wave;
-        if (c + 1 < nb) inv_column<T, LDL, true>(gA, make_gop(D, (int64_t)w * w, 0, 1, w), D, w, nb, c, s_x, &s_d, tiles, dd);
-    }
-}
-
-// ---------------------------------------------------------------- INV(k)
-// The off-diagonal tiles of D = L_kk^{-1} after a FACT that stored L_kk and
-// the diagonal tiles D_JJ = L_JJ^{-1} only (blocks of elimination chains: the
-// inverse is then built beside the chain instead of inside FACT).  Block
-// forward substitution on L D = I, column block c of D at a time:
-//   D_Jc = -D_JJ (sum_{c <= K < J} L_JK D_Kc),   J = c+1 .. nb-1,
-// one column block per wave (c = wave, wave + 4, ...).  Per step: S = the
-// sum (32 x 32, inner dimension 32 (J - c), operands read from the panel and
-// from D, the D_Kc written by this wave's earlier steps), S to LDS, then
-// -D_JJ S on the matrix cores, written to D.  Rows of a partial last block
-// beyond w only reach results that are not stored (operands past the
-// arrays read zeros).
-template <class T>
-__device__ __noinline__ void task_inv(const SchedArgs& a, int k, T* Pb)
-{
-    typedef typename MM<T>::acc acc_t;
-    const DevPlan& pl = a.pl;
-    const int w = pl.lcol[k] - pl.fcol[k] + 1;
-    const int64_t ld = pl.stride[k];
-    const T* A = static_cast<const T*>(a.panels) + pl.panel_off[k];
-    T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
-    const int nb = (w + kNB - 1) / kNB;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int li = lane & 15, lk = lane >> 4;
-    T* Sl = Pb + wave * (kNB * 33);   // this wave's S (32 x 32, ld 33)
-    for (int c = wave; c + 1 < nb; c += kThreads / 64) {
-        for (int J = c + 1; J < nb; ++J) {
-            // S(r, q) = sum_p L(32J + r, 32c + p) D(32c + p, 32c + q)
-            acc_t acc[2][2];
-            zero_acc(acc);
-            wave_gemm<2, T, 2>(acc, make_gop(A, ld * w, kNB * J + (int64_t)kNB * c * ld, 1, ld),
-                               make_gop(D, (int64_t)w * w, kNB * c + (int64_t)kNB * c * w, w, 1), kNB * (J - c));
-            wave_store<T>(acc, kNB, kNB, [&](int r, int q, T v) { Sl[r + q * 33] = v; });
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
-            // D_Jc(r, q) = -sum_t D_JJ(r, t) S(t, q)
-            const GOp gJ = make_gop(D, (int64_t)w * w, kNB * J + (int64_t)kNB * J * w, 1, w);
-            acc_t acc2[2][2];
-            zero_acc(acc2);
-#pragma unroll
-            for (int st = 0; st < kNB / 4; ++st) {
-                const int t = 4 * st + lk;
-                T xs[2], ys[2];
-#pragma unroll
-                for (int b = 0; b < 2; ++b) {
-                    xs[b] = gload<T>(gJ, gJ.off + (16 * b + li) * gJ.si + t * gJ.sk);
-                    ys[b] = Sl[t + (16 * b + li) * 33];
-                }
-#pragma unroll
-                for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-                    for (int bj = 0; bj < 2; ++bj) acc2[bi][bj] = MM<T>::mfma(ys[bi], xs[bj], acc2[bi][bj]);
-            }
-            const int jb = min(kNB, w - kNB * J);
-            wave_store<T>(acc2, jb, kNB, [&](int r, int q, T v) {
-                D[(kNB * J + r) + (int64_t)(kNB * c + q) * w] = -v;
-            });
-            // this wave's next steps read D_Jc: stores complete before their loads
-            __builtin_amdgcn_s_waitcnt(0);
-            __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        }
+        if (c + 1 < nb) inv_column<T, LDL, true>(gA, gD, D, w, nb, c, s_x, &s_d, tiles, dd);
     }
 }
 
@@ -1256,7 +1292,8 @@ __device__ __noinline__ void task_inv(const SchedArgs& a, int k, T* Pb)
 // row block J+4 overwrites tile J's after row block J+3 is factored, so only
 // the row blocks up to J+3 take it from LDS.  At w = 256 in FP64 the
 // right-looking form before it took 490 us in a kernel of its own (FP32
-// 410), this one @LU256@.
+// 410), this one 248 us (215), 145 us on the chain without the inverses'
+// off-diagonal blocks.
 template <class T>
 __device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt, double* tiles)
 {
@@ -1277,56 +1314,49 @@ __device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt,
     if (tid < 8) s_x[tid] = 0;
     if (tid == 8) s_d = 0;
     __syncthreads();
-    for (int i = wave; i < nb; i += kThreads / 64) {
+    auto step = [&](int i, int J, Blk<T>& S) {
         const int i0 = kNB * i, jb = min(kNB, w - i0);
-        Blk<T> S, XL, XU;
-        blk_zero<T>(S);
-        for (int J = 0; J < i; ++J) {
-            Blk<T> CL, CU;
-            blk_zero<T>(CL);
-            blk_zero<T>(CU);
-            if (J > 0) {
-                wait_for(&s_x[J], J - 1);
-                blk_gemm<T, false, false>(CL, gA, i0, 0, gAt, kNB * J, 0, J - 1, nullptr);
-                blk_gemm<T, false, false>(CU, gAt, i0, 0, gA, kNB * J, 0, J - 1, nullptr);
-                wait_for(&s_x[J], J);
-                Blk<T> Q;
-                blk_load<T>(Q, gAt, kNB * J, kNB * (J - 1));
-                blk_mul<T, false, false>(CL, XL, Q);
-                blk_load<T>(Q, gA, kNB * J, kNB * (J - 1));
-                blk_mul<T, false, false>(CU, XU, Q);
-            }
-            {
-                Blk<T> B;
-                blk_load<T>(B, gA, i0, kNB * J);
-                blk_sub<T>(CL, B);
-                blk_load<T>(B, gAt, i0, kNB * J);
-                blk_sub<T>(CU, B);
-            }
-            Blk<T> Q;
-            blk_zero<T>(XL);
-            blk_zero<T>(XU);
-            if (J + 3 >= i) {
-                wait_for(&s_d, J + 1);
-                blk_from_lds<T>(Q, tiles + (2 * (J & 3) + 1) * kTSz);
-                blk_mul<T, false, true>(XL, CL, Q);
-                blk_from_lds<T>(Q, tiles + 2 * (J & 3) * kTSz);
-                blk_mul<T, false, true>(XU, CU, Q);
-            } else {
-                wait_for(&s_x[J], J + 1);
-                blk_load<T>(Q, gY, kNB * J, kNB * J);
-                blk_neg<T>(Q);
-                blk_mul<T, false, true>(XL, CL, Q);
-                blk_load<T>(Q, gX, kNB * J, kNB * J);
-                blk_neg<T>(Q);
-                blk_mul<T, false, true>(XU, CU, Q);
-            }
-            blk_store<T>(XL, glob(A + i0 + (int64_t)kNB * J * ld), 1, ld, jb);
-            blk_store<T>(XU, glob(A + kNB * J + (int64_t)i0 * ld), ld, 1, jb);
-            blk_mul<T, false, false>(S, XL, XU);
-            publish(&s_x[i], J + 1);
+        Blk<T> CL, CU, Q;
+        blk_zero<T>(CL);
+        blk_zero<T>(CU);
+        if (J > 0) {
+            wait_for(&s_x[J], J - 1);
+            blk_gemm<T, false, false>(CL, gA, i0, 0, gAt, kNB * J, 0, J - 1, nullptr);
+            blk_gemm<T, false, false>(CU, gAt, i0, 0, gA, kNB * J, 0, J - 1, nullptr);
+            wait_for(&s_x[J], J);
+            blk_gemm<T, false, false>(CL, gA, i0, kNB * (J - 1), gAt, kNB * J, kNB * (J - 1), 1, nullptr);
+            blk_gemm<T, false, false>(CU, gAt, i0, kNB * (J - 1), gA, kNB * J, kNB * (J - 1), 1, nullptr);
         }
-        // the tile, identity padded, to LDS; row block i-1 is done with Lt (s_d)
+        blk_load<T>(Q, gA, i0, kNB * J);
+        blk_sub<T>(CL, Q);
+        blk_load<T>(Q, gAt, i0, kNB * J);
+        blk_sub<T>(CU, Q);
+        Blk<T> XL, XU;
+        blk_zero<T>(XL);
+        blk_zero<T>(XU);
+        if (J + 3 >= i) {
+            wait_for(&s_d, J + 1);
+            blk_from_lds<T>(Q, tiles + (2 * (J & 3) + 1) * kTSz);
+            blk_mul<T, false, true>(XL, CL, Q);
+            blk_from_lds<T>(Q, tiles + 2 * (J & 3) * kTSz);
+            blk_mul<T, false, true>(XU, CU, Q);
+        } else {
+            wait_for(&s_x[J], J + 1);
+            blk_load<T>(Q, gY, kNB * J, kNB * J);
+            blk_neg<T>(Q);
+            blk_mul<T, false, true>(XL, CL, Q);
+            blk_load<T>(Q, gX, kNB * J, kNB * J);
+            blk_neg<T>(Q);
+            blk_mul<T, false, true>(XU, CU, Q);
+        }
+        blk_store<T>(XL, glob(A + i0 + (int64_t)kNB * J * ld), 1, ld, jb);
+        blk_store<T>(XU, glob(A + kNB * J + (int64_t)i0 * ld), ld, 1, jb);
+        blk_mul<T, false, false>(S, XL, XU);
+        publish(&s_x[i], J + 1);
+    };
+    auto tile = [&](int i, const Blk<T>& S) {
+        const int i0 = kNB * i, jb = min(kNB, w - i0);
+        // identity padded, to LDS; row block i-1 is done with Lt (s_d)
         {
             Blk<T> B;
             blk_load<T>(B, gA, i0, i0);
@@ -1343,33 +1373,83 @@ __device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt,
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
         }
         auto Ti = lds(tiles + 2 * (i & 3) * kTSz);   // -X_ii, then -Y_ii
-        const int vL = uni(gA.off + i0 * gA.si + i0 * gA.sk), lim = jb;
+        const int vL = uni(gA.off + i0 * gA.si + i0 * gA.sk), vD = uni(i0 * (gX.si + gX.sk));
         auto out = [&](int c, int ln, double x, double z) {
             // (masked entries go past the array, where the store is dropped)
             const int r = ln & 31;
-            const int vo = ln >= 32 ? (r >= c && r < lim && c < lim ? c * gA.si + r * gA.sk : kOffNone)
-                                    : (r > c && r < lim && c < lim ? r * gA.si + c * gA.sk : kOffNone);
+            const int vo = ln >= 32 ? (r >= c && r < jb && c < jb ? c * gA.si + r * gA.sk : kOffNone)
+                                    : (r > c && r < jb && c < jb ? r * gA.si + c * gA.sk : kOffNone);
             gstore_s(gA, vo, vL, (T)x);
             Ti[(ln >= 32 ? kTSz : 0) + 33 * r + c] = -z;
         };
         tile_lu_inv(Lt, bc, jb, f + i0, a.status, out);
         publish_lds(&s_d, i + 1);
-        auto oX = glob(X + (int64_t)i0 * (w + 1)), oY = glob(Y + (int64_t)i0 * (w + 1));
-        for (int idx = lane; idx < kNB * kNB; idx += 64) {
-            const int r = idx & 31, c = idx >> 5;
-            if (r < jb && c <= r) {
-                oX[r + (int64_t)c * w] = (T)-Ti[r + 33 * c];
-                oY[r + (int64_t)c * w] = (T)-Ti[kTSz + r + 33 * c];
-            }
+        const int r = lane & 31;
+#pragma unroll
+        for (int cb = 0; cb < kNB; cb += 2) {
+            const int c = cb + (lane >> 5), vo = r >= c && r < jb ? r * gX.si + c * gX.sk : kOffNone;
+            gstore_s(gX, vo, vD, (T)-Ti[r + 33 * c]);
+            gstore_s(gY, vo, vD, (T)-Ti[kTSz + r + 33 * c]);
         }
         publish(&s_x[i], i + 1);
+    };
+    // (the two row blocks of a wave side by side, as in task_fact)
+    const int i1 = wave, i2 = wave + kThreads / 64;
+    Blk<T> S1, S2;
+    blk_zero<T>(S1);
+    blk_zero<T>(S2);
+    if (i1 < nb) {
+        for (int J = 0; J + 1 < i1; ++J) {
+            step(i1, J, S1);
+            if (i2 < nb) step(i2, J, S2);
+        }
+        if (i1 > 0) step(i1, i1 - 1, S1);
+        tile(i1, S1);
     }
+    if (i2 < nb) {
+        for (int J = max(0, i1 - 1); J < i2; ++J) step(i2, J, S2);
+        tile(i2, S2);
+    }
+    if (a.inv_item != nullptr && uni(a.inv_item[k]) >= 0) return;   // (left to the INV item)
     // block columns 0 .. nb - 2 of both inverses, dealt as in task_fact
     for (int t = 0; t < 4; ++t) {
         const int c = (t & 2) == 0 ? wave : 7 - wave;
         if (c + 1 >= nb) continue;
         if ((t & 1) == 0) inv_column<T, false, false>(gA, gX, X, w, nb, c, s_x, &s_d, tiles, nullptr);
         else inv_column<T, false, false>(gAt, gY, Y, w, nb, c, s_x, &s_d, tiles, nullptr);
+    }
+}
+
+// ---------------------------------------------------------------- INV(k)
+// The off-diagonal tiles of the kept inverse after a FACT that stored the
+// factor and the diagonal tiles D_JJ only (blocks of elimination chains: the
+// inverse is then built beside the chain instead of inside FACT): the block
+// columns of inv_column, two per wave; L U: of both inverses.
+template <class T, bool LDL, bool LU>
+__device__ __noinline__ void task_inv(const SchedArgs& a, int k)
+{
+    const DevPlan& pl = a.pl;
+    const int w = uni(pl.lcol[k] - pl.fcol[k] + 1);
+    const int64_t ld = pl.stride[k];
+    const T* A = static_cast<const T*>(a.panels) + pl.panel_off[k];
+    T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
+    const GOp gA = make_gop(A, ld * w, 0, 1, ld);
+    const int tid = threadIdx.x, wave = uni(tid >> 6), nb = (w + kNB - 1) / kNB;
+    __shared__ int s_x[8], s_d;
+    __shared__ double dd[LDL ? 256 : 1];
+    if (tid < 8) s_x[tid] = 9;   // everything is there
+    if (tid == 8) s_d = 9;
+    if (LDL && tid < w) dd[tid] = (double)A[tid * (ld + 1)];
+    __syncthreads();
+    for (int t = 0; t < 2; ++t) {
+        const int c = t == 0 ? wave : 7 - wave;
+        if (c + 1 >= nb) continue;
+        inv_column<T, LDL, false>(gA, make_gop(D, (int64_t)w * w, 0, 1, w), D, w, nb, c, s_x, &s_d, nullptr, dd);
+        if constexpr (LU) {
+            T* Y = D + a.uinv;
+            inv_column<T, false, false>(make_gop(A, ld * w, 0, ld, 1), make_gop(Y, (int64_t)w * w, 0, 1, w), Y, w, nb, c, s_x, &s_d,
+                                        nullptr, nullptr);
+        }
     }
 }
 
@@ -1413,112 +1493,128 @@ __device__ __noinline__ void task_trsm(const SchedArgs& a, int k, int row0, int 
                       [&](int r, int c, T v) { B[(r0 + r) + (int64_t)(c0 + c) * ld] = v; });
 }
 
-// Rows [row0, row0+nrows) (nrows <= 64) of a chain block's panel below its
+// Rows [row0, row0+nrows) (nrows <= 16) of a chain block's panel below its
 // diagonal block, by block forward substitution with the diagonal tiles of
-// the inverse only (the rest of L_kk^{-1} is formed beside the chain, by the
-// INV item):
-//   X_J = (B_J - sum_{K<J} X_K L_JK^T) D_JJ^T,   J = 0 .. NBK-1   (X = B L_kk^{-T}),
-// wave v taking rows 16v .. 16v+15.  The finished column blocks X_K stay in
-// registers in the operand layout of the products (xop[K][s] = X(r, 32K + 4s
-// + l/16), r = l%16); each new block passes once through LDS from the
-// result layout to the operand layout.  NBK = number of 32-column blocks
-// (every loop fully unrolled: a branch in them sends xop to scratch).
-// Entries past a partial last block read zeros (operands past the arrays)
-// or finite panel entries that only meet zeros of D.
-template <class T, int NBK>
-__device__ __noinline__ void task_trsm_subst(const SchedArgs& a, int k, int row0, int nrows, T* Pb)
+// the inverse only (the rest of the inverse is formed beside the chain, by
+// the INV item):
+//   X_J = (B_J - sum_{K<J} X_K L_JK^T) D_JJ^T,   J = 0 .. nb-1   (X = B L_kk^{-T}),
+// by the four waves together: wave v owns the column blocks v and v + 4.  A
+// finished X_K goes to LDS as it lies in the lanes (results have the form of
+// operands, see Blk) and every wave adds its product to the sums of its own
+// later blocks while the owner of the next one goes on; L_JK for the next
+// K is on its way meanwhile.  L D L^T: X_K D_K is what goes to LDS (Y_JJ in
+// place of D_JJ); L U: the L rows take U_kk^T and Y_JJ (uside 0), the U^T
+// rows L_kk and X_JJ (uside 1).
+// A chain link waits for these items, so they are cut for latency: 28
+// products of 16x16x4 per step of the substitution.  One wave per 16 rows
+// with all of its blocks (576 products in a row at 256 columns) took 36 us
+// on the chain, this form 20 to 24 us.
+template <class T, bool LDL, bool LU>
+__device__ __noinline__ void task_trsm_chain(const SchedArgs& a, int k, int row0, int nrows, int uside, double* tiles)
 {
     typedef typename MM<T>::acc acc_t;
     const DevPlan& pl = a.pl;
-    const int w = pl.lcol[k] - pl.fcol[k] + 1;
+    const int w = uni(pl.lcol[k] - pl.fcol[k] + 1);
     const int64_t ld = pl.stride[k];
-    T* P = static_cast<T*>(a.panels) + pl.panel_off[k];
-    const T* D = static_cast<const T*>(a.dinv) + pl.dinv_off[k];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int li = lane & 15, lk = lane >> 4;
-    const int r0 = 16 * wave;
-    if (r0 >= nrows) return;
-    const int mv = min(16, nrows - r0);
-    const GOp gP = make_gop(P, ld * w, row0 + r0, 1, ld);   // rows of this wave: X(r, j) at r + j*ld
-    const GOp gL = make_gop(P, ld * w, 0, 1, ld);           // L_kk(i, j) at i + j*ld
-    const GOp gD = make_gop(D, (int64_t)w * w, 0, 1, w);    // D(i, j) at i + j*w
-    T* Sl = Pb + wave * (kNB * 17);   // this wave's 16 x 32 staging block (ld 17)
-    T xop[NBK][8];
+    const T* A = static_cast<const T*>(a.panels) + pl.panel_off[k];
+    T* P = static_cast<T*>(a.panels) + pl.panel_off[k] + (LU && uside ? a.upanel : 0);
+    const T* D = static_cast<const T*>(a.dinv) + pl.dinv_off[k] + (LU && !uside ? a.uinv : 0);
+    const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
+    const int nb = (w + kNB - 1) / kNB;
+    const GOp gP = make_gop(P, ld * w, row0, 1, ld);
+    const GOp gA = make_gop(A, ld * w, 0, 1, ld);
+    const GOp gL = LU && !uside ? make_gop(A, ld * w, 0, ld, 1) : gA;   // (c, p) of L_kk or U_kk^T
+    const GOp gD = make_gop(D, (int64_t)w * w, 0, 1, w);
+    T* xs = reinterpret_cast<T*>(tiles);   // X_K: entry s of lane l at (8 K + s) * 64 + l
+    __shared__ int s_t[8];                 // X_K is in LDS
+    if (tid < 8) s_t[tid] = 0;
+    __syncthreads();
+    // rows 0..15 of a block row, columns col0.. of g: m[p][v] = M(li, 16 p + drow(v, lk))
+    auto load = [&](T (&m)[2][4], const GOp& g, int r0, int col0) {
+        const int vo = li * g.si + MM<T>::drow(0, lk) * g.sk;
 #pragma unroll
-    for (int J = 0; J < NBK; ++J) {
-        acc_t acc[2][1];
-        zero_acc(acc);
-        // the block of B, in the result layout: row li, column 16 bi + drow(v, l/16)
-        T bj[2][4];
+        for (int p = 0; p < 2; ++p)
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+            for (int v = 0; v < 4; ++v) m[p][v] = gload_s(g, vo, uni(g.off + r0 * g.si + (col0 + 16 * p + MM<T>::drow(v, 0)) * g.sk), T(0));
+    };
+    // (everything in flight at once fits the registers: the tile of D and the
+    // pivots of one own block at a time, L_JK of the next K into the
+    // registers of the last)
+    T B[2][2][4], L[2][2][2][4], Dj[2][2][4], d[2][4];   // [own block][column tile][p][v]
+    acc_t S[2][2];
+    auto load_own = [&](int J) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v)
-                bj[bi][v] = gload<T>(gP, gP.off + li * gP.si + (kNB * J + 16 * bi + MM<T>::drow(v, lk)) * gP.sk);
-        // S = sum_{K<J} X_K L_JK^T: Y(c, p) = L(32J + c, 32K + p), X(r, p) = X_K
+        for (int h = 0; h < 2; ++h) {
+            load(Dj[h], gD, kNB * J + 16 * h, kNB * J);
 #pragma unroll
-        for (int K = 0; K < J; ++K) {
-            T y0[8], y1[8];
-#pragma unroll
-            for (int st = 0; st < 8; ++st) {
-                const int pcol = kNB * K + 4 * st + lk;
-                y0[st] = gload<T>(gL, (kNB * J + li) * gL.si + pcol * gL.sk);
-                y1[st] = gload<T>(gL, (kNB * J + 16 + li) * gL.si + pcol * gL.sk);
-            }
-#pragma unroll
-            for (int st = 0; st < 8; ++st) {
-                acc[0][0] = MM<T>::mfma(y0[st], xop[K][st], acc[0][0]);
-                acc[1][0] = MM<T>::mfma(y1[st], xop[K][st], acc[1][0]);
-            }
+            for (int v = 0; v < 4 && LDL; ++v)
+                d[h][v] = gload_s(gA, MM<T>::drow(0, lk) * (gA.si + gA.sk),
+                                  uni(gA.off + (kNB * J + 16 * h + MM<T>::drow(v, 0)) * (gA.si + gA.sk)), T(0));
         }
-        // T_J = B_J - S, to the operand layout through LDS
+    };
 #pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
+    for (int o = 0; o < 2; ++o) {
+        load(B[o], gP, 0, kNB * (wave + 4 * o));   // (blocks past w read zeros and are not used)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) Sl[li + (16 * bi + MM<T>::drow(v, lk)) * 17] = bj[bi][v] - acc[bi][0][v];
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
-        T tj[8];
-#pragma unroll
-        for (int st = 0; st < 8; ++st) tj[st] = Sl[li + (4 * st + lk) * 17];
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-        // X_J = T_J D_JJ^T: Y(c, t) = D(32J + c, 32J + t)
-        acc_t acc2[2][1];
-        zero_acc(acc2);
-#pragma unroll
-        for (int st = 0; st < 8; ++st) {
-            const int t = kNB * J + 4 * st + lk;
-            const T d0 = gload<T>(gD, (kNB * J + li) * gD.si + t * gD.sk);
-            const T d1 = gload<T>(gD, (kNB * J + 16 + li) * gD.si + t * gD.sk);
-            acc2[0][0] = MM<T>::mfma(d0, tj[st], acc2[0][0]);
-            acc2[1][0] = MM<T>::mfma(d1, tj[st], acc2[1][0]);
+        for (int h = 0; h < 2; ++h) {
+            load(L[o][h], gL, kNB * (wave + 4 * o) + 16 * h, 0);
+            S[o][h] = acc_t{0, 0, 0, 0};
         }
-        // X_J to the panel and, in the operand layout, to xop[J]
-        auto out = glob(P);
-#pragma unroll
-        for (int bi = 0; bi < 2; ++bi)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int c = 16 * bi + MM<T>::drow(v, lk);
-                const T x = acc2[bi][0][v];
-                Sl[li + c * 17] = x;
-                if (li < mv && kNB * J + c < w) out[(row0 + r0 + li) + (int64_t)(kNB * J + c) * ld] = x;
-            }
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
-#pragma unroll
-        for (int st = 0; st < 8; ++st) xop[J][st] = Sl[li + (4 * st + lk) * 17];
-        __atomic_signal_fence(__ATOMIC_SEQ_CST);
     }
-}
-
-template <class T>
-__device__ __forceinline__ void trsm_subst(const SchedArgs& a, int k, int row0, int nrows, T* Pb)
-{
-    switch ((a.pl.lcol[k] - a.pl.fcol[k] + kNB) / kNB) {
-    case 4: task_trsm_subst<T, 4>(a, k, row0, nrows, Pb); break;
-    case 5: task_trsm_subst<T, 5>(a, k, row0, nrows, Pb); break;
-    case 6: task_trsm_subst<T, 6>(a, k, row0, nrows, Pb); break;
-    case 7: task_trsm_subst<T, 7>(a, k, row0, nrows, Pb); break;
-    default: task_trsm_subst<T, 8>(a, k, row0, nrows, Pb); break;
+    load_own(wave);
+    for (int K = 0; K < nb; ++K) {
+        if ((K & 3) == wave) {
+            // X_K = (B_K - S) D_KK^T; columns past w count zero
+            T x[2][4];
+            const int jb = w - kNB * K;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const T r = K < 4 ? B[0][p][v] - S[0][p][v] : B[1][p][v] - S[1][p][v];
+                    x[p][v] = 16 * p + MM<T>::drow(v, lk) < jb ? r : T(0);
+                }
+            acc_t X[2] = {acc_t{0, 0, 0, 0}, acc_t{0, 0, 0, 0}};
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int h = p; h < 2; ++h) X[h] = MM<T>::mfma(Dj[h][p][v], x[p][v], X[h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) lds(xs)[(8 * K + 4 * h + v) * 64 + lane] = LDL ? X[h][v] * d[h][v] : X[h][v];
+            publish_lds(&s_t[K], 1);
+            auto out = glob(P);
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    const int c = 16 * h + MM<T>::drow(v, lk);
+                    if (li < nrows && c < jb) out[(row0 + li) + (int64_t)(kNB * K + c) * ld] = X[h][v];
+                }
+            if (K < 4) load_own(wave + 4);
+        }
+        if (K + 1 >= nb || K >= wave + 4) continue;   // no own block after K
+        wait_for(&s_t[K], 1);
+        T x[2][4];
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[p][v] = lds(xs)[(8 * K + 4 * p + v) * 64 + lane];
+#pragma unroll
+        for (int o = 0; o < 2; ++o) {
+            if (o == 0 && K >= wave) continue;
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) S[o][h] = MM<T>::mfma(L[o][h][p][v], x[p][v], S[o][h]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) load(L[o][h], gL, kNB * (wave + 4 * o) + 16 * h, kNB * (K + 1));
+        }
     }
 }
 
@@ -1715,12 +1811,15 @@ __device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const
     }
     __syncthreads();
     if (wave == 0) {
-        auto out = [&](int c, int ln, double x, double d) {
-            *(ln >= 32 ? lds(Dt) + c + 33 * (ln - 32) : lds(Lt) + ln + 33 * c) = (LDL && ln == c) ? d : x;
+        auto tile = [&](auto nc) {
+            TileChol<decltype(nc)::value, LDL> tc;
+            tc.run(Lt, bc, bc + 64, w, f, a.status);
+            tc.put_inverse(Dt, 1.0);
+            tc.put_rows([&](int r, int c, double x) { lds(Lt)[r + 33 * c] = x; });
         };
-        if (w <= 8) tile_chol_inv<8, LDL>(Lt, bc, w, f, a.status, out);
-        else if (w <= 16) tile_chol_inv<16, LDL>(Lt, bc, w, f, a.status, out);
-        else tile_chol_inv<32, LDL>(Lt, bc, w, f, a.status, out);
+        if (w <= 8) tile(std::integral_constant<int, 8>());
+        else if (w <= 16) tile(std::integral_constant<int, 16>());
+        else tile(std::integral_constant<int, 32>());
     }
     __syncthreads();
     for (int idx = tid; idx < kNB * kNB; idx += kThreads) {
@@ -1873,7 +1972,9 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
             __builtin_amdgcn_s_setprio(0);
         } else if (kind == kTrsm) {
             __builtin_amdgcn_s_setprio(2);
-            if constexpr (LU) {
+            if (d0.x & kSubstItem) {
+                task_trsm_chain<T, LDL, LU>(a, d0.y, d0.z, d0.w, (d0.x & kUSideItem) != 0, tiles);
+            } else if constexpr (LU) {
                 if (thin) {
                     task_trsm<T, 1>(a, d0.y, d0.z, d0.w, 0, a.uinv);
                     task_trsm<T, 1>(a, d0.y, d0.z, d0.w, a.upanel, 0);
@@ -1882,9 +1983,7 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
                     task_trsm<T>(a, d0.y, d0.z, d0.w, a.upanel, 0);
                 }
             } else {
-                if (d0.x & kSubstItem) {
-                    if constexpr (!LDL) trsm_subst<T>(a, d0.y, d0.z, d0.w, Pb);
-                } else if (thin) {
+                if (thin) {
                     task_trsm<T, 1>(a, d0.y, d0.z, d0.w);
                 } else {
                     task_trsm<T>(a, d0.y, d0.z, d0.w);
@@ -1895,11 +1994,9 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
             if (thin) task_update<T, LDL, LU, 1>(a, d0, d1, rpos, cpos);
             else task_update<T, LDL, LU>(a, d0, d1, rpos, cpos);
         } else if (kind == kInv) {
-            if constexpr (!LDL && !LU) {
-                __builtin_amdgcn_s_setprio(2);
-                task_inv<T>(a, d0.y, Pb);
-                __builtin_amdgcn_s_setprio(0);
-            }
+            __builtin_amdgcn_s_setprio(2);
+            task_inv<T, LDL, LU>(a, d0.y);
+            __builtin_amdgcn_s_setprio(0);
         } else if constexpr (!LU) {
             task_small<T, LDL>(a, d0, d1, Lt, Dt, Pb);
         }

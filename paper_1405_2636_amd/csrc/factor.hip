@@ -143,16 +143,8 @@ __device__ __forceinline__ float gload<float>(const GOp& g, int voff)
 // so the load returns zero (the value is discarded by a select anyway).
 constexpr int kOffNone = 0x7f000000;
 
-// Element at byte offset voff (per lane) + soff (wave-uniform) of g's array;
-// stores outside the array are dropped.
-__device__ __forceinline__ double gload_s(const GOp& g, int voff, int soff, double)
-{
-    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(g.rs, voff, soff, 0));
-}
-__device__ __forceinline__ float gload_s(const GOp& g, int voff, int soff, float)
-{
-    return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(g.rs, voff, soff, 0));
-}
+// Store at byte offset voff (per lane, range-checked) + soff (wave-uniform,
+// not) of g's array; a voff outside the array drops the store.
 __device__ __forceinline__ void gstore_s(const GOp& g, int voff, int soff, double v)
 {
     __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), g.rs, voff, soff, 0);
@@ -859,7 +851,10 @@ __device__ __forceinline__ void blk_zero(Blk<T>& m)
     zero_acc(m.b);
 }
 
-// rows row0.., columns col0.. of g's array; half h only if given
+// rows row0.. of half h (16 columns) of the block at column col0 of g's
+// array.  The whole offset is in the vector offset: the range check, which
+// makes rows and columns past the array read as zero, does not see a scalar
+// offset.
 template <class T>
 __device__ __forceinline__ void blk_load_half(T (&m)[2][4], const GOp& g, int row0, int col0, int h)
 {
@@ -869,7 +864,7 @@ __device__ __forceinline__ void blk_load_half(T (&m)[2][4], const GOp& g, int ro
     for (int q = 0; q < 2; ++q)
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            m[q][v] = gload_s(g, vo, uni(g.off + (row0 + 16 * q) * g.si + (col0 + 16 * h + MM<T>::drow(v, 0)) * g.sk), T(0));
+            m[q][v] = gload<T>(g, vo + uni(g.off + (row0 + 16 * q) * g.si + (col0 + 16 * h + MM<T>::drow(v, 0)) * g.sk));
 }
 
 template <class T>
@@ -1535,7 +1530,7 @@ __device__ __noinline__ void task_trsm_chain(const SchedArgs& a, int k, int row0
 #pragma unroll
         for (int p = 0; p < 2; ++p)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) m[p][v] = gload_s(g, vo, uni(g.off + r0 * g.si + (col0 + 16 * p + MM<T>::drow(v, 0)) * g.sk), T(0));
+            for (int v = 0; v < 4; ++v) m[p][v] = gload<T>(g, vo + uni(g.off + r0 * g.si + (col0 + 16 * p + MM<T>::drow(v, 0)) * g.sk));
     };
     // (everything in flight at once fits the registers: the tile of D and the
     // pivots of one own block at a time, L_JK of the next K into the
@@ -1548,8 +1543,7 @@ __device__ __noinline__ void task_trsm_chain(const SchedArgs& a, int k, int row0
             load(Dj[h], gD, kNB * J + 16 * h, kNB * J);
 #pragma unroll
             for (int v = 0; v < 4 && LDL; ++v)
-                d[h][v] = gload_s(gA, MM<T>::drow(0, lk) * (gA.si + gA.sk),
-                                  uni(gA.off + (kNB * J + 16 * h + MM<T>::drow(v, 0)) * (gA.si + gA.sk)), T(0));
+                d[h][v] = gload<T>(gA, (kNB * J + 16 * h + MM<T>::drow(v, lk)) * (gA.si + gA.sk));
         }
     };
 #pragma unroll

@@ -145,13 +145,11 @@ struct spx_handle {
     int32_t nsmall = 0, nfused_tiles = 0;   // fused small blocks and their update tiles
     DevBuf<int4> desc;
     DevBuf<int32_t> rmap;
-    DevBuf<int32_t> trsm_first, trsm_count, upd_first, upd_hp, upd_count, hp_cblk, fact_dep0, fact_dep, trsm_left,
+    DevBuf<int32_t> trsm_count, hp_item, fact_dep0, fact_dep, trsm_left,
         queue, hp_queue, ready, qctr, status;
-    DevBuf<int4> ftab;
+    DevBuf<int4> ftab, tiny;
     // deterministic mode: update pairs (see SchedArgs)
     int32_t npair = 0, ubase = 0;
-    int32_t ninv = 0;                 // INV items (chain blocks)
-    DevBuf<int32_t> inv_item;
     DevBuf<int32_t> upair, kpair, pdep0, pdep, pleft;
     DevBuf<int4> pairs;
     DevBuf<int64_t> trace;   // per-item task trace, allocated when the trace option is on
@@ -356,7 +354,7 @@ void build_tasks(spx_handle* h)
     };
     // fused small blocks: width <= 32, at most 128 panel rows, tables within
     // the bounds of the item's LDS
-    std::vector<char> small(nc, 0);
+    std::vector<char> small(nc, 0), tiny(nc, 0);
     int32_t nsmall = 0;
     if (h->opt.fuse_small) {
         for (int32_t k = 0; k < nc; ++k) {
@@ -373,9 +371,38 @@ void build_tasks(spx_handle* h)
             if (ntiles <= kSmallMaxUpd && nmap <= kSmallMap) {
                 small[k] = 1;
                 ++nsmall;
+                tiny[k] = w <= kTinyW && ld <= kTinyRows && ntiles <= kTinyTiles && nmap <= kTinyMap;
             }
         }
     }
+    // groups of tiny blocks: consecutive ones of a dependency level, so many
+    // per item that a level still has kTinyItems items (the workgroups that
+    // run at once), at most kTinyGroup.  item[k]: the item that factors k
+    constexpr int32_t kTinyGroup = 8, kTinyItems = 512;
+    std::vector<int32_t> item(nc, -1), group;   // group: blocks of the tiny items, item by item
+    std::vector<int32_t> gptr{0}, first_of;      // their ends; first block of every factoring item
+    {
+        std::vector<int32_t> ntiny(static_cast<size_t>(nc) + 1, 0), open(static_cast<size_t>(nc) + 1, -1);
+        for (int32_t k = 0; k < nc; ++k)
+            if (tiny[k]) ++ntiny[lvl[k]];
+        std::vector<int32_t> members;   // of the open item of every level
+        for (int32_t k = 0; k < nc; ++k) {
+            if (tiny[k]) {
+                const int32_t g = std::clamp(ntiny[lvl[k]] / kTinyItems, 1, kTinyGroup);
+                int32_t& o = open[lvl[k]];
+                if (o >= 0 && hp[first_of[o]] == hp[k] && members[o] < g) {
+                    item[k] = o;
+                    ++members[o];
+                    continue;
+                }
+                o = static_cast<int32_t>(first_of.size());
+            }
+            item[k] = static_cast<int32_t>(first_of.size());
+            first_of.push_back(k);
+            members.push_back(1);
+        }
+    }
+    const int32_t nfact = static_cast<int32_t>(first_of.size());
     // merged updates of split supernodes: the pieces of a supernode are
     // consecutive column blocks sharing the rows below the supernode, and
     // piece p's panel rows are the rows of a later piece k shifted by
@@ -407,15 +434,45 @@ void build_tasks(spx_handle* h)
         }
         k0 = k1 + 1;
     }
-    std::vector<int4> desc;
-    desc.reserve(static_cast<size_t>(nc) * 2);
-    std::vector<int32_t> tf(nc), tc(nc), uf(nc), uh(nc), ucnt(nc), dep(nc, 0);
-    std::vector<int32_t> rmap;
+    std::vector<int4> desc;   // four int4 per item (see device.hpp)
+    desc.reserve(static_cast<size_t>(nc) * 8);
+    std::vector<int64_t> doff(static_cast<size_t>(nc) + 1, 0);   // kept inverses
     for (int32_t k = 0; k < nc; ++k) {
-        desc.push_back(int4{small[k] ? kSmall : kFact, k, 0, 0});
-        desc.push_back(int4{0, 0, 0, 0});
+        const int64_t w = P.lcol[k] - P.fcol[k] + 1;
+        doff[k + 1] = doff[k] + w * w;
     }
-    int32_t id = nc;
+    auto lo = [](int64_t v) { return static_cast<int32_t>(v & 0xffffffff); };
+    auto hi = [](int64_t v) { return static_cast<int32_t>(v >> 32); };
+    auto geo = [&](int32_t k) {   // second half of FACT, TRSM, SMALL and INV items
+        desc.push_back(int4{P.lcol[k] - P.fcol[k] + 1, P.stride[k], lo(P.panel_off[k]), hi(P.panel_off[k])});
+        desc.push_back(int4{lo(doff[k]), hi(doff[k]), 0, 0});
+    };
+    std::vector<int32_t> tf(nc), tc(nc), uf(nc), uh(nc), ucnt(nc), dep(nfact, 0);
+    std::vector<int4> trec(3 * static_cast<size_t>(nc));   // tiny records by block
+    std::vector<int32_t> rmap;
+    {
+        // blocks of the tiny items, item by item
+        std::vector<int32_t> cnt(static_cast<size_t>(nfact) + 1, 0);
+        for (int32_t k = 0; k < nc; ++k)
+            if (tiny[k]) ++cnt[item[k] + 1];
+        for (int32_t i = 0; i < nfact; ++i) cnt[i + 1] += cnt[i];
+        gptr = cnt;
+        group.resize(static_cast<size_t>(cnt[nfact]));
+        for (int32_t k = 0; k < nc; ++k)
+            if (tiny[k]) group[cnt[item[k]]++] = k;
+    }
+    for (int32_t i = 0; i < nfact; ++i) {
+        const int32_t k = first_of[i];
+        if (tiny[k]) {
+            desc.push_back(int4{kTiny, k, gptr[i], gptr[i + 1] - gptr[i]});
+            for (int q = 0; q < 3; ++q) desc.push_back(int4{0, 0, 0, 0});
+        } else {
+            desc.push_back(int4{small[k] ? kSmall : kFact, k, P.fcol[k], 0});
+            desc.push_back(int4{0, 0, 0, 0});   // (filled in below)
+            geo(k);
+        }
+    }
+    int32_t id = nfact;
     for (int32_t k = 0; k < nc; ++k) {
         const int32_t w = P.lcol[k] - P.fcol[k] + 1, ld = P.stride[k];
         tf[k] = id;
@@ -427,6 +484,7 @@ void build_tasks(spx_handle* h)
             for (int32_t side = 0; side < (inv[k] && h->lu() ? 2 : 1); ++side) {   // (L U: L rows, U^T rows)
                 desc.push_back(int4{kTrsm | tflag | (side ? kUSideItem : 0), k, r, std::min(trows, ld - r)});
                 desc.push_back(int4{0, 0, 0, 0});
+                geo(k);
                 ++id;
             }
         tc[k] = id - tf[k];
@@ -478,16 +536,18 @@ void build_tasks(spx_handle* h)
             const int32_t ttr = thin ? 64 : h->tile_rows, ttc = thin ? 64 : h->tile_cols;
             const int32_t pfirst = id;
             for_tiles(k, b, b2, ttr, ttc, [&](int32_t r0, int32_t mr, int32_t c0, int32_t ncl) {
-                ++dep[j];
+                ++dep[item[j]];
                 if (small[k]) {
                     const int64_t po = P.panel_off[j];
-                    ftab.push_back(int4{j, r0, mr, c0});
+                    ftab.push_back(int4{item[j], r0, mr, c0});
                     ftab.push_back(int4{ncl, mbase, P.stride[j], 0});
                     ftab.push_back(int4{static_cast<int32_t>(po & 0xffffffff), static_cast<int32_t>(po >> 32), 0, 0});
                     return;
                 }
                 desc.push_back(int4{kUpdate | ((npieces - 1) << 8) | (thin ? kThinItem : 0), k, j, r0});
                 desc.push_back(int4{mr, c0, ncl, mbase});
+                desc.push_back(int4{item[j], P.stride[j], lo(P.panel_off[j]), hi(P.panel_off[j])});
+                desc.push_back(int4{P.lcol[k] - P.fcol[k] + 1, ld, lo(P.panel_off[k]), hi(P.panel_off[k])});
                 ++id;
                 if (first_pair && hp[k]) ++uh[k];
             });
@@ -506,8 +566,15 @@ void build_tasks(spx_handle* h)
         nhp_upd += uh[k];
         if (small[k]) {
             const int32_t nt = static_cast<int32_t>(ftab.size() / 3) - ftile0;
-            desc[2 * static_cast<size_t>(k) + 1] =
-                int4{ftile0, nt, static_cast<int32_t>(mstart), static_cast<int32_t>(rmap.size() - mstart)};
+            const int32_t m0 = static_cast<int32_t>(mstart), ml = static_cast<int32_t>(rmap.size() - mstart);
+            if (tiny[k]) {
+                int4* t = &trec[3 * static_cast<size_t>(k)];
+                t[0] = int4{P.fcol[k], (P.lcol[k] - P.fcol[k] + 1) | (ld << 8) | (nt << 16), m0, ml};
+                t[1] = int4{lo(P.panel_off[k]), hi(P.panel_off[k]), lo(doff[k]), hi(doff[k])};
+                t[2] = int4{ftile0, 0, 0, 0};
+            } else {
+                desc[4 * static_cast<size_t>(item[k]) + 1] = int4{ftile0, nt, m0, ml};
+            }
         }
     }
     kpair[nc] = static_cast<int32_t>(pairs.size());
@@ -517,8 +584,15 @@ void build_tasks(spx_handle* h)
         if (inv[k] && !small[k]) {
             desc.push_back(int4{kInv, k, 0, 0});
             desc.push_back(int4{0, 0, 0, 0});
+            geo(k);
             inv_item[k] = id++;
         }
+    for (int32_t k = 0; k < nc; ++k) {
+        if (small[k]) continue;
+        desc[4 * static_cast<size_t>(item[k]) + 1] = int4{tf[k], tc[k], inv_item[k], hp[k]};
+        for (int32_t i = 0; i < tc[k]; ++i)
+            desc[4 * static_cast<size_t>(tf[k] + i) + 1] = int4{uf[k], uh[k], ucnt[k], 0};
+    }
     h->total = id;
     h->npair = static_cast<int32_t>(pairs.size());
     h->ubase = ubase;
@@ -536,29 +610,33 @@ void build_tasks(spx_handle* h)
     h->nfused_tiles = static_cast<int32_t>(ftab.size() / 3);
     int64_t hp_items = nhp_upd;
     for (int32_t k = 0; k < nc; ++k)
-        if (hp[k]) hp_items += 1 + tc[k];   // (INV items: normal queue)
+        if (hp[k]) hp_items += tc[k];   // (INV items: normal queue)
+    for (int32_t i = 0; i < nfact; ++i) hp_items += hp[first_of[i]];
     h->hp_total = static_cast<int32_t>(hp_items);
     h->total_normal = h->total - h->hp_total;
     std::vector<int32_t> ready;   // high-priority ones first
-    for (int32_t k = 0; k < nc; ++k)
-        if (dep[k] == 0 && hp[k]) ready.push_back(k);
+    std::vector<int32_t> hp_item(nfact);
+    for (int32_t i = 0; i < nfact; ++i) hp_item[i] = hp[first_of[i]];
+    for (int32_t i = 0; i < nfact; ++i)
+        if (dep[i] == 0 && hp_item[i]) ready.push_back(i);
     h->nready_hp = static_cast<int32_t>(ready.size());
-    for (int32_t k = 0; k < nc; ++k)
-        if (dep[k] == 0 && !hp[k]) ready.push_back(k);
+    for (int32_t i = 0; i < nfact; ++i)
+        if (dep[i] == 0 && !hp_item[i]) ready.push_back(i);
     h->nready = static_cast<int32_t>(ready.size());
-    h->hp_cblk.upload(hp);
+    h->hp_item.upload(hp_item);
+    {
+        std::vector<int4> t;   // records in the order of the items
+        t.reserve(3 * group.size() + 1);
+        for (int32_t k : group) t.insert(t.end(), trec.begin() + 3 * static_cast<size_t>(k), trec.begin() + 3 * static_cast<size_t>(k) + 3);
+        if (t.empty()) t.push_back(int4{0, 0, 0, 0});
+        h->tiny.upload(t);
+    }
     h->desc.upload(desc);
     if (ftab.empty()) ftab.push_back(int4{0, 0, 0, 0});
     h->ftab.upload(ftab);
     h->rmap.upload(rmap);
-    h->ninv = 0;
-    for (int32_t k = 0; k < nc; ++k) h->ninv += inv_item[k] >= 0 ? 1 : 0;
-    h->inv_item.upload(inv_item);
-    h->trsm_first.upload(tf);
     h->trsm_count.upload(tc);
-    h->upd_first.upload(uf);
-    h->upd_hp.upload(uh);
-    h->upd_count.upload(ucnt);
+    dep.resize(nc, 0);
     h->fact_dep0.upload(dep);
     h->fact_dep.alloc(nc);
     h->trsm_left.alloc(nc);
@@ -918,14 +996,11 @@ SchedArgs sched_args(spx_handle* h)
     a.desc = h->desc.p;
     a.rmap = h->rmap.p;
     a.ftab = h->ftab.p;
+    a.tiny = h->tiny.p;
     a.hp_total = h->hp_total;
     a.total_normal = h->total_normal;
-    a.trsm_first = h->trsm_first.p;
     a.trsm_count = h->trsm_count.p;
-    a.upd_first = h->upd_first.p;
-    a.upd_hp = h->upd_hp.p;
-    a.upd_count = h->upd_count.p;
-    a.hp_cblk = h->hp_cblk.p;
+    a.hp_item = h->hp_item.p;
     a.fact_dep = h->fact_dep.p;
     a.trsm_left = h->trsm_left.p;
     a.queue = h->queue.p;
@@ -937,7 +1012,6 @@ SchedArgs sched_args(spx_handle* h)
     a.status = h->status.p;
     a.timeout_ticks = h->timeout_ticks;
     a.trace = h->opt.trace ? h->trace.p : nullptr;
-    a.inv_item = h->ninv > 0 ? h->inv_item.p : nullptr;
     a.npair = h->npair;
     a.ubase = h->ubase;
     a.upair = h->upair.p;
@@ -1498,14 +1572,15 @@ int64_t spx_get_trace(spx_handle* h, int64_t* dst, int64_t cap, int32_t* kinds)
         if (cap < h->total) throw InvalidArgument("trace buffer too small");
         HIPCHK(hipMemcpy(dst, h->trace.p, static_cast<size_t>(h->total) * 4 * sizeof(int64_t), hipMemcpyDeviceToHost));
         if (kinds) {
-            std::vector<int4> d(static_cast<size_t>(h->total) * 2);
+            std::vector<int4> d(static_cast<size_t>(h->total) * 4);
             HIPCHK(hipMemcpy(d.data(), h->desc.p, d.size() * sizeof(int4), hipMemcpyDeviceToHost));
             for (int32_t i = 0; i < h->total; ++i) {
-                const int32_t kind = d[2 * i].x & 0xff;
-                kinds[4 * i + 0] = kind;         // kind
-                kinds[4 * i + 1] = d[2 * i].y;   // source cblk (the last piece of a merged update)
-                kinds[4 * i + 2] = kind == kUpdate ? d[2 * i].z : d[2 * i].y;   // target cblk
-                kinds[4 * i + 3] = kind == kUpdate ? d[2 * i + 1].x * d[2 * i + 1].z : d[2 * i].w;
+                const int4 *e = &d[4 * static_cast<size_t>(i)];
+                const int32_t kind = e[0].x & 0xff;
+                kinds[4 * i + 0] = kind == kTiny ? static_cast<int32_t>(kSmall) : kind;   // kind
+                kinds[4 * i + 1] = e[0].y;   // source cblk (the last piece of a merged update)
+                kinds[4 * i + 2] = kind == kUpdate ? e[0].z : e[0].y;   // target cblk
+                kinds[4 * i + 3] = kind == kUpdate ? e[1].x * e[1].z : e[0].w;
             }
         }
         return h->total;

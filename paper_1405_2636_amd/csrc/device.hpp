@@ -23,21 +23,29 @@ struct DevPlan {
 // Work-item kinds of the device scheduler (low byte of the first word; an
 // update keeps its merged piece count - 1 in bits 8..11; bit 12 marks a thin
 // TRSM or update item of an elimination chain: 16-row wave tiles).
-enum ItemKind : int32_t { kFact = 0, kTrsm = 1, kUpdate = 2, kSmall = 3, kInv = 4 };
+enum ItemKind : int32_t { kFact = 0, kTrsm = 1, kUpdate = 2, kSmall = 3, kInv = 4, kTiny = 5 };
 constexpr int32_t kThinItem = 1 << 12;
 constexpr int32_t kSubstItem = 1 << 13;   // TRSM of a chain block: substitution with the diagonal tiles of D (16 rows)
 constexpr int32_t kUSideItem = 1 << 14;   // (L U) such an item of the U^T rows; else of the L rows
 
-// Two int4 per item: {kind, k, a, b}, {c, d, e, f}
-//   kFact:   k
-//   kTrsm:   k, row0 = first panel row, nrows (<= 64 * (4 / ceil(w / 64)); thin: 16 * ...)
-//   kUpdate: k (source), j (target), row0 (first source panel row);
-//            mrows, col0 (first facing panel row), ncols, mbase (row-map base)
-//   kSmall:  k; first tile of k in the fused-tile table, tile count, first
-//            row-map entry of k, row-map entries of k
-//   kInv:    k (the off-diagonal tiles of L_kk^{-1} after a FACT that left them)
+// Four int4 per item (64 bytes, one load round): what the item is, and the
+// geometry of its panels, so that its first operand loads do not wait for
+// the plan's arrays.  A 64-bit offset is two words, low then high.
+//   kFact:   {kind, k, first column, 0}, {first TRSM item, TRSM items, INV item or -1, high priority},
+//            {width, stride, panel offset}, {inverse offset, 0, 0}
+//   kTrsm:   {kind, k, row0 = first panel row, nrows (<= 64 * (4 / ceil(w / 64)); thin: 16 * ...; chain: 16)},
+//            {first update item, high-priority updates, updates, 0}, {width, stride, panel offset}, {inverse offset, 0, 0}
+//   kUpdate: {kind, k (source), j (target), row0 (first source panel row)},
+//            {mrows, col0 (first facing panel row), ncols, mbase (row-map base)},
+//            {item that factors j, stride of j, panel offset of j}, {width of k, stride of k, panel offset of k}
+//   kSmall:  {kind, k, first column, 0}, {first tile of k in the fused-tile table, tile count, first
+//            row-map entry of k, row-map entries of k}, geometry of k as kFact
+//   kInv:    geometry of k as kFact (the off-diagonal tiles of the inverse after a FACT that left them)
+//   kTiny:   {kind, first block, first record in the tiny table, blocks}, -, -, -
+// Tiny table: three int4 per block, {first column, width | stride << 8 | tiles << 16, first row-map
+//   entry, row-map entries}, {panel offset, inverse offset}, {first tile in the fused-tile table, 0, 0, 0}
 // Fused-tile table: three int4 per update tile of a fused block,
-//   {j, row0, mrows, col0}, {ncols, mbase, stride of j, 0},
+//   {item that factors j, row0, mrows, col0}, {ncols, mbase, stride of j, 0},
 //   {panel offset of j: low word, high word, 0, 0}
 struct SchedArgs {
     DevPlan pl;
@@ -50,15 +58,12 @@ struct SchedArgs {
     const int4* desc;
     const int32_t* rmap;     // panel row of k -> row inside panel j, per update pair
     const int4* ftab;        // update tiles of fused small blocks
+    const int4* tiny;        // records of tiny blocks
     int32_t hp_total;        // items of the high-priority queue (FACT, TRSM, chain updates)
     int32_t total_normal;    // items of the normal queue (other updates)
-    const int32_t* trsm_first;
     const int32_t* trsm_count;
-    const int32_t* upd_first;
-    const int32_t* upd_hp;   // leading update items of a cblk that go to the high-priority queue
-    const int32_t* upd_count;
-    const int32_t* hp_cblk;  // 1 if the items of the cblk go to the high-priority queue
-    int32_t* fact_dep;
+    const int32_t* hp_item;  // per item that factors blocks (ids from 0): 1 if it goes to the high-priority queue
+    int32_t* fact_dep;       // and its unfinished update tiles
     int32_t* trsm_left;
     int32_t* queue;
     int32_t* qhead;
@@ -72,10 +77,6 @@ struct SchedArgs {
     // Deterministic mode (npair > 0): the update items of one (source,
     // target) pair are released when the source's panel solves are done and
     // the previous pair into the same target (ascending source) has finished.
-    // Blocks of elimination chains: FACT leaves the off-diagonal tiles
-    // of the inverse to an INV item, released with the panel solves (which
-    // use the diagonal tiles only) and off the chain.
-    const int32_t* inv_item;   // INV item of block k, or -1 (FACT computes the whole inverse)
     int32_t npair;          // update pairs (0: any-order mode)
     int32_t ubase;          // id of the first update item
     const int32_t* upair;   // pair of update item ubase + i
@@ -154,6 +155,9 @@ constexpr int kStatusWords = 5 * kCtrStride;
 constexpr int kSmallRows = 128;
 constexpr int kSmallMaxUpd = 64;
 constexpr int kSmallMap = 2048;
+// and those of at most kTinyW columns and kTinyRows panel rows, with at most
+// kTinyTiles update tiles and kTinyMap row-map entries, as groups
+constexpr int kTinyW = 16, kTinyRows = 32, kTinyTiles = 8, kTinyMap = 256;
 
 // Residual statistics: one 256-byte line per statistic (five of them),
 // filled by a fixed grid of blocks.

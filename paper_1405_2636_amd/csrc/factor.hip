@@ -17,6 +17,8 @@
 //                    pieces of a split supernode, the sum of their products
 //   SMALL(k)         a narrow column block (width <= 32, <= 128 rows): all
 //                    three steps and every update tile of the block at once
+//   TINY(k, ...)     the same for a group of blocks of width <= 16 with at most
+//                    32 rows, a wave each
 // Dependencies are counters: FACT(j) becomes ready when every UPDATE tile
 // into j is done, the TRSM tiles of k when FACT(k) is done, the UPDATE tiles
 // of k when its last TRSM tile is done.  FACT, TRSM and the updates into the
@@ -490,6 +492,13 @@ __device__ __forceinline__ void wave_store(const typename MM<T>::acc (&acc)[NB][
             }
 }
 
+// Geometry of a panel, from the second half of an item's descriptor
+struct Geo {
+    int f, w, ld;         // first column, width, panel stride
+    int64_t poff, doff;   // panel and kept inverse
+};
+__device__ __forceinline__ int64_t words64(int lo, int hi) { return (int64_t)(uint32_t)lo | ((int64_t)hi << 32); }
+
 // ---------------------------------------------------------------- FACT(k)
 // 1/d from the hardware estimate and two Newton-Raphson steps
 __device__ __forceinline__ double recip_nr(double d)
@@ -670,18 +679,11 @@ struct TileChol {
             column<C + 1>();
         }
     }
-    __device__ __forceinline__ void run(double* Lt_g, double* bc_g, double* dg_g, int jb_, int col0, int32_t* status)
+    // rows of the tile from LDS (column-major, ld 33), columns of the identity
+    __device__ __forceinline__ void load(const double* Lt_g)
     {
-        static_assert(NC == 8 || NC == 16 || NC == 32, "tile width");
         auto Lt = lds(Lt_g);
-        bc = lds(bc_g);
-        dg = lds(dg_g);
-        jb = jb_;
-        bad = rep = 0;
-        thr = LDL ? readlane_d(bc[kThrSlot], 0) : 0.0;
-        lane = threadIdx.x & 63;
-        asm volatile("" : "+v"(lane));   // (keeps the columns' lane masks from being formed ahead and held)
-        const int r = lane & 31;
+        const int ln = threadIdx.x & 63, r = ln & 31;
 #pragma unroll
         for (int c = 0; c < NC; ++c) v[c] = Lt[r + c * 33];
         // (all loads issued before the selects: a conditional load is a branch each)
@@ -689,8 +691,20 @@ struct TileChol {
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             asm volatile("" : "+v"(v[c]));
-            v[c] = lane >= 32 ? (c == r ? 1.0 : 0.0) : v[c];
+            v[c] = ln >= 32 ? (c == r ? 1.0 : 0.0) : v[c];
         }
+    }
+    // factors what is in v; bc: 64 entries, dg: NC entries (L D L^T) of LDS
+    __device__ __forceinline__ void run(double* bc_g, double* dg_g, double thr_, int jb_, int col0, int32_t* status)
+    {
+        static_assert(NC == 8 || NC == 16 || NC == 32, "tile width");
+        bc = lds(bc_g);
+        dg = lds(dg_g);
+        jb = jb_;
+        bad = rep = 0;
+        thr = thr_;
+        lane = threadIdx.x & 63;
+        asm volatile("" : "+v"(lane));   // (keeps the columns' lane masks from being formed ahead and held)
         d = readlane_d(v[0], 0);
         estimate<0>();
         if constexpr (LDL) {
@@ -1142,8 +1156,8 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
 // The rest of the inverse follows by block columns,
 //   D_Jc = -D_JJ sum_{c<=K<J} L_JK D_Kc,
 // dealt to the waves as they run out of row blocks (the longest columns to
-// the wave that is free first); a chain block (inv_item) leaves it to its
-// INV item.  Bound: the chain of 32-column tile factorizations.
+// the wave that is free first); a chain block leaves it to its INV item
+// (full false).  Bound: the chain of 32-column tile factorizations.
 // The right-looking form before it (trailing blocks read, updated and
 // written in memory at every 32-column step, two barriers per step) took
 // 294 us at w = 256 in FP64 and 252 us without the inverse's off-diagonal
@@ -1157,21 +1171,18 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
 // the rows below stay one product A_rows Y^T): the same with d between the
 // factors of every product of two L's, and -Y_JJ in place of -D_JJ.
 template <class T, bool LDL = false>
-__device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, double* tiles)
+__device__ __noinline__ void task_fact(const SchedArgs& a, Geo g, bool full, double* Lt, double* tiles)
 {
-    const DevPlan& pl = a.pl;
-    const int f = uni(pl.fcol[k]);
-    const int w = uni(pl.lcol[k]) - f + 1;
-    const int64_t ld = pl.stride[k];
-    T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
-    T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
+    const int f = uni(g.f), w = uni(g.w);
+    const int64_t ld = g.ld;
+    T* A = static_cast<T*>(a.panels) + g.poff;
+    T* D = static_cast<T*>(a.dinv) + g.doff;
     const GOp gA = make_gop(A, ld * w, 0, 1, ld);           // A(i, p) at i + p*ld
     const GOp gD = make_gop(D, (int64_t)w * w, 0, 1, w);    // D(i, p) at i + p*w
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     double* bc = Lt + kNB * 33;
     __shared__ int s_x[8], s_d;      // blocks of row block i published (i + 1: D_ii too); tiles factored
     __shared__ double dd[LDL ? 256 : 1];   // (L D L^T) the pivots
-    const bool full = a.inv_item == nullptr || uni(a.inv_item[k]) < 0;
     const int nb = (w + kNB - 1) / kNB;
     if (tid < 8) s_x[tid] = 0;
     if (tid == 8) s_d = 0;
@@ -1224,7 +1235,8 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
             __atomic_signal_fence(__ATOMIC_SEQ_CST);
         }
         TileChol<kNB, LDL> tc;
-        tc.run(Lt, bc, LDL ? dd + i0 : bc, jb, f + i0, a.status);
+        tc.load(Lt);
+        tc.run(bc, LDL ? dd + i0 : bc, LDL ? readlane_d(lds(bc)[kThrSlot], 0) : 0.0, jb, f + i0, a.status);
         tc.put_inverse(tiles + i * kTSz, -1.0);
         publish_lds(&s_d, i + 1);
         // (masked entries go past the arrays, where the stores are dropped)
@@ -1290,14 +1302,12 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, int k, double* Lt, do
 // 410), this one 248 us (215), 145 us on the chain without the inverses'
 // off-diagonal blocks.
 template <class T>
-__device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt, double* tiles)
+__device__ __noinline__ void task_fact_lu(const SchedArgs& a, Geo g, bool full, double* Lt, double* tiles)
 {
-    const DevPlan& pl = a.pl;
-    const int f = uni(pl.fcol[k]);
-    const int w = uni(pl.lcol[k]) - f + 1;
-    const int64_t ld = pl.stride[k];
-    T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
-    T* X = static_cast<T*>(a.dinv) + pl.dinv_off[k];
+    const int f = uni(g.f), w = uni(g.w);
+    const int64_t ld = g.ld;
+    T* A = static_cast<T*>(a.panels) + g.poff;
+    T* X = static_cast<T*>(a.dinv) + g.doff;
     T* Y = X + a.uinv;
     const GOp gA = make_gop(A, ld * w, 0, 1, ld);    // A(i, p) at i + p*ld
     const GOp gAt = make_gop(A, ld * w, 0, ld, 1);   // A^T
@@ -1405,7 +1415,7 @@ __device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt,
         for (int J = max(0, i1 - 1); J < i2; ++J) step(i2, J, S2);
         tile(i2, S2);
     }
-    if (a.inv_item != nullptr && uni(a.inv_item[k]) >= 0) return;   // (left to the INV item)
+    if (!full) return;   // (left to the INV item)
     // block columns 0 .. nb - 2 of both inverses, dealt as in task_fact
     for (int t = 0; t < 4; ++t) {
         const int c = (t & 2) == 0 ? wave : 7 - wave;
@@ -1421,13 +1431,12 @@ __device__ __noinline__ void task_fact_lu(const SchedArgs& a, int k, double* Lt,
 // inverse is then built beside the chain instead of inside FACT): the block
 // columns of inv_column, two per wave; L U: of both inverses.
 template <class T, bool LDL, bool LU>
-__device__ __noinline__ void task_inv(const SchedArgs& a, int k)
+__device__ __noinline__ void task_inv(const SchedArgs& a, Geo g)
 {
-    const DevPlan& pl = a.pl;
-    const int w = uni(pl.lcol[k] - pl.fcol[k] + 1);
-    const int64_t ld = pl.stride[k];
-    const T* A = static_cast<const T*>(a.panels) + pl.panel_off[k];
-    T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
+    const int w = uni(g.w);
+    const int64_t ld = g.ld;
+    const T* A = static_cast<const T*>(a.panels) + g.poff;
+    T* D = static_cast<T*>(a.dinv) + g.doff;
     const GOp gA = make_gop(A, ld * w, 0, 1, ld);
     const int tid = threadIdx.x, wave = uni(tid >> 6), nb = (w + kNB - 1) / kNB;
     __shared__ int s_x[8], s_d;
@@ -1458,15 +1467,14 @@ __device__ __noinline__ void task_inv(const SchedArgs& a, int k)
 // RB: 16-row blocks per wave tile (4: 64-row wave tiles; 1: the thin items
 // of elimination chains, a quarter of the work per wave).
 template <class T, int RB = 4>
-__device__ __noinline__ void task_trsm(const SchedArgs& a, int k, int row0, int nrows, int64_t poff = 0,
+__device__ __noinline__ void task_trsm(const SchedArgs& a, Geo g, int row0, int nrows, int64_t poff = 0,
                                        int64_t doff = 0)
 {
-    const DevPlan& pl = a.pl;
-    const int w = pl.lcol[k] - pl.fcol[k] + 1;
-    const int64_t ld = pl.stride[k];
-    T* P = static_cast<T*>(a.panels) + poff + pl.panel_off[k];
+    const int w = g.w;
+    const int64_t ld = g.ld;
+    T* P = static_cast<T*>(a.panels) + poff + g.poff;
     auto B = glob(P + row0);
-    const T* D = static_cast<const T*>(a.dinv) + doff + pl.dinv_off[k];
+    const T* D = static_cast<const T*>(a.dinv) + doff + g.doff;
     const int wave = threadIdx.x >> 6;
     typename MM<T>::acc acc[4][RB];
     zero_acc(acc);
@@ -1505,15 +1513,14 @@ __device__ __noinline__ void task_trsm(const SchedArgs& a, int k, int row0, int 
 // with all of its blocks (576 products in a row at 256 columns) took 36 us
 // on the chain, this form 20 to 24 us.
 template <class T, bool LDL, bool LU>
-__device__ __noinline__ void task_trsm_chain(const SchedArgs& a, int k, int row0, int nrows, int uside, double* tiles)
+__device__ __noinline__ void task_trsm_chain(const SchedArgs& a, Geo g, int row0, int nrows, int uside, double* tiles)
 {
     typedef typename MM<T>::acc acc_t;
-    const DevPlan& pl = a.pl;
-    const int w = uni(pl.lcol[k] - pl.fcol[k] + 1);
-    const int64_t ld = pl.stride[k];
-    const T* A = static_cast<const T*>(a.panels) + pl.panel_off[k];
-    T* P = static_cast<T*>(a.panels) + pl.panel_off[k] + (LU && uside ? a.upanel : 0);
-    const T* D = static_cast<const T*>(a.dinv) + pl.dinv_off[k] + (LU && !uside ? a.uinv : 0);
+    const int w = uni(g.w);
+    const int64_t ld = g.ld;
+    const T* A = static_cast<const T*>(a.panels) + g.poff;
+    T* P = static_cast<T*>(a.panels) + g.poff + (LU && uside ? a.upanel : 0);
+    const T* D = static_cast<const T*>(a.dinv) + g.doff + (LU && !uside ? a.uinv : 0);
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     const int nb = (w + kNB - 1) / kNB;
     const GOp gP = make_gop(P, ld * w, row0, 1, ld);
@@ -1631,7 +1638,8 @@ __device__ __noinline__ void task_trsm_chain(const SchedArgs& a, int k, int row0
 // RB = 1: a thin tile of an elimination chain, at most 64 x 64, each wave
 // 16 rows of it (a quarter of the work of a 64-row wave tile).
 template <class T, bool LDL = false, bool LU = false, int RB = 4>
-__device__ __noinline__ void task_update(const SchedArgs& a, const int4 d0, const int4 d1, int* rpos_g, int* cpos_g)
+__device__ __noinline__ void task_update(const SchedArgs& a, const int4 d0, const int4 d1, const int4 d2, const int4 d3,
+                                         int* rpos_g, int* cpos_g)
 {
     // the row and column maps are LDS arrays of the calling kernel: stated,
     // so that their accesses are LDS operations without a generic-address
@@ -1641,8 +1649,8 @@ __device__ __noinline__ void task_update(const SchedArgs& a, const int4 d0, cons
     const DevPlan& pl = a.pl;
     const int k = d0.y, j = d0.z, row0 = d0.w, np = ((d0.x >> 8) & 15) + 1;
     const int mrows = d1.x, col0 = d1.y, ncols = d1.z, mbase = d1.w;
-    const int64_t ldj = pl.stride[j];
-    auto Cg = glob(static_cast<T*>(a.panels) + pl.panel_off[j]);
+    const int64_t ldj = d2.y;
+    auto Cg = glob(static_cast<T*>(a.panels) + words64(d2.z, d2.w));
     const int tid = threadIdx.x, wave = tid >> 6;
     if (tid < mrows) rpos[tid] = a.rmap[mbase + row0 + tid];
     if (tid < ncols) cpos[tid] = a.rmap[mbase + col0 + tid];
@@ -1652,20 +1660,24 @@ __device__ __noinline__ void task_update(const SchedArgs& a, const int4 d0, cons
     const int c0 = square ? 64 * (wave >> 1) : 0;
     const int mv = min(16 * RB, mrows - r0), nv = min(64, ncols - c0);
     if (mv > 0 && nv > 0) {
-        const int fk = pl.fcol[k];
         // half 0: W = X Y^T with X the rows and Y the facing rows of the L
         // panels (L U: Y from the U^T panels); half 1 (L U, rows below j's
         // diagonal block only): X from the U^T panels, Y from the L panels
-        const int wj = pl.lcol[j] - pl.fcol[j] + 1;
+        const int wj = LU ? pl.lcol[j] - pl.fcol[j] + 1 : 0;
         const int nhalf = (LU && rpos[r0 + mv - 1] >= wj) ? 2 : 1;
         for (int half = 0; half < nhalf; ++half) {
             typename MM<T>::acc acc[4][RB];
             zero_acc(acc);
             const int64_t xo = (LU && half == 1) ? a.upanel : 0, yo = (LU && half == 0) ? a.upanel : 0;
-            for (int p = k - np + 1; p <= k; ++p) {
-                const int fp = pl.fcol[p], w = pl.lcol[p] - fp + 1, sh = fk - fp;
-                const int64_t ld = pl.stride[p];
-                const T* A = static_cast<const T*>(a.panels) + pl.panel_off[p];
+            // piece p = k first (its geometry is in the descriptor); a piece
+            // before it has as many more panel rows as it has columns, and
+            // its panel ends where the next one begins
+            int w = d3.x, sh = 0;
+            int64_t ld = d3.y, po = words64(d3.z, d3.w);
+            for (int p = k;; --p) {
+                int wn = 0;   // width of the next piece, on its way meanwhile
+                if (p > k - np + 1) wn = pl.lcol[p - 1] - pl.fcol[p - 1] + 1;
+                const T* A = static_cast<const T*>(a.panels) + po;
                 if constexpr (LDL)
                     tile_gemm<4, T, RB, true>(acc, make_gop(A, ld * w, row0 + r0 + sh, 1, ld),
                                               make_gop(A, ld * w, col0 + c0 + sh, 1, ld), w, a.split != 0,
@@ -1673,6 +1685,11 @@ __device__ __noinline__ void task_update(const SchedArgs& a, const int4 d0, cons
                 else
                     tile_gemm<4, T, RB>(acc, make_gop(A + xo, ld * w, row0 + r0 + sh, 1, ld),
                                         make_gop(A + yo, ld * w, col0 + c0 + sh, 1, ld), w, a.split != 0);
+                if (p == k - np + 1) break;
+                sh += wn;
+                ld += wn;
+                po -= ld * wn;
+                w = wn;
             }
             if constexpr (LU) {
                 auto Cu = Cg + (half == 1 ? a.upanel : 0);
@@ -1728,12 +1745,12 @@ __device__ __noinline__ void release_pairs(const SchedArgs& a, int k)
         if (__hip_atomic_fetch_add(&a.pdep[p], -1, __ATOMIC_RELAXED, AGENT) == 1) push_pair(a, p);
 }
 
-// Count down one update tile of target j (any lane); queue j when it was the
-// last one.
+// Count down one update tile of a target (j: the item that factors it); queue
+// that item when it was the last one (any lane).
 __device__ __forceinline__ void finish_update(const SchedArgs& a, int j)
 {
     if (__hip_atomic_fetch_add(&a.fact_dep[j], -1, __ATOMIC_RELAXED, AGENT) != 1) return;
-    const bool hp = a.hp_cblk[j] != 0;
+    const bool hp = a.hp_item[j] != 0;
     const int slot = __hip_atomic_fetch_add(hp ? a.hp_tail : a.qtail, 1, __ATOMIC_RELAXED, AGENT);
     if (slot < (hp ? a.hp_total : a.total_normal))
         __hip_atomic_store(&(hp ? a.hp_queue : a.queue)[slot], j, __ATOMIC_RELAXED, AGENT);
@@ -1764,17 +1781,13 @@ static_assert((kSLd * kNB * sizeof(float) + (kSmallMap + 8 * kSmallMaxUpd) * siz
 static_assert(kSmallRows * kNB % kThreads == 0, "rows below per thread");
 
 template <class T, bool LDL = false>
-__device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const int4 d1, double* Lt, double* Dt, T* Pb)
+__device__ __noinline__ void task_small(const SchedArgs& a, Geo g, const int4 d1, double* Lt, double* Dt, T* Pb)
 {
-    const DevPlan& pl = a.pl;
-    const int k = d0.y;
     const int tfirst = d1.x, nupd = d1.y, mstart = d1.z, mlen = d1.w;
-    const int f = pl.fcol[k];
-    const int w = pl.lcol[k] - f + 1;
-    const int ld = pl.stride[k];
+    const int f = g.f, w = g.w, ld = g.ld;
     const int R = ld - w;   // rows below the diagonal block
-    T* A = static_cast<T*>(a.panels) + pl.panel_off[k];
-    T* D = static_cast<T*>(a.dinv) + pl.dinv_off[k];
+    T* A = static_cast<T*>(a.panels) + g.poff;
+    T* D = static_cast<T*>(a.dinv) + g.doff;
     T* S = Pb;                                                // S[r + c*kSLd] for panel rows r >= w
     int* smap = reinterpret_cast<int*>(S + kSLd * kNB);       // row-map entries mstart ..
     int* dtab = smap + kSmallMap;                             // per tile: j, row0, mrows, col0, ncols, map base, ldj
@@ -1801,13 +1814,14 @@ __device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const
         e[4] = u1.x;
         e[5] = u1.y - mstart;
         e[6] = u1.z;
-        dpo[tid] = (int64_t)(uint32_t)u2.x | ((int64_t)u2.y << 32);
+        dpo[tid] = words64(u2.x, u2.y);
     }
     __syncthreads();
     if (wave == 0) {
         auto tile = [&](auto nc) {
             TileChol<decltype(nc)::value, LDL> tc;
-            tc.run(Lt, bc, bc + 64, w, f, a.status);
+            tc.load(Lt);
+            tc.run(bc, bc + 64, LDL ? readlane_d(lds(bc)[kThrSlot], 0) : 0.0, w, f, a.status);
             tc.put_inverse(Dt, 1.0);
             tc.put_rows([&](int r, int c, double x) { lds(Lt)[r + 33 * c] = x; });
         };
@@ -1874,6 +1888,128 @@ __device__ __noinline__ void task_small(const SchedArgs& a, const int4 d0, const
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();   // every atomic of the item has completed
     if (tid < nupd) finish_update(a, dtab[8 * tid]);
+}
+
+// ---------------------------------------------------------------- tiny blocks
+// Column blocks of at most 16 columns and 32 panel rows, a wave each, up to
+// kTinyGroup blocks of one dependency level per item (no block of a level
+// depends on another one).  At the bottom of a 2-D problem or of a batch
+// nearly all blocks are a few columns wide; as an item of a whole workgroup
+// each of them cost about ten round trips to memory and four barriers for a
+// few hundred flops.  Here the round trips of a claim, of the record, of the
+// operands and of the counters are shared by the group, and the whole panel
+// goes through the tile factorization: its rows below the block are more
+// rows of the tile (l_rc = (a_rc - sum) / l_cc, stepped with the block's own
+// columns), so that L comes out in one pass.  The update tiles are formed
+// from LDS, row by lane, two columns at a time, and scattered by atomics.
+// LDS per wave: rows of L (stride NC + 2), the row map, the target of every
+// facing row, the broadcast buffer.
+constexpr int kTinyLds = 1024;   // doubles per wave
+static_assert(kTinyRows * (kTinyW + 2) + kTinyMap / 2 + 2 * kTinyRows + 64 + kTinyW + 4 * kTinyTiles <= kTinyLds, "LDS of a tiny block");
+static_assert((kThreads / 64) * kTinyLds <= kTiles * kTSz, "LDS of a group of tiny blocks");
+
+template <class T, int NC, bool LDL>
+__device__ __forceinline__ void tiny_block(const SchedArgs& a, const int4 q0, const int4 q1, int tfirst, double thr, double* ws)
+{
+    constexpr int LS = NC + 2;
+    const int f = uni(q0.x), w = uni(q0.y) & 255, ld = (uni(q0.y) >> 8) & 255, nupd = uni(q0.y) >> 16, mstart = uni(q0.z),
+              mlen = uni(q0.w);
+    T* A = static_cast<T*>(a.panels) + words64(uni(q1.x), uni(q1.y));
+    T* D = static_cast<T*>(a.dinv) + words64(uni(q1.z), uni(q1.w));
+    const int lane = threadIdx.x & 63, r = lane & 31;
+    auto S = lds(ws);
+    auto smap = reinterpret_cast<__attribute__((address_space(3))) int*>(S + kTinyRows * (kTinyW + 2));
+    auto tab = smap + kTinyMap;             // facing row r: map base, stride and panel offset of its target
+    auto dt = tab + 4 * kTinyRows;          // tile u: gate, first and last + 1 facing row, map base, stride, offset
+    double* bc = ws + kTinyRows * (kTinyW + 2) + (kTinyMap + 4 * kTinyRows + 8 * kTinyTiles) / 2;
+    const GOp gA = make_gop(A, (int64_t)ld * w, 0, 1, ld);
+    T av[NC];
+#pragma unroll
+    for (int c = 0; c < NC; ++c) av[c] = gload<T>(gA, c < w && r < ld ? r * gA.si + c * gA.sk : kOffNone);
+    int mv[kTinyMap / 64];
+#pragma unroll
+    for (int q = 0; q < kTinyMap / 64; ++q) mv[q] = a.rmap[mlen > 0 ? mstart + min(lane + 64 * q, mlen - 1) : 0];
+    int4 u0 = {0, 0, 0, 0}, u1 = u0, u2 = u0;
+    if (lane < nupd) {
+        const int4* ft = a.ftab + 3 * (int64_t)(tfirst + lane);
+        u0 = ft[0];
+        u1 = ft[1];
+        u2 = ft[2];
+    }
+    TileChol<NC, LDL> tc;
+#pragma unroll
+    for (int c = 0; c < NC; ++c) tc.v[c] = lane >= 32 || c >= w ? (c == r ? 1.0 : 0.0) : (double)av[c];
+    tc.run(bc, bc + 64, thr, w, f, a.status);
+    // L and the inverse to memory; the rows of L, as stored, to LDS
+    const double dr = LDL ? lds(bc)[64 + min(lane, NC - 1)] : 0.0;
+    auto oA = glob(A), oD = glob(D);
+#pragma unroll
+    for (int c = 0; c < NC; ++c) {
+        if (c < w) {
+            if (lane < 32) {
+                if (r >= c && r < ld) oA[r + c * ld] = (T)(LDL && r == c ? dr : tc.v[c]);
+            } else if (r <= c) {
+                oD[c + r * w] = (T)tc.v[c];
+            }
+        }
+    }
+    if (lane < 32) {
+#pragma unroll
+        for (int c = 0; c < NC; ++c) S[r * LS + c] = c < w ? (double)(T)tc.v[c] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < kTinyMap / 64; ++q) smap[lane + 64 * q] = mv[q];
+    if (lane < nupd) {
+        auto e = dt + 8 * lane;
+        e[0] = u0.w;               // first facing row
+        e[1] = u0.w + u1.x;        // and past the last
+        e[2] = u1.y - mstart;
+        e[3] = u1.z;
+        e[4] = u2.x;
+        e[5] = u2.y;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
+    for (int u = 0; u < nupd; ++u) {
+        const int b = dt[8 * u], e = dt[8 * u + 1];
+        if (lane < 32 && r >= b && r < e) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) tab[4 * r + i] = dt[8 * u + 2 + i];
+        }
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    // C_j[rmap(r), rmap(c)] -= L_r . L_c (L D L^T: L_r D L_c), r >= c; the
+    // halves of the wave take the facing rows c alternately
+    double own[NC];
+#pragma unroll
+    for (int t = 0; t < NC; ++t) {
+        const double s = S[min(r, ld - 1) * LS + t];
+        own[t] = !LDL ? s : t < w ? s * lds(bc)[64 + t] : 0.0;   // (pivots past w are undefined)
+    }
+    if (nupd > 0)
+        for (int c = w + (lane >> 5); c < ld; c += 2) {
+            double acc = 0.0;
+#pragma unroll
+            for (int t = 0; t < NC; ++t) acc += own[t] * S[c * LS + t];
+            const int mb = tab[4 * c], ldj = tab[4 * c + 1];
+            auto Cg = glob(static_cast<T*>(a.panels) + words64(tab[4 * c + 2], tab[4 * c + 3]));
+            if (r >= c && r < ld)
+                __hip_atomic_fetch_add(Cg + (int64_t)smap[mb + c] * ldj + smap[mb + r], (T)(-acc), __ATOMIC_RELAXED, AGENT);
+        }
+    __builtin_amdgcn_s_waitcnt(0);   // the block's atomics have completed
+    if (lane < nupd) finish_update(a, u0.x);
+}
+
+template <class T, bool LDL>
+__device__ __noinline__ void task_tiny(const SchedArgs& a, int first, int count, double thr, double* tiles)
+{
+    const int wave = uni((int)threadIdx.x >> 6);
+    for (int q = wave; q < count; q += kThreads / 64) {
+        const int4* t = a.tiny + 3 * (int64_t)(first + q);
+        const int4 q0 = t[0], q1 = t[1];
+        const int tf = uni(t[2].x);
+        if ((uni(q0.y) & 255) <= 8) tiny_block<T, 8, LDL>(a, q0, q1, tf, thr, tiles + wave * kTinyLds);
+        else tiny_block<T, 16, LDL>(a, q0, q1, tf, thr, tiles + wave * kTinyLds);
+    }
 }
 
 // ---------------------------------------------------------------- scheduler
@@ -1955,44 +2091,46 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
         if (item < 0) break;
         if (tid < 64) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         __syncthreads();
-        const int4 d0 = a.desc[2 * item];
-        const int4 d1 = a.desc[2 * item + 1];
+        const int4 d0 = a.desc[4 * (int64_t)item], d1 = a.desc[4 * (int64_t)item + 1];
+        const int4 d2 = a.desc[4 * (int64_t)item + 2], d3 = a.desc[4 * (int64_t)item + 3];
+        const Geo g{d0.z, d2.x, d2.y, words64(d2.z, d2.w), words64(d3.x, d3.y)};   // (not of an update)
         const int kind = d0.x & 0xff;   // (bits 8..11 of an update: pieces merged - 1; bit 12: thin item)
         const bool thin = (d0.x & kThinItem) != 0;
         if (kind == kFact) {
             __builtin_amdgcn_s_setprio(3);
-            if constexpr (LU) task_fact_lu<T>(a, d0.y, Lt, tiles);
-            else task_fact<T, LDL>(a, d0.y, Lt, tiles);
+            if constexpr (LU) task_fact_lu<T>(a, g, d1.z < 0, Lt, tiles);
+            else task_fact<T, LDL>(a, g, d1.z < 0, Lt, tiles);
             __builtin_amdgcn_s_setprio(0);
         } else if (kind == kTrsm) {
             __builtin_amdgcn_s_setprio(2);
             if (d0.x & kSubstItem) {
-                task_trsm_chain<T, LDL, LU>(a, d0.y, d0.z, d0.w, (d0.x & kUSideItem) != 0, tiles);
+                task_trsm_chain<T, LDL, LU>(a, g, d0.z, d0.w, (d0.x & kUSideItem) != 0, tiles);
             } else if constexpr (LU) {
                 if (thin) {
-                    task_trsm<T, 1>(a, d0.y, d0.z, d0.w, 0, a.uinv);
-                    task_trsm<T, 1>(a, d0.y, d0.z, d0.w, a.upanel, 0);
+                    task_trsm<T, 1>(a, g, d0.z, d0.w, 0, a.uinv);
+                    task_trsm<T, 1>(a, g, d0.z, d0.w, a.upanel, 0);
                 } else {
-                    task_trsm<T>(a, d0.y, d0.z, d0.w, 0, a.uinv);
-                    task_trsm<T>(a, d0.y, d0.z, d0.w, a.upanel, 0);
+                    task_trsm<T>(a, g, d0.z, d0.w, 0, a.uinv);
+                    task_trsm<T>(a, g, d0.z, d0.w, a.upanel, 0);
                 }
             } else {
                 if (thin) {
-                    task_trsm<T, 1>(a, d0.y, d0.z, d0.w);
+                    task_trsm<T, 1>(a, g, d0.z, d0.w);
                 } else {
-                    task_trsm<T>(a, d0.y, d0.z, d0.w);
+                    task_trsm<T>(a, g, d0.z, d0.w);
                 }
             }
             __builtin_amdgcn_s_setprio(0);
         } else if (kind == kUpdate) {
-            if (thin) task_update<T, LDL, LU, 1>(a, d0, d1, rpos, cpos);
-            else task_update<T, LDL, LU>(a, d0, d1, rpos, cpos);
+            if (thin) task_update<T, LDL, LU, 1>(a, d0, d1, d2, d3, rpos, cpos);
+            else task_update<T, LDL, LU>(a, d0, d1, d2, d3, rpos, cpos);
         } else if (kind == kInv) {
             __builtin_amdgcn_s_setprio(2);
-            task_inv<T, LDL, LU>(a, d0.y);
+            task_inv<T, LDL, LU>(a, g);
             __builtin_amdgcn_s_setprio(0);
         } else if constexpr (!LU) {
-            task_small<T, LDL>(a, d0, d1, Lt, Dt, Pb);
+            if (kind == kTiny) task_tiny<T, LDL>(a, d0.z, d0.w, LDL ? Lt[kNB * 33 + kThrSlot] : 0.0, tiles);
+            else task_small<T, LDL>(a, g, d1, Lt, Dt, Pb);
         }
         // every wave's stores and atomics have completed before the barrier
         // (FACT and TRSM items ran at raised wave priority: they are on the
@@ -2005,30 +2143,29 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
             if (kind == kFact) {
                 // the panel solves; a chain block (high priority) also its
                 // INV item, in the normal queue
-                if (a.hp_cblk[d0.y]) {
-                    hf = a.trsm_first[d0.y];
-                    hc = a.trsm_count[d0.y];
-                    const int ii = a.inv_item ? a.inv_item[d0.y] : -1;
-                    if (ii >= 0) { nf = ii; nc = 1; }
+                if (d1.w) {
+                    hf = d1.x;
+                    hc = d1.y;
+                    if (d1.z >= 0) { nf = d1.z; nc = 1; }
                 } else {
-                    nf = a.trsm_first[d0.y];
-                    nc = a.trsm_count[d0.y];
+                    nf = d1.x;
+                    nc = d1.y;
                 }
             } else if (kind == kTrsm) {
                 if (__hip_atomic_fetch_add(&a.trsm_left[d0.y], -1, __ATOMIC_RELAXED, AGENT) == 1) {
                     if (a.npair > 0) {
                         s_rel = d0.y;   // its pairs, below
                     } else {
-                        hf = a.upd_first[d0.y];
-                        hc = a.upd_hp[d0.y];
+                        hf = d1.x;
+                        hc = d1.y;
                         nf = hf + hc;
-                        nc = a.upd_count[d0.y] - hc;
+                        nc = d1.z - hc;
                     }
                 }
             } else if (kind == kUpdate) {
-                if (__hip_atomic_fetch_add(&a.fact_dep[d0.z], -1, __ATOMIC_RELAXED, AGENT) == 1) {
-                    if (a.hp_cblk[d0.z]) { hf = d0.z; hc = 1; }
-                    else { nf = d0.z; nc = 1; }
+                if (__hip_atomic_fetch_add(&a.fact_dep[d2.x], -1, __ATOMIC_RELAXED, AGENT) == 1) {
+                    if (a.hp_item[d2.x]) { hf = d2.x; hc = 1; }
+                    else { nf = d2.x; nc = 1; }
                 }
                 if (a.npair > 0) {
                     // the pair's last item releases the next pair into the
@@ -2079,7 +2216,11 @@ __global__ void __launch_bounds__(kThreads, 2) update_bench_kernel(SchedArgs a, 
 {
     __shared__ int rpos[256], cpos[128];
     const int4 t = tiles[blockIdx.x % ntiles];
-    task_update<T, LDL, false>(a, int4{kUpdate, 0, 1, t.x}, int4{t.y, t.z, t.w, mbase}, rpos, cpos);
+    const DevPlan& pl = a.pl;
+    const int64_t po = pl.panel_off[1];
+    task_update<T, LDL, false>(a, int4{kUpdate, 0, 1, t.x}, int4{t.y, t.z, t.w, mbase},
+                               int4{1, pl.stride[1], (int)(po & 0xffffffff), (int)(po >> 32)},
+                               int4{pl.lcol[0] - pl.fcol[0] + 1, pl.stride[0], 0, 0}, rpos, cpos);
 }
 
 hipError_t launch_update_bench(const SchedArgs& a, bool f32, bool ldl, const int4* tiles, int ntiles, int mbase,

@@ -162,81 +162,65 @@ __device__ __forceinline__ void gstore_s(const GOp& g, int voff, int soff, float
 // beyond the caller's bounds produce results that are not stored.
 // Y feeds operand A and X operand B (lane layout in MM), so
 //   acc[bi][bj][v] = C(16*bj + l%16, 16*bi + drow(v, l/16))
-// and the 16 lanes of a result slot cover 16 consecutive rows of C.  The
-// inner dimension advances 8 at a time through register buffers: FP32 uses
-// three (the operands of the next 16 in flight while the products of the
-// current 8 are issued); FP64 two (the next 8 in flight): with a third, the
-// 128 accumulator registers and the operands exceed the 256 registers of a
-// wave at two workgroups per CU, and the spilled operands each cost a wait
-// for every outstanding load.
+// and the 16 lanes of a result slot cover 16 consecutive rows of C.  Rows of
+// X and of Y are consecutive in memory (si of both is the element size).
+// The inner dimension advances 4 at a time through a ring of NBUF operand
+// buffers, each loaded again as soon as its products are issued: NBUF - 1
+// steps are in flight (a step is 16 products of 64 cycles in FP64, 32 in
+// FP32).  Four buffers in FP64 and eight in FP32 fill the 256 registers of a
+// wave at two workgroups per CU beside the accumulators; six and sixteen
+// spill.  Update tiles alone with an inner dimension of 2048: 62 TFLOP/s in
+// FP64 and 122 in FP32, 52 and 102 with two and three buffers of 8 inner
+// indices whose 16 offsets were formed anew per chunk (100^3 scheduler
+// kernel 89.9 -> 86.4 ms).  A load between every two products instead of a
+// step's loads in one go: 53 and 126.
+// The offset of a step is added to one vector register per operand, the
+// 16-row blocks of a step are immediate offsets of it: both are range-checked.
 template <int NB, class T, int RB = 4>
 __device__ __forceinline__ void wave_gemm(typename MM<T>::acc (&acc)[NB][RB], const GOp& X, const GOp& Y, int K)
 {
+    constexpr int e = (int)sizeof(T);
+    constexpr int NBUF = sizeof(T) == 8 ? 4 : 8;
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lk = lane >> 4;
-    const int nchunks = (K + 7) >> 3;
-    if (nchunks <= 0) return;
-    int xo[2][RB], yo[2][NB];
+    const int steps = (K + 3) >> 2;
+    if (steps <= 0) return;
+    int xo = X.off + li * e + lk * X.sk, yo = Y.off + li * e + lk * Y.sk;
+    const int dx = 4 * X.sk, dy = 4 * Y.sk;
+    T xs[NBUF][RB], ys[NBUF][NB];
+    // (scheduling barriers keep every group of loads behind the products
+    // whose buffer it fills and ahead of the next ones; left alone, the
+    // compiler sinks the loads next to their uses and waits for them)
+    auto load = [&](int q) {
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+        for (int b = 0; b < RB; ++b) xs[q][b] = gload<T>(X, xo + 16 * e * b);
 #pragma unroll
-        for (int b = 0; b < RB; ++b) xo[u][b] = X.off + (16 * b + li) * X.si + (4 * u + lk) * X.sk;
-#pragma unroll
-        for (int b = 0; b < NB; ++b) yo[u][b] = Y.off + (16 * b + li) * Y.si + (4 * u + lk) * Y.sk;
-    }
-    const int dx = 8 * X.sk, dy = 8 * Y.sk;
-    T xa[2][RB], ya[2][NB], xb[2][RB], yb[2][NB], xc[2][RB], yc[2][NB];
-    // (scheduling barriers keep every group of loads ahead of the products
-    // it is meant to overlap; left alone, the compiler sinks the FP32 loads
-    // next to their uses and waits for them)
-    auto load = [&](T (&xs)[2][RB], T (&ys)[2][NB], int ch) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-#pragma unroll
-            for (int b = 0; b < RB; ++b) xs[u][b] = gload<T>(X, xo[u][b] + ch * dx);
-#pragma unroll
-            for (int b = 0; b < NB; ++b) ys[u][b] = gload<T>(Y, yo[u][b] + ch * dy);
-        }
+        for (int b = 0; b < NB; ++b) ys[q][b] = gload<T>(Y, yo + 16 * e * b);
+        xo += dx;
+        yo += dy;
         __builtin_amdgcn_sched_barrier(0);
     };
-    auto mma = [&](const T (&xs)[2][RB], const T (&ys)[2][NB]) {
+    auto mma = [&](int q) {
 #pragma unroll
-        for (int u = 0; u < 2; ++u)
+        for (int bi = 0; bi < NB; ++bi)
 #pragma unroll
-            for (int bi = 0; bi < NB; ++bi)
-#pragma unroll
-                for (int bj = 0; bj < RB; ++bj) acc[bi][bj] = MM<T>::mfma(ys[u][bi], xs[u][bj], acc[bi][bj]);
+            for (int bj = 0; bj < RB; ++bj) acc[bi][bj] = MM<T>::mfma(ys[q][bi], xs[q][bj], acc[bi][bj]);
         __builtin_amdgcn_sched_barrier(0);
     };
-    // (reads past the last chunk repeat it and are not used)
-    const int last = nchunks - 1;
-    if constexpr (sizeof(T) == 8) {
-        (void)xc;
-        (void)yc;
-        load(xa, ya, 0);
-        int ch = 0;
-        for (; ch + 2 <= nchunks; ch += 2) {
-            load(xb, yb, ch + 1);
-            mma(xa, ya);
-            load(xa, ya, min(ch + 2, last));
-            mma(xb, yb);
+    // (steps past the last one read zeros past the array, or entries that are not used)
+#pragma unroll
+    for (int q = 0; q < NBUF - 1; ++q) load(q);
+    int st = 0;
+    for (; st + NBUF <= steps; st += NBUF) {
+#pragma unroll
+        for (int q = 0; q < NBUF; ++q) {
+            load((q + NBUF - 1) % NBUF);
+            mma(q);
         }
-        if (ch < nchunks) mma(xa, ya);
-    } else {
-        load(xa, ya, 0);
-        load(xb, yb, min(1, last));
-        int ch = 0;
-        for (; ch + 3 <= nchunks; ch += 3) {
-            load(xc, yc, min(ch + 2, last));
-            mma(xa, ya);
-            load(xa, ya, min(ch + 3, last));
-            mma(xb, yb);
-            load(xb, yb, min(ch + 4, last));
-            mma(xc, yc);
-        }
-        if (ch < nchunks) mma(xa, ya);
-        if (ch + 1 < nchunks) mma(xb, yb);
     }
+#pragma unroll
+    for (int q = 0; q < NBUF - 1; ++q)
+        if (st + q < steps) mma(q);
 }
 
 // L D L^T update products: acc += X (Y D)^T, the facing operand Y scaled by

@@ -39,8 +39,8 @@ hipError_t launch_bwd_off(const SweepArgs& a, const OffItem* items, int count, b
 hipError_t launch_bwd_diag(const SweepArgs& a, const DiagItem* items, int count, int lanes, hipStream_t s);
 hipError_t launch_pair_inv(const void* panels, void* dinv, bool f32, bool ldlt, const PairItem* items, int count,
                            int maxnb, hipStream_t s);
-hipError_t launch_fwd_small(const SweepArgs& a, const int32_t* cblks, int count, hipStream_t s);
-hipError_t launch_bwd_small(const SweepArgs& a, const int32_t* cblks, int count, hipStream_t s);
+hipError_t launch_fwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s);
+hipError_t launch_bwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s);
 hipError_t launch_permute_in(double* y, const double* b, int64_t ldb, const int32_t* perm, int32_t n, int32_t nrhs,
                              hipStream_t s);
 hipError_t launch_permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs,
@@ -107,6 +107,8 @@ struct Level {
     std::vector<int32_t> cptr;   // cblks of level l: cblk[cptr[l]..cptr[l+1])
     std::vector<int32_t> cblk;   // (each level's small blocks first: cblk[cptr[l]..cptr[l]+nsmall[l]))
     std::vector<int32_t> nsmall; // blocks of width <= 32 with at most 128 panel rows, per level
+    std::vector<SmallItem> small;   // them: small[sptr[l]..sptr[l]+nsmall[l]), the ntiny[l] tiny ones first
+    std::vector<int32_t> sptr, ntiny;
     std::vector<int32_t> dptr;   // diagonal items of level l: ditem[dptr[l]..dptr[l+1])
     std::vector<DiagItem> ditem;
     std::vector<uint8_t> narrow; // level l holds fewer than 64 blocks (its sweep items are cut finer)
@@ -155,7 +157,7 @@ struct spx_handle {
     DevBuf<int64_t> trace;   // per-item task trace, allocated when the trace option is on
     // levels for the sweeps
     Level lv;
-    DevBuf<int32_t> lv_cblk;
+    DevBuf<SmallItem> lv_small;
     DevBuf<DiagItem> lv_ditem;
     DevBuf<OffItem> lv_chunk, lv_chunk1;
     DevBuf<OffItem> lv_bchunk;
@@ -733,6 +735,21 @@ void build_levels(spx_handle* h, const std::vector<int64_t>& doff, const std::ve
         }
     for (int32_t k = 0; k < nc; ++k)
         if (!small(k) && unit[k] == k) L.cblk[pos[lvl[k]]++] = k;
+    // their records, tiny ones (width <= 8, at most 32 rows: 16 lanes each in
+    // the sweeps) first
+    L.sptr.assign(nl + 1, 0);
+    L.ntiny.assign(nl, 0);
+    for (int32_t l = 0; l < nl; ++l) {
+        for (int pass = 0; pass < 2; ++pass)
+            for (int32_t q = L.cptr[l]; q < L.cptr[l] + L.nsmall[l]; ++q) {
+                const int32_t k = L.cblk[q], w = width(k), ld = P.stride[k];
+                const bool tiny = w <= 8 && ld <= 32;
+                if (tiny != (pass == 0)) continue;
+                L.small.push_back(SmallItem{doff[k], P.panel_off[k], rgo[k], P.fcol[k], w | (ld << 8)});
+                if (tiny) ++L.ntiny[l];
+            }
+        L.sptr[l + 1] = static_cast<int32_t>(L.small.size());
+    }
     // diagonal items: 16-row parts on levels with fewer than kNarrowLevel
     // blocks (16 lanes per row: fewer dependent load rounds), else 64-row
     constexpr int32_t kNarrowLevel = 64;
@@ -823,7 +840,7 @@ void build_levels(spx_handle* h, const std::vector<int64_t>& doff, const std::ve
             }
         L.bptr[l + 1] = static_cast<int32_t>(L.bchunk.size());
     }
-    h->lv_cblk.upload(L.cblk);
+    h->lv_small.upload(L.small);
     h->lv_ditem.upload(L.ditem);
     h->lv_chunk.upload(L.chunk);
     h->lv_chunk1.upload(L.chunk1);
@@ -935,17 +952,17 @@ void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
     const Level& L = h->lv;
     const int nl = static_cast<int>(L.cptr.size()) - 1;
     for (int l = 0; l < nl; ++l) {
-        const int32_t* sm = h->lv_cblk.p + L.cptr[l];
-        const int ns = L.nsmall[l];
-        HIPCHK(launch_fwd_small(a, sm, ns, s));
+        const SmallItem* sm = h->lv_small.p + L.sptr[l];
+        const int ns = L.nsmall[l], nt = L.ntiny[l];
+        HIPCHK(launch_fwd_small(a, sm, ns, nt, s));
         HIPCHK(launch_fwd_diag(a, h->lv_ditem.p + L.dptr[l], L.dptr[l + 1] - L.dptr[l], L.dlanes[l], s));
         if (nrhs == 1) HIPCHK(launch_fwd_off(a, h->lv_chunk1.p + L.kptr1[l], L.kptr1[l + 1] - L.kptr1[l], s));
         else HIPCHK(launch_fwd_off(a, h->lv_chunk.p + L.kptr[l], L.kptr[l + 1] - L.kptr[l], s));
     }
     HIPCHK(launch_fill_f64(w.tacc, static_cast<int64_t>(h->n) * nrhs, 0.0, s));
     for (int l = nl - 1; l >= 0; --l) {
-        const int32_t* sm = h->lv_cblk.p + L.cptr[l];
-        const int ns = L.nsmall[l];
+        const SmallItem* sm = h->lv_small.p + L.sptr[l];
+        const int ns = L.nsmall[l], nt = L.ntiny[l];
         // (256-row items for one right-hand side only: with a block of
         // several, gathering a 256-row slice of x per 16 columns costs more
         // than the atomics it saves)
@@ -955,7 +972,7 @@ void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
             HIPCHK(launch_bwd_off(a, h->lv_chunk1.p + L.kptr1[l], L.kptr1[l + 1] - L.kptr1[l], false, s));
         else HIPCHK(launch_bwd_off(a, h->lv_chunk.p + L.kptr[l], L.kptr[l + 1] - L.kptr[l], false, s));
         HIPCHK(launch_bwd_diag(a, h->lv_ditem.p + L.dptr[l], L.dptr[l + 1] - L.dptr[l], L.dlanes[l], s));
-        HIPCHK(launch_bwd_small(a, sm, ns, s));
+        HIPCHK(launch_bwd_small(a, sm, ns, nt, s));
     }
 }
 

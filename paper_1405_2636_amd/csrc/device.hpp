@@ -127,6 +127,14 @@ struct OffItem {           // panel rows row0 .. row0 + nr - 1 of k by the colum
     int32_t cnr;           // c0 | c1 << 9 | nr << 18 (widths are at most 256, nr at most 256)
 };
 
+struct SmallItem {         // a block of width <= 32 with at most 128 panel rows
+    int64_t dofs, pofs;    // kept inverse, panel
+    int64_t gofs;          // position of its rows below in the row list
+    int32_t f, wld;        // first column; width | panel stride << 8
+    __host__ __device__ int w() const { return wld & 255; }
+    __host__ __device__ int ld() const { return wld >> 8; }
+};
+
 // Two consecutive pieces p, q of a split supernode solved as one block in
 // the sweeps: the pair's inverse [[D_p, 0], [X, D_q]] with
 // X = -D_q L_qp D_p (the inverse of the block lower-triangular diagonal

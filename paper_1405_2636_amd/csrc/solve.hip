@@ -18,7 +18,7 @@
 // the panels (each loaded entry serves the whole block); with 4 or 8 the
 // off-diagonal steps are matrix-core products (fwd_off_mm, bwd_off_mm).
 // Column blocks of width <= 32 with at most 128 panel rows take both halves
-// of a step in one kernel per level, a group of 16 lanes per block
+// of a step in one kernel per level, a wave or 16 lanes per block
 // (fwd_small, bwd_small).
 // Every sweep step writes a different vector than it reads (y -> z -> x), so
 // a diagonal block can be spread over several workgroups.  Every dot product
@@ -54,10 +54,10 @@ __device__ __forceinline__ double group_sum(double v)
 }
 
 // Every sweep kernel handles the right-hand sides in blocks of NR (1, 4 or
-// 8, the small-block kernels 1 or 2; chosen from nrhs at launch): the panel and inverse entries a thread
+// 8; chosen from nrhs at launch): the panel and inverse entries a thread
 // loads serve all NR columns of the block, so a panel is read once per
 // block of right-hand sides instead of once per right-hand side.  The
-// diagonal and off-diagonal kernels take one block per grid row (a loop
+// kernels take one block per grid row (a loop
 // over the blocks kept the loop-invariant addresses of the hoisted loads
 // live: 150-210 registers per lane instead of 85-135, and half the
 // resident waves).
@@ -410,194 +410,323 @@ __global__ void __launch_bounds__(256) bwd_diag(SweepArgs a, const DiagItem* ite
 }
 
 // ---- small blocks (width <= 32, at most 128 panel rows), both halves of a
-// sweep step in one kernel per level: a group of 16 lanes per block, 16 blocks per
-// workgroup (the bottom levels of small systems hold tens of thousands of
-// blocks a few columns wide; one workgroup per block would leave most of
-// each workgroup idle and the launch bound by workgroup dispatch).
-constexpr int kSG = 16;                    // lanes per small block
-constexpr int kSGroups = 256 / kSG;        // small blocks per workgroup
+// sweep step in one kernel per level.  Two sizes in one launch: tiny blocks
+// (width <= 8, at most 32 rows), 16 lanes each, 16 per workgroup (the bottom
+// levels of small systems hold tens of thousands of blocks a few columns
+// wide), and the others, a wave each, 4 per workgroup; one block of right-hand
+// sides per grid row.  What bounds them is latency: a level is a few
+// microseconds, and its launches follow each other.  So every block has a
+// record with all of its offsets, and its inverse, its panel (the whole of a
+// tiny one, the first columns of a larger one), its row numbers and its part
+// of the vector are requested in one go after it: two round trips to memory
+// instead of one per four or eight columns.  256 grids of side 16 to 96, one
+// right-hand side, 18 levels: 344 -> 212 us forward, 324 -> 179 backward (16
+// lanes for every block, four or eight columns per round trip); 48^3 with 13
+// right-hand sides, 3 levels: 358 -> 48 and 506 -> 58 us (the blocks of
+// right-hand sides were a loop of two at a time inside the kernels).
+constexpr int kSG = 16;                    // lanes per tiny block
+constexpr int kSGroups = 256 / kSG;        // tiny blocks per workgroup
 
-// forward: z_k = D y_k, then y[g(r)] -= L[r, :] z_k for the rows below
-constexpr int kMaxPass = (128 + kSG - 1) / kSG;   // rows below per lane, at most
-
+// forward, tiny block: z_k = D y_k, then y[g(r)] -= L[r, :] z_k
 template <class T, int NR>
-__global__ void __launch_bounds__(256) fwd_small(SweepArgs a, const int32_t* cblks, int count)
+__device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it, bool on)
 {
-    __shared__ double ys[kSGroups][32 * NR];
-    __shared__ double zs[kSGroups][32 * NR];
-    const int tid = threadIdx.x, g = tid / kSG, l = tid % kSG;
-    const int idx = blockIdx.x * kSGroups + g;
-    const bool on = idx < count;
-    const int k = cblks[on ? idx : count - 1];
-    const DevPlan& pl = a.pl;
-    const int f = pl.fcol[k];
-    const int w = on ? pl.lcol[k] - f + 1 : 0;
-    const int ld = on ? pl.stride[k] : 0;
-    const T* D = static_cast<const T*>(a.dinv) + pl.dinv_off[k];
-    const T* L = static_cast<const T*>(a.panels) + pl.panel_off[k];
-    const int32_t* rg = a.rowg + a.rowg_off[k] - w;   // rg[r]: global row of panel row r >= w
-    for (int rb = 0; rb < a.nrhs; rb += NR) {
-        const int nv = min(NR, a.nrhs - rb);
-        for (int r = l; r < w; r += kSG)
+    const int l = threadIdx.x % kSG, w = it.w(), ld = it.ld(), f = it.f;
+    const T* D = static_cast<const T*>(a.dinv) + it.dofs;
+    const T* L = static_cast<const T*>(a.panels) + it.pofs;
+    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int lw = min(l, w - 1);
+    T d[8], lv[2][8];
+    int g[2];
+    double y[NR];
+    // (indices past the triangle or the panel are clamped, their terms
+    // multiplied by zero or not stored)
 #pragma unroll
-            for (int j = 0; j < NR; ++j) ys[g][r * NR + j] = j < nv ? a.y[(int64_t)(rb + j) * a.n + f + r] : 0.0;
-        __syncthreads();
-        // (indices past the triangle or the panel are clamped; their terms
-        // are multiplied by zero, so the loads of a round are unconditional)
-        for (int r = l; r < w; r += kSG) {
-            double v[NR];
+    for (int p = 0; p < 8; ++p) d[p] = D[lw + min(p, lw) * w];
 #pragma unroll
-            for (int j = 0; j < NR; ++j) v[j] = 0.0;
-#pragma unroll 1
-            for (int p0 = 0; p0 <= r; p0 += 8) {
-                T d[8];
+    for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int u = 0; u < 8; ++u) d[u] = D[r + min(p0 + u, r) * w];
+        for (int c = 0; c < 8; ++c) lv[i][c] = L[min(w + l + kSG * i, ld - 1) + min(c, w - 1) * ld];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const double dv = p0 + u <= r ? (double)d[u] : 0.0;
-                    const double* yp = &ys[g][min(p0 + u, r) * NR];
+    for (int i = 0; i < 2; ++i) g[i] = ld > w ? a.rowg[it.gofs + min(l + kSG * i, ld - w - 1)] : 0;
 #pragma unroll
-                    for (int j = 0; j < NR; ++j) v[j] += dv * yp[j];
-                }
-            }
-            const double s = a.ldlt ? (double)L[r * (ld + 1)] : 1.0;
+    for (int j = 0; j < NR; ++j) y[j] = a.y[(int64_t)(rb + min(j, nv - 1)) * a.n + f + lw];
+    const double s = a.ldlt ? (double)L[lw * (ld + 1)] : 1.0;
+    double z[NR];
 #pragma unroll
-            for (int j = 0; j < NR; ++j) zs[g][r * NR + j] = v[j] * s;
-            for (int j = 0; j < nv; ++j) a.z[(int64_t)(rb + j) * a.n + f + r] = v[j];
+    for (int j = 0; j < NR; ++j) {
+        z[j] = 0.0;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) z[j] += (p <= lw ? (double)d[p] : 0.0) * __shfl(y[j], p, kSG);
+        if (on && l < w && j < nv) a.z[(int64_t)(rb + j) * a.n + f + l] = z[j];
+        z[j] *= s;
+        double v[2] = {0.0, 0.0};
+#pragma unroll
+        for (int c = 0; c < 8; ++c) {
+            const double zc = c < w ? __shfl(z[j], c, kSG) : 0.0;
+#pragma unroll
+            for (int i = 0; i < 2; ++i) v[i] += (double)lv[i][c] * zc;
         }
-        __syncthreads();
-        if (ld > w) {
-            double v[kMaxPass][NR];
 #pragma unroll
-            for (int i = 0; i < kMaxPass; ++i)
-#pragma unroll
-                for (int j = 0; j < NR; ++j) v[i][j] = 0.0;
-#pragma unroll 1
-            for (int c0 = 0; c0 < w; c0 += 4) {
-                T lv[4][kMaxPass];
-#pragma unroll
-                for (int u = 0; u < 4; ++u)
-#pragma unroll
-                    for (int i = 0; i < kMaxPass; ++i)
-                        lv[u][i] = L[min(w + l + kSG * i, ld - 1) + (int64_t)min(c0 + u, w - 1) * ld];
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const bool cu = c0 + u < w;
-                    const double* zp = &zs[g][min(c0 + u, 31) * NR];
-#pragma unroll
-                    for (int j = 0; j < NR; ++j) {
-                        const double z = cu ? zp[j] : 0.0;
-#pragma unroll
-                        for (int i = 0; i < kMaxPass; ++i) v[i][j] += (double)lv[u][i] * z;
-                    }
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < kMaxPass; ++i) {
-                const int r = w + l + kSG * i;
-                if (r < ld)
-                    for (int j = 0; j < nv; ++j) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + rg[r], -v[i][j]);
-            }
-        }
-        __syncthreads();
+        for (int i = 0; i < 2; ++i)
+            if (on && w + l + kSG * i < ld && j < nv) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + g[i], -v[i]);
     }
 }
 
-// backward: t = L_off^T x[g(rows below)] (sums over the group's lanes),
-// then x_k = D^T (z_k - t)
+// forward, a wave: lane = row and half of the columns of D, then lane = row
+// below (two of them)
 template <class T, int NR>
-__global__ void __launch_bounds__(256) bwd_small(SweepArgs a, const int32_t* cblks, int count)
+__device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it, bool on, double* ys, double* zs)
 {
-    __shared__ double us[kSGroups][32 * NR];
-    const int tid = threadIdx.x, g = tid / kSG, l = tid % kSG;
-    const int idx = blockIdx.x * kSGroups + g;
-    const bool on = idx < count;
-    const int k = cblks[on ? idx : count - 1];
-    const DevPlan& pl = a.pl;
-    const int f = pl.fcol[k];
-    const int w = on ? pl.lcol[k] - f + 1 : 0;
-    const int ld = on ? pl.stride[k] : 0;
-    const T* D = static_cast<const T*>(a.dinv_b) + pl.dinv_off[k];
-    const T* L = static_cast<const T*>(a.panels_b) + pl.panel_off[k];
-    const int32_t* rg = a.rowg + a.rowg_off[k] - w;
-    for (int rb = 0; rb < a.nrhs; rb += NR) {
-        const int nv = min(NR, a.nrhs - rb);
-        double xr[kMaxPass][NR];
+    const int lane = threadIdx.x & 63, w = it.w(), ld = it.ld(), f = it.f, R = ld - w;
+    const T* D = static_cast<const T*>(a.dinv) + it.dofs;
+    const T* L = static_cast<const T*>(a.panels) + it.pofs;
+    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int r = lane & 31, half = lane >> 5, rw = min(r, w - 1);
+    T d[16], lv[2][8];
+    int g[2];
 #pragma unroll
-        for (int i = 0; i < kMaxPass; ++i) {
-            const int r = w + l + kSG * i;
+    for (int i = 0; i < 16; ++i) d[i] = D[rw + min(2 * i + half, rw) * w];
 #pragma unroll
-            for (int j = 0; j < NR; ++j) xr[i][j] = (r < ld && j < nv) ? a.x[(int64_t)(rb + j) * a.n + rg[r]] : 0.0;
-        }
-        // (xr is zero for rows past the panel: their clamped loads count zero)
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) lv[i][c] = L[min(w + lane + 64 * i, ld - 1) + min(c, w - 1) * ld];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) g[i] = R > 0 ? a.rowg[it.gofs + min(lane + 64 * i, R - 1)] : 0;
+    for (int idx = lane; idx < 32 * NR; idx += 64) {
+        const int c = idx / NR, j = idx % NR;
+        ys[idx] = c < w && j < nv ? a.y[(int64_t)(rb + j) * a.n + f + c] : 0.0;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
+    double z[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) z[j] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const double dv = 2 * i + half <= rw ? (double)d[i] : 0.0;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) z[j] += dv * ys[(2 * i + half) * NR + j];
+    }
+    const double s = a.ldlt ? (double)L[rw * (ld + 1)] : 1.0;
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        z[j] += __shfl_xor(z[j], 32);
+        if (half == 0) zs[r * NR + j] = r < w ? z[j] * s : 0.0;
+        if (on && half == 0 && r < w && j < nv) a.z[(int64_t)(rb + j) * a.n + f + r] = z[j];
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    if (R <= 0) return;
+    double v[2][NR];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NR; ++j) v[i][j] = 0.0;
 #pragma unroll 1
-        for (int c0 = 0; c0 < w; c0 += 4) {
-            double v[4][NR];
+    for (int c0 = 0; c0 < w; c0 += 8) {
+        T ln[2][8];   // the next eight columns, on their way
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                T lv[kMaxPass];
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int i = 0; i < kMaxPass; ++i)
-                    lv[i] = L[min(w + l + kSG * i, ld - 1) + (int64_t)min(c0 + u, w - 1) * ld];
+            for (int c = 0; c < 8; ++c) ln[i][c] = L[min(w + lane + 64 * i, ld - 1) + min(c0 + 8 + c, w - 1) * ld];
 #pragma unroll
-                for (int j = 0; j < NR; ++j) {
-                    double t = 0.0;
+        for (int c = 0; c < 8; ++c) {
+            const double* zc = zs + (c0 + c) * NR;   // (zero past w)
 #pragma unroll
-                    for (int i = 0; i < kMaxPass; ++i) t += (double)lv[i] * xr[i][j];
-                    v[u][j] = group_sum<kSG>(t);
-                }
-            }
-            if (l < 4 && c0 + l < w) {
-                const double s = a.ldlt ? (double)L[(c0 + l) * (ld + 1)] : 1.0;
+            for (int i = 0; i < 2; ++i)
 #pragma unroll
-                for (int j = 0; j < NR; ++j) {
-                    const double t = l == 0 ? v[0][j] : l == 1 ? v[1][j] : l == 2 ? v[2][j] : v[3][j];
-                    const double u = j < nv ? a.z[(int64_t)(rb + j) * a.n + f + c0 + l] - t : 0.0;
-                    us[g][(c0 + l) * NR + j] = u * s;
-                }
-            }
+                for (int j = 0; j < NR; ++j) v[i][j] += (double)lv[i][c] * zc[j];
         }
-        __syncthreads();
-        for (int c = l; c < w; c += kSG) {
-            double v[NR];
 #pragma unroll
-            for (int j = 0; j < NR; ++j) v[j] = 0.0;
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int c = 0; c < 8; ++c) lv[i][c] = ln[i][c];
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if (on && lane + 64 * i < R)
+            for (int j = 0; j < nv; ++j) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + g[i], -v[i][j]);
+}
+
+// grid: ceil(ntiny / 16) workgroups of tiny blocks, then ceil((count -
+// ntiny) / 4) of the others
+template <class T, int NR>
+__global__ void __launch_bounds__(256) fwd_small(SweepArgs a, const SmallItem* items, int count, int ntiny)
+{
+    __shared__ double sm[4][2][32 * NR];
+    const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
+    if ((int)blockIdx.x < nt) {
+        const int idx = blockIdx.x * kSGroups + tid / kSG;
+        const SmallItem it = items[min(idx, ntiny - 1)];
+        fwd_tiny<T, NR>(a, it, idx < ntiny);
+    } else {
+        const int wave = tid >> 6, idx = ntiny + ((int)blockIdx.x - nt) * 4 + wave;
+        const SmallItem it = items[min(idx, count - 1)];
+        fwd_wave<T, NR>(a, it, idx < count, sm[wave][0], sm[wave][1]);
+    }
+}
+
+// backward, tiny block: t = L_off^T x[g(rows below)], x_k = D^T (z_k - t)
+template <class T, int NR>
+__device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it, bool on)
+{
+    const int l = threadIdx.x % kSG, w = it.w(), ld = it.ld(), f = it.f;
+    const T* D = static_cast<const T*>(a.dinv_b) + it.dofs;
+    const T* L = static_cast<const T*>(a.panels_b) + it.pofs;
+    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    // after the sums below lane l holds column (l >> 1) & 7; lane c of the
+    // first eight takes column c of D^T
+    const int cs = (l >> 1) & 7, cw = min(cs, w - 1), lw = min(l, w - 1);
+    int g[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) g[i] = ld > w ? a.rowg[it.gofs + min(l + kSG * i, ld - w - 1)] : 0;
+    T d[8], lv[2][8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) d[p] = D[min(max(p, lw), w - 1) + lw * w];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int c = 0; c < 8; ++c) lv[i][c] = L[min(w + l + kSG * i, ld - 1) + min(c, w - 1) * ld];
+    const double s = a.ldlt ? (double)L[cw * (ld + 1)] : 1.0;
+    double zc[NR], x[2][NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        const int64_t o = (int64_t)(rb + min(j, nv - 1)) * a.n;
+        zc[j] = a.z[o + f + cw];
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i][j] = w + l + kSG * i < ld ? a.x[o + g[i]] : 0.0;
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        double t[8];
+#pragma unroll
+        for (int c = 0; c < 8; ++c) t[c] = (double)lv[0][c] * x[0][j] + (double)lv[1][c] * x[1][j];
+        // sums over the 16 lanes, half of the columns handed over per step
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const double keep = l & 8 ? t[c + 4] : t[c], give = l & 8 ? t[c] : t[c + 4];
+            t[c] = keep + __shfl_xor(give, 8);
+        }
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const double keep = l & 4 ? t[c + 2] : t[c], give = l & 4 ? t[c] : t[c + 2];
+            t[c] = keep + __shfl_xor(give, 4);
+        }
+        const double keep = l & 2 ? t[1] : t[0], give = l & 2 ? t[0] : t[1];
+        t[0] = keep + __shfl_xor(give, 2);
+        t[0] += __shfl_xor(t[0], 1);
+        const double u = (zc[j] - t[0]) * s;   // column cs
+        double v = 0.0;
+#pragma unroll
+        for (int p = 0; p < 8; ++p) {
+            const double up = __shfl(u, 2 * p, kSG);
+            v += (p >= l && p < w ? (double)d[p] : 0.0) * (p < w ? up : 0.0);
+        }
+        if (on && l < w && j < nv) a.x[(int64_t)(rb + j) * a.n + f + l] = v;
+    }
+}
+
+// backward, a wave: lane = column and half of the rows below, then of the
+// rows of D
+template <class T, int NR>
+__device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it, bool on, double* xs, double* us)
+{
+    const int lane = threadIdx.x & 63, w = it.w(), ld = it.ld(), f = it.f, R = ld - w;
+    const T* D = static_cast<const T*>(a.dinv_b) + it.dofs;
+    const T* L = static_cast<const T*>(a.panels_b) + it.pofs;
+    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int c = lane & 31, half = lane >> 5, cw = min(c, w - 1);
+    int g[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) g[i] = R > 0 ? a.rowg[it.gofs + min(lane + 64 * i, R - 1)] : 0;
+    T d[16], lv[8];
+    const int Rh = (R + 1) / 2, rs = half * Rh, re = min(R, rs + Rh);   // this half's rows below
+    const T* Lc = L + (int64_t)cw * ld + w;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) lv[u] = Lc[min(rs + u, ld - w - 1)];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) d[i] = D[min(max(2 * i + half, cw), w - 1) + cw * w];
+    const double s = a.ldlt ? (double)L[cw * (ld + 1)] : 1.0;
+    double zc[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) zc[j] = a.z[(int64_t)(rb + min(j, nv - 1)) * a.n + f + cw];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < NR; ++j)
+            xs[(lane + 64 * i) * NR + j] = lane + 64 * i < R && j < nv ? a.x[(int64_t)(rb + j) * a.n + g[i]] : 0.0;
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
+    double t[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) t[j] = 0.0;
 #pragma unroll 1
-            for (int p0 = c; p0 < w; p0 += 8) {
-                T d[8];
+    for (int r0 = rs; r0 < re; r0 += 8) {
+        T ln[8];   // the next eight rows, on their way
 #pragma unroll
-                for (int u = 0; u < 8; ++u) d[u] = D[min(p0 + u, w - 1) + c * w];
+        for (int u = 0; u < 8; ++u) ln[u] = Lc[min(r0 + 8 + u, ld - w - 1)];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const double dv = p0 + u < w ? (double)d[u] : 0.0;
-                    const double* up = &us[g][min(p0 + u, w - 1) * NR];
+        for (int u = 0; u < 8; ++u) {
+            const double lu = r0 + u < re ? (double)lv[u] : 0.0;
+            const double* xp = xs + min(r0 + u, 127) * NR;
 #pragma unroll
-                    for (int j = 0; j < NR; ++j) v[j] += dv * up[j];
-                }
-            }
-            for (int j = 0; j < nv; ++j) a.x[(int64_t)(rb + j) * a.n + f + c] = v[j];
+            for (int j = 0; j < NR; ++j) t[j] += lu * xp[j];
         }
-        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < 8; ++u) lv[u] = ln[u];
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        t[j] += __shfl_xor(t[j], 32);
+        if (half == 0) us[c * NR + j] = c < w ? (zc[j] - t[j]) * s : 0.0;
+    }
+    __atomic_signal_fence(__ATOMIC_SEQ_CST);
+    double v[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) v[j] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+        const int p = 2 * i + half;
+        const double dv = p >= c && p < w ? (double)d[i] : 0.0;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) v[j] += dv * us[p * NR + j];
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) {
+        v[j] += __shfl_xor(v[j], 32);
+        if (on && half == 0 && c < w && j < nv) a.x[(int64_t)(rb + j) * a.n + f + c] = v[j];
+    }
+}
+
+template <class T, int NR>
+__global__ void __launch_bounds__(256) bwd_small(SweepArgs a, const SmallItem* items, int count, int ntiny)
+{
+    __shared__ double xs[4][128 * NR];
+    __shared__ double us[4][32 * NR];
+    const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
+    if ((int)blockIdx.x < nt) {
+        const int idx = blockIdx.x * kSGroups + tid / kSG;
+        const SmallItem it = items[min(idx, ntiny - 1)];
+        bwd_tiny<T, NR>(a, it, idx < ntiny);
+    } else {
+        const int wave = tid >> 6, idx = ntiny + ((int)blockIdx.x - nt) * 4 + wave;
+        const SmallItem it = items[min(idx, count - 1)];
+        bwd_wave<T, NR>(a, it, idx < count, xs[wave], us[wave]);
     }
 }
 
 // ---- vector kernels
 __global__ void permute_in(double* y, const double* b, int64_t ldb, const int32_t* perm, int32_t n, int32_t nrhs)
 {
-    const int64_t tot = (int64_t)n * nrhs;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = t / n, i = t - c * n;
-        y[t] = b[c * ldb + perm[i]];
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t p = perm[i];
+        for (int32_t c = blockIdx.y; c < nrhs; c += gridDim.y) y[(int64_t)c * n + i] = b[c * ldb + p];
     }
 }
 
 __global__ void permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs)
 {
-    const int64_t tot = (int64_t)n * nrhs;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = t / n, i = t - c * n;
-        x[c * ldx + perm[i]] = y[t];
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int32_t p = perm[i];
+        for (int32_t c = blockIdx.y; c < nrhs; c += gridDim.y) x[c * ldx + p] = y[(int64_t)c * n + i];
     }
 }
 
@@ -643,35 +772,50 @@ __device__ __forceinline__ unsigned long long block_max(unsigned long long v)
 // stats[1] = max |r_i|, stats[2] = max |x_i|, stats[3] = max |b_i|, stats[4] = max_i sum_j |a_ij|
 // (stats[q] at word q * kStatStride: every block adds its maxima by atomics,
 // one cache line per statistic; a fixed grid of kResidualBlocks blocks)
+// A thread takes a row and NR right-hand sides at a time (grid rows): its
+// entries are read once for all of them, with no division per element.
+template <int NR>
 __global__ void __launch_bounds__(256) residual_kernel(const int64_t* rptr, const int32_t* rcol, const double* rv,
                                                        const double* x, const double* b,
                                                        int64_t ldb, double* r, int32_t n, int32_t nrhs,
                                                        unsigned long long* stats)
 {
     unsigned long long m0 = 0, m1 = 0, m2 = 0, m3 = 0, m4 = 0;
-    const int64_t tot = (int64_t)n * nrhs;
-    for (int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; t < tot; t += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t c = t / n, i = t - c * n;
-        const double* xc = x + c * n;
-        const double bi = b[c * ldb + i];
-        double acc = bi, den = fabs(bi), arow = 0.0;
+    auto up = [](unsigned long long& m, double v) {
+        const unsigned long long k = key_of(v);
+        m = k > m ? k : m;
+    };
+    const int c0 = blockIdx.y * NR, nv = min(NR, nrhs - c0);
+    const double* xc = x + (int64_t)c0 * n;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        double acc[NR], den[NR], arow = 0.0;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            const double bi = b[(c0 + min(j, nv - 1)) * ldb + i];
+            acc[j] = bi;
+            den[j] = fabs(bi);
+            up(m3, fabs(bi));
+        }
         for (int64_t q = rptr[i]; q < rptr[i + 1]; ++q) {
             const double av = rv[q];
-            const double xv = xc[rcol[q]];
-            acc -= av * xv;
-            den += fabs(av) * fabs(xv);
+            const int32_t col = rcol[q];
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                const double xv = xc[(int64_t)min(j, nv - 1) * n + col];
+                acc[j] -= av * xv;
+                den[j] += fabs(av) * fabs(xv);
+            }
             arow += fabs(av);
         }
-        r[t] = acc;
-        const double ar = fabs(acc);
-        const double om = ar == 0.0 ? 0.0 : (den == 0.0 ? __builtin_inf() : ar / den);
-        unsigned long long k0 = key_of(om), k1 = key_of(ar), k2 = key_of(fabs(xc[i])), k3 = key_of(fabs(bi)),
-                           k4 = key_of(arow);
-        m0 = k0 > m0 ? k0 : m0;
-        m1 = k1 > m1 ? k1 : m1;
-        m2 = k2 > m2 ? k2 : m2;
-        m3 = k3 > m3 ? k3 : m3;
-        m4 = k4 > m4 ? k4 : m4;
+#pragma unroll
+        for (int j = 0; j < NR; ++j) {
+            if (j < nv) r[(int64_t)(c0 + j) * n + i] = acc[j];
+            const double ar = fabs(acc[j]);
+            up(m0, ar == 0.0 ? 0.0 : (den[j] == 0.0 ? __builtin_inf() : ar / den[j]));
+            up(m1, ar);
+            up(m2, fabs(xc[(int64_t)min(j, nv - 1) * n + i]));
+        }
+        up(m4, arow);
     }
     m0 = block_max(m0);
     m1 = block_max(m1);
@@ -833,8 +977,7 @@ __global__ void __launch_bounds__(256) pair_inv(const T* panels, T* dinv, const 
 // ---- host launchers
 static int grid_for(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192)); }
 
-// right-hand sides per pass over a panel: 1, 4 or 8 (16-lane small-block
-// kernels, whose lanes each keep up to 8 rows: 1 or 2)
+// right-hand sides per pass over a panel: 1, 4 or 8
 static int nr_block(int nrhs) { return nrhs <= 1 ? 1 : (nrhs <= 4 ? 4 : 8); }
 
 #define SPX_NR_DISPATCH(NRV, CALL) \
@@ -927,13 +1070,13 @@ hipError_t launch_pair_inv(const void* panels, void* dinv, bool f32, bool ldlt, 
 hipError_t launch_permute_in(double* y, const double* b, int64_t ldb, const int32_t* perm, int32_t n, int32_t nrhs,
                              hipStream_t s)
 {
-    permute_in<<<grid_for((int64_t)n * nrhs), 256, 0, s>>>(y, b, ldb, perm, n, nrhs);
+    permute_in<<<dim3(grid_for(n), std::min(nrhs, 64)), 256, 0, s>>>(y, b, ldb, perm, n, nrhs);
     return hipGetLastError();
 }
 hipError_t launch_permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs,
                               hipStream_t s)
 {
-    permute_out<<<grid_for((int64_t)n * nrhs), 256, 0, s>>>(x, ldx, y, perm, n, nrhs);
+    permute_out<<<dim3(grid_for(n), std::min(nrhs, 64)), 256, 0, s>>>(x, ldx, y, perm, n, nrhs);
     return hipGetLastError();
 }
 hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s)
@@ -942,31 +1085,23 @@ hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t launch_fwd_small(const SweepArgs& a, const int32_t* cblks, int count, hipStream_t s)
+hipError_t launch_fwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
-    const int blocks = (count + kSGroups - 1) / kSGroups;
-    if (a.nrhs <= 1) {
-        if (a.f32) fwd_small<float, 1><<<blocks, 256, 0, s>>>(a, cblks, count);
-        else fwd_small<double, 1><<<blocks, 256, 0, s>>>(a, cblks, count);
-    } else {
-        if (a.f32) fwd_small<float, 2><<<blocks, 256, 0, s>>>(a, cblks, count);
-        else fwd_small<double, 2><<<blocks, 256, 0, s>>>(a, cblks, count);
-    }
+    const int nrv = nr_block(a.nrhs);
+    const dim3 grid((ntiny + kSGroups - 1) / kSGroups + (count - ntiny + 3) / 4, (a.nrhs + nrv - 1) / nrv);
+    SPX_NR_DISPATCH(nrv, (a.f32 ? fwd_small<float, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)
+                                : fwd_small<double, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)));
     return hipGetLastError();
 }
 
-hipError_t launch_bwd_small(const SweepArgs& a, const int32_t* cblks, int count, hipStream_t s)
+hipError_t launch_bwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
-    const int blocks = (count + kSGroups - 1) / kSGroups;
-    if (a.nrhs <= 1) {
-        if (a.f32) bwd_small<float, 1><<<blocks, 256, 0, s>>>(a, cblks, count);
-        else bwd_small<double, 1><<<blocks, 256, 0, s>>>(a, cblks, count);
-    } else {
-        if (a.f32) bwd_small<float, 2><<<blocks, 256, 0, s>>>(a, cblks, count);
-        else bwd_small<double, 2><<<blocks, 256, 0, s>>>(a, cblks, count);
-    }
+    const int nrv = nr_block(a.nrhs);
+    const dim3 grid((ntiny + kSGroups - 1) / kSGroups + (count - ntiny + 3) / 4, (a.nrhs + nrv - 1) / nrv);
+    SPX_NR_DISPATCH(nrv, (a.f32 ? bwd_small<float, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)
+                                : bwd_small<double, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)));
     return hipGetLastError();
 }
 
@@ -979,8 +1114,11 @@ hipError_t launch_residual(const int64_t* rptr, const int32_t* rcol, const doubl
                            const double* b, int64_t ldb, double* r, int32_t n, int32_t nrhs,
                            unsigned long long* stats, hipStream_t s)
 {
-    const int blocks = (int)std::min<int64_t>(kResidualBlocks, std::max<int64_t>(1, ((int64_t)n * nrhs + 255) / 256));
-    residual_kernel<<<blocks, 256, 0, s>>>(rptr, rcol, rv, x, b, ldb, r, n, nrhs, stats);
+    const int nr = nrhs <= 1 ? 1 : 4;
+    const int rows = (nrhs + nr - 1) / nr;
+    const int blocks = (int)std::min<int64_t>(std::max(1, kResidualBlocks / rows), std::max<int64_t>(1, ((int64_t)n + 255) / 256));
+    if (nr == 1) residual_kernel<1><<<dim3(blocks, rows), 256, 0, s>>>(rptr, rcol, rv, x, b, ldb, r, n, nrhs, stats);
+    else residual_kernel<4><<<dim3(blocks, rows), 256, 0, s>>>(rptr, rcol, rv, x, b, ldb, r, n, nrhs, stats);
     return hipGetLastError();
 }
 

@@ -33,20 +33,19 @@ int sched_blocks_per_cu(bool f32, bool ldlt, bool lu);
 hipError_t launch_sched(const SchedArgs& a, bool f32, bool lu, int grid, hipStream_t s);
 hipError_t launch_update_bench(const SchedArgs& a, bool f32, bool ldl, const int4* tiles, int ntiles, int mbase,
                                int copies, hipStream_t s);
-hipError_t launch_fwd_diag(const SweepArgs& a, const DiagItem* items, int count, int lanes, hipStream_t s);
+hipError_t launch_fwd_level(const SweepArgs& a, const DiagItem* ditems, int nd, int lanes, const SmallItem* items,
+                            int count, int ntiny, hipStream_t s);
+hipError_t launch_bwd_level(const SweepArgs& a, const DiagItem* ditems, int nd, int lanes, const SmallItem* items,
+                            int count, int ntiny, hipStream_t s);
 hipError_t launch_fwd_off(const SweepArgs& a, const OffItem* items, int count, hipStream_t s);
 hipError_t launch_bwd_off(const SweepArgs& a, const OffItem* items, int count, bool tall, hipStream_t s);
-hipError_t launch_bwd_diag(const SweepArgs& a, const DiagItem* items, int count, int lanes, hipStream_t s);
 hipError_t launch_pair_inv(const void* panels, void* dinv, bool f32, bool ldlt, const PairItem* items, int count,
                            int maxnb, hipStream_t s);
-hipError_t launch_fwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s);
-hipError_t launch_bwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s);
-hipError_t launch_permute_in(double* y, const double* b, int64_t ldb, const int32_t* perm, int32_t n, int32_t nrhs,
-                             hipStream_t s);
+hipError_t launch_permute_in(double* y, double* t, const double* b, int64_t ldb, const int32_t* perm, int32_t n,
+                             int32_t nrhs, hipStream_t s);
 hipError_t launch_permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs,
-                              hipStream_t s);
+                              unsigned long long* stats, hipStream_t s);
 hipError_t launch_axpy(double* x, const double* d, int64_t n, hipStream_t s);
-hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s);
 hipError_t launch_values_grad(const int32_t* erow, const int32_t* ecol, int64_t nnz, const double* x, const double* db,
                               int64_t ld, int32_t nrhs, double* grad, hipStream_t s);
 hipError_t launch_residual(const int64_t* rptr, const int32_t* rcol, const double* rv, const double* x,
@@ -926,9 +925,17 @@ struct SweepBufs {
 };
 
 // One application of (L L^T)^{-1} to the permuted vectors in w.y (consumed):
-// result in w.x.
+// result in w.x.  w.tacc is zero at the start (permute_in).
 void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
 {
+    constexpr int32_t kMaxRhs = 1 << 18;   // (grid rows of a launch, eight right-hand sides each)
+    if (nrhs > kMaxRhs) {
+        for (int32_t c = 0; c < nrhs; c += kMaxRhs) {
+            const int64_t o = static_cast<int64_t>(c) * h->n;
+            sweeps(h, SweepBufs{w.y + o, w.z + o, w.x + o, w.tacc + o}, std::min(kMaxRhs, nrhs - c), s);
+        }
+        return;
+    }
     SweepArgs a;
     a.pl = h->devplan();
     a.panels = h->panel_ptr();
@@ -951,18 +958,15 @@ void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
     a.nrhs = nrhs;
     const Level& L = h->lv;
     const int nl = static_cast<int>(L.cptr.size()) - 1;
+    auto diag = [&](int l) { return h->lv_ditem.p + L.dptr[l]; };
+    auto ndiag = [&](int l) { return L.dptr[l + 1] - L.dptr[l]; };
+    auto small = [&](int l) { return h->lv_small.p + L.sptr[l]; };
     for (int l = 0; l < nl; ++l) {
-        const SmallItem* sm = h->lv_small.p + L.sptr[l];
-        const int ns = L.nsmall[l], nt = L.ntiny[l];
-        HIPCHK(launch_fwd_small(a, sm, ns, nt, s));
-        HIPCHK(launch_fwd_diag(a, h->lv_ditem.p + L.dptr[l], L.dptr[l + 1] - L.dptr[l], L.dlanes[l], s));
+        HIPCHK(launch_fwd_level(a, diag(l), ndiag(l), L.dlanes[l], small(l), L.nsmall[l], L.ntiny[l], s));
         if (nrhs == 1) HIPCHK(launch_fwd_off(a, h->lv_chunk1.p + L.kptr1[l], L.kptr1[l + 1] - L.kptr1[l], s));
         else HIPCHK(launch_fwd_off(a, h->lv_chunk.p + L.kptr[l], L.kptr[l + 1] - L.kptr[l], s));
     }
-    HIPCHK(launch_fill_f64(w.tacc, static_cast<int64_t>(h->n) * nrhs, 0.0, s));
     for (int l = nl - 1; l >= 0; --l) {
-        const SmallItem* sm = h->lv_small.p + L.sptr[l];
-        const int ns = L.nsmall[l], nt = L.ntiny[l];
         // (256-row items for one right-hand side only: with a block of
         // several, gathering a 256-row slice of x per 16 columns costs more
         // than the atomics it saves)
@@ -971,8 +975,7 @@ void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
         else if (nrhs == 1)
             HIPCHK(launch_bwd_off(a, h->lv_chunk1.p + L.kptr1[l], L.kptr1[l + 1] - L.kptr1[l], false, s));
         else HIPCHK(launch_bwd_off(a, h->lv_chunk.p + L.kptr[l], L.kptr[l + 1] - L.kptr[l], false, s));
-        HIPCHK(launch_bwd_diag(a, h->lv_ditem.p + L.dptr[l], L.dptr[l + 1] - L.dptr[l], L.dlanes[l], s));
-        HIPCHK(launch_bwd_small(a, sm, ns, nt, s));
+        HIPCHK(launch_bwd_level(a, diag(l), ndiag(l), L.dlanes[l], small(l), L.nsmall[l], L.ntiny[l], s));
     }
 }
 
@@ -1103,24 +1106,26 @@ void run_factorization(spx_handle* h, hipStream_t s)
 }
 
 // Refinement shared by the solve entry points (FP64 residual, Section III's
-// solve followed by iterative refinement): apply_b() sets xw = A^{-1} b;
+// solve followed by iterative refinement): apply_b() sets x0 = A^{-1} b;
 // then, until omega <= ir_tol, ir_max_iter steps or stagnation (omega above
 // half its previous value twice in a row): r = b - A xw with its statistics
 // (stats: 5 lines of kStatStride words), apply_r() sets dw = A^{-1} rw,
-// xw += dw.  b is a device array with leading dimension ldb.
+// xw += dw (xw = x0 first; x0 may be dw or xw).  Every application clears the
+// statistics (permute_out).  b is a device array with leading dimension ldb; x
+// is set to the result's place, x0 or xw.
 template <class FB, class FR>
-spx_solve_info refine(spx_handle* h, int32_t nrhs, const double* b, int64_t ldb, double* xw, double* rw,
-                      const double* dw, unsigned long long* stats, FB apply_b, FR apply_r, hipStream_t s)
+spx_solve_info refine(spx_handle* h, int32_t nrhs, const double* b, int64_t ldb, const double* x0, double* xw,
+                      double* rw, const double* dw, const double** x, unsigned long long* stats, FB apply_b, FR apply_r, hipStream_t s)
 {
     const int32_t n = h->n;
     const size_t tot = static_cast<size_t>(n) * nrhs;
     apply_b();
+    *x = x0;
     int iters = 0, slow = 0;
     double omega = 0.0, eta = 0.0, prev = INFINITY;
     const double tol = h->opt.ir_tol;
     for (;;) {
-        HIPCHK(launch_zero_u64(stats, 5 * kStatStride, s));
-        HIPCHK(launch_residual(h->rptr.p, h->rcol.p, h->rv.p, xw, b, ldb, rw, n, nrhs, stats, s));
+        HIPCHK(launch_residual(h->rptr.p, h->rcol.p, h->rv.p, *x, b, ldb, rw, n, nrhs, stats, s));
         unsigned long long st[5 * kStatStride];
         HIPCHK(hipMemcpyAsync(st, stats, sizeof st, hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
@@ -1133,6 +1138,10 @@ spx_solve_info refine(spx_handle* h, int32_t nrhs, const double* b, int64_t ldb,
         slow = omega > 0.5 * prev ? slow + 1 : 0;
         if (slow >= 2) break;
         prev = omega;
+        if (*x != xw) {
+            HIPCHK(hipMemcpyAsync(xw, *x, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
+            *x = xw;
+        }
         apply_r();
         HIPCHK(launch_axpy(xw, dw, static_cast<int64_t>(tot), s));
         ++iters;
@@ -1360,13 +1369,13 @@ int spx_solve(spx_handle* h, int32_t nrhs, double* b, int64_t ldb, int32_t b_on_
         }
         h->stats.alloc(5 * kStatStride);
         if (h->graph_nrhs != nrhs) {
-            // one application of A^{-1}: dw = P^T L^{-T} L^{-1} P rw, captured once per nrhs
+            // one application of A^{-1} to the permuted right-hand sides in y:
+            // dw = P^T L^{-T} L^{-1} y, captured once per nrhs
             h->drop_graph();
             if (!h->cap_stream) HIPCHK(hipStreamCreateWithFlags(&h->cap_stream, hipStreamNonBlocking));
             HIPCHK(hipStreamBeginCapture(h->cap_stream, hipStreamCaptureModeThreadLocal));
-            HIPCHK(launch_permute_in(h->y.p, h->rw.p, n, h->perm.p, n, nrhs, h->cap_stream));
             sweeps(h, SweepBufs{h->y.p, h->zv.p, h->xv.p, h->tacc.p}, nrhs, h->cap_stream);
-            HIPCHK(launch_permute_out(h->dw.p, n, h->xv.p, h->perm.p, n, nrhs, h->cap_stream));
+            HIPCHK(launch_permute_out(h->dw.p, n, h->xv.p, h->perm.p, n, nrhs, h->stats.p, h->cap_stream));
             HIPCHK(hipStreamEndCapture(h->cap_stream, &h->graph));
             HIPCHK(hipGraphInstantiate(&h->graph_exec, h->graph, nullptr, nullptr, 0));
             h->graph_nrhs = nrhs;
@@ -1374,15 +1383,15 @@ int spx_solve(spx_handle* h, int32_t nrhs, double* b, int64_t ldb, int32_t b_on_
         // the right-hand side, packed (leading dimension n)
         HIPCHK(hipMemcpy2DAsync(h->bw.p, n * sizeof(double), b, ldb * sizeof(double), n * sizeof(double), nrhs,
                                 b_on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, s));
+        const double* x = nullptr;
+        auto apply = [&](const double* r) {
+            HIPCHK(launch_permute_in(h->y.p, h->tacc.p, r, n, h->perm.p, n, nrhs, s));
+            HIPCHK(hipGraphLaunch(h->graph_exec, s));
+        };
         const spx_solve_info si = refine(
-            h, nrhs, h->bw.p, n, h->xw.p, h->rw.p, h->dw.p, h->stats.p,
-            [&] {   // x0 = A^{-1} b
-                HIPCHK(hipMemcpyAsync(h->rw.p, h->bw.p, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
-                HIPCHK(hipGraphLaunch(h->graph_exec, s));
-                HIPCHK(hipMemcpyAsync(h->xw.p, h->dw.p, tot * sizeof(double), hipMemcpyDeviceToDevice, s));
-            },
-            [&] { HIPCHK(hipGraphLaunch(h->graph_exec, s)); }, s);
-        HIPCHK(hipMemcpy2DAsync(b, ldb * sizeof(double), h->xw.p, n * sizeof(double), n * sizeof(double), nrhs,
+            h, nrhs, h->bw.p, n, h->dw.p, h->xw.p, h->rw.p, h->dw.p, &x, h->stats.p, [&] { apply(h->bw.p); },
+            [&] { apply(h->rw.p); }, s);
+        HIPCHK(hipMemcpy2DAsync(b, ldb * sizeof(double), x, n * sizeof(double), n * sizeof(double), nrhs,
                                 b_on_device ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
         if (info) *info = si;
@@ -1424,20 +1433,16 @@ int spx_solve_noalloc(spx_handle* h, int32_t nrhs, double* b, int64_t ldb, spx_s
         const SweepBufs w{v[0], v[1], v[2], v[3]};
         double *xw = v[4], *rw = v[5], *dw = v[6];
         hipStream_t s = static_cast<hipStream_t>(hip_stream);
+        const double* x = nullptr;
+        auto apply = [&](const double* r, int64_t ldr, double* to) {
+            HIPCHK(launch_permute_in(w.y, w.tacc, r, ldr, h->perm.p, n, nrhs, s));
+            sweeps(h, w, nrhs, s);
+            HIPCHK(launch_permute_out(to, n, w.x, h->perm.p, n, nrhs, stats, s));
+        };
         const spx_solve_info si = refine(
-            h, nrhs, b, ldb, xw, rw, dw, stats,
-            [&] {   // x0 = A^{-1} b, read in place
-                HIPCHK(launch_permute_in(w.y, b, ldb, h->perm.p, n, nrhs, s));
-                sweeps(h, w, nrhs, s);
-                HIPCHK(launch_permute_out(xw, n, w.x, h->perm.p, n, nrhs, s));
-            },
-            [&] {
-                HIPCHK(launch_permute_in(w.y, rw, n, h->perm.p, n, nrhs, s));
-                sweeps(h, w, nrhs, s);
-                HIPCHK(launch_permute_out(dw, n, w.x, h->perm.p, n, nrhs, s));
-            },
-            s);
-        HIPCHK(hipMemcpy2DAsync(b, ldb * sizeof(double), xw, n * sizeof(double), n * sizeof(double), nrhs,
+            h, nrhs, b, ldb, xw, xw, rw, dw, &x, stats, [&] { apply(b, ldb, xw); },   // (b read in place)
+            [&] { apply(rw, n, dw); }, s);
+        HIPCHK(hipMemcpy2DAsync(b, ldb * sizeof(double), x, n * sizeof(double), n * sizeof(double), nrhs,
                                 hipMemcpyDeviceToDevice, s));
         HIPCHK(hipStreamSynchronize(s));
         if (info) *info = si;

@@ -65,70 +65,86 @@ __device__ __forceinline__ double group_sum(double v)
 // term is formed as 0 * value, so clamped indices stay inside the staged
 // entries: a value read from unwritten LDS may be NaN)
 
+// cnt values, s[idx] = fin(i, load(idx)), idx = threadIdx.x + 256 i: all N loads
+// of a thread before the first use (j = idx % NR is the same for all of them)
+template <int N, class F, class G>
+__device__ __forceinline__ void stage(double* s, int cnt, F load, G fin)
+{
+    const int tid = threadIdx.x;
+    double v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        v[i] = 0.0;
+        if (256 * i < cnt) v[i] = load(min(tid + 256 * i, cnt - 1));
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if (tid + 256 * i < cnt) s[tid + 256 * i] = fin(i, v[i]);
+}
+
 // ---- forward, diagonal block: z_k = D y_k, D = L_kk^{-1} (lower, w x w,
 // column-major).  LANES lanes per row, one workgroup per item: the rows
 // r0 .. r0 + 256/LANES - 1 of one block; lane q of a row takes the
 // columns p = q, q+LANES, ..., sixteen loads at a time (p > row clamped and
 // multiplied by zero).  Narrow levels (few blocks) use 16 lanes, or 32 when
 // they hold a pair of pieces (a 512-wide inverse): fewer dependent load
-// rounds; wide levels 4 (the items of a level are cut to match).
+// rounds; wide levels 4 (the items of a level are cut to match).  ys:
+// kMaxPairWidth * NR
+template <class T, int LANES, int NR>
+__device__ __forceinline__ void fwd_diag_step(const SweepArgs& a, const DiagItem& it, int rb, double* ys)
+{
+    const int f = it.f, w = it.w, r0 = it.r0;
+    const T* D = static_cast<const T*>(a.dinv) + it.dofs;
+    const int tid = threadIdx.x, q = tid % LANES, row = min(r0 + tid / LANES, w - 1);
+    const int nv = min(NR, a.nrhs - rb);
+    T d[16];   // the first sixteen loads are issued before the staging barrier
+#pragma unroll
+    for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(row + min(q + LANES * u, row) * w)];
+    stage<2 * NR>(ys, w * NR, [&](int idx) {
+        return a.y[(int64_t)(rb + min(idx % NR, nv - 1)) * a.n + f + idx / NR];
+    }, [&](int, double v) { return tid % NR < nv ? v : 0.0; });
+    __syncthreads();
+    double v[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) v[j] = 0.0;
+    for (int pb = 0; pb <= row; pb += 16 * LANES) {
+        if (pb != 0) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(row + min(pb + q + LANES * u, row) * w)];
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int p = pb + q + LANES * u;
+            const double dv = p <= row ? (double)d[u] : 0.0;
+            const double* yp = ys + min(p, w - 1) * NR;
+#pragma unroll
+            for (int j = 0; j < NR; ++j) v[j] += dv * yp[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) v[j] = group_sum<LANES>(v[j]);
+    if (r0 + tid / LANES < w && q == 0)
+        for (int j = 0; j < nv; ++j) a.z[(int64_t)(rb + j) * a.n + f + row] = v[j];
+}
 template <class T, int LANES, int NR>
 __global__ void __launch_bounds__(256) fwd_diag(SweepArgs a, const DiagItem* items)
 {
     __shared__ double ys[kMaxPairWidth * NR];
-    const DiagItem it = items[blockIdx.x];
-    const int f = it.f, w = it.w, r0 = it.r0;
-    const T* D = static_cast<const T*>(a.dinv) + it.dofs;
-    const int tid = threadIdx.x, q = tid % LANES, row = min(r0 + tid / LANES, w - 1);
-    {   // the grid row's block of right-hand sides
-        const int rb = blockIdx.y * NR;
-        const int nv = min(NR, a.nrhs - rb);
-        T d[16];   // the first sixteen loads are issued before the staging barrier
-#pragma unroll
-        for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(row + min(q + LANES * u, row) * w)];
-        for (int idx = tid; idx < w * NR; idx += 256) {
-            const int c = idx / NR, j = idx - c * NR;
-            ys[idx] = j < nv ? a.y[(int64_t)(rb + j) * a.n + f + c] : 0.0;
-        }
-        __syncthreads();
-        double v[NR];
-#pragma unroll
-        for (int j = 0; j < NR; ++j) v[j] = 0.0;
-        for (int pb = 0; pb <= row; pb += 16 * LANES) {
-            if (pb != 0) {
-#pragma unroll
-                for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(row + min(pb + q + LANES * u, row) * w)];
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int p = pb + q + LANES * u;
-                const double dv = p <= row ? (double)d[u] : 0.0;
-                const double* yp = ys + min(p, w - 1) * NR;
-#pragma unroll
-                for (int j = 0; j < NR; ++j) v[j] += dv * yp[j];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < NR; ++j) v[j] = group_sum<LANES>(v[j]);
-        if (r0 + tid / LANES < w && q == 0)
-            for (int j = 0; j < nv; ++j) a.z[(int64_t)(rb + j) * a.n + f + row] = v[j];
-        __syncthreads();
-    }
+    fwd_diag_step<T, LANES, NR>(a, items[blockIdx.x], blockIdx.y * NR, ys);
 }
 
-// ---- forward, off-diagonal rows: y[g(r)] -= sum_c L[r, c] z_k[c].  One
-// workgroup per item: up to 64 panel rows from row0 by the columns
-// c0..c1-1 (levels with few row chunks split each chunk's columns over
-// several items so that the launch fills the chip; their partial sums meet
-// in the atomics).  Lane = row (each load covers 64 consecutive rows of one
-// column), wave v = quarter v of the columns, issued 16 at a time, the
+// ---- forward, off-diagonal rows, one right-hand side: y[g(r)] -= sum_c
+// L[r, c] z_k[c].  One workgroup per item: up to 64 panel rows from row0 by
+// the columns c0..c1-1 (levels with few row chunks split each chunk's columns
+// over several items so that the launch fills the chip; their partial sums
+// meet in the atomics).  Lane = row (each load covers 64 consecutive rows of
+// one column), wave v = quarter v of the columns, issued 16 at a time, the
 // first sixteen before the staging barrier; the four partial sums meet in
 // LDS.
-template <class T, int NR>
+template <class T>
 __global__ void __launch_bounds__(256) fwd_off(SweepArgs a, const OffItem* items)
 {
-    __shared__ double zk[256 * NR];
-    __shared__ double part[4 * 64 * NR];
+    __shared__ double zk[256], part[4 * 64];
     const OffItem it = items[blockIdx.x];
     const int f = it.f, c0 = it.cnr & 511, c1 = (it.cnr >> 9) & 511, nr = it.cnr >> 18;
     const int64_t ld = it.ld;
@@ -138,113 +154,72 @@ __global__ void __launch_bounds__(256) fwd_off(SweepArgs a, const OffItem* items
     const int qw = (c1 - c0 + 3) >> 2, cb = c0 + wave * qw, ce = min(c1, cb + qw);
     const T* Lr = static_cast<const T*>(a.panels) + it.pofs + r;
     const T* Pd = static_cast<const T*>(a.panels) + (it.pofs - it.row0);   // d_c at c * (ld + 1) (L D L^T)
-    {   // the grid row's block of right-hand sides
-        const int rb = blockIdx.y * NR;
-        const int nv = min(NR, a.nrhs - rb);
-        T l[16];
+    T l[16];
 #pragma unroll
-        for (int u = 0; u < 16; ++u) l[u] = Lr[(int64_t)min(cb + u, c1 - 1) * ld];
-        for (int idx = tid; idx < (c1 - c0) * NR; idx += 256) {
-            const int c = c0 + idx / NR, j = idx % NR;
-            zk[idx] = j < nv ? a.z[(int64_t)(rb + j) * a.n + f + c] * (a.ldlt ? (double)Pd[c * (ld + 1)] : 1.0) : 0.0;
-        }
-        __syncthreads();
-        double v[NR];
+    for (int u = 0; u < 16; ++u) l[u] = Lr[(int64_t)min(cb + u, c1 - 1) * ld];
+    const int cz = min(c0 + tid, c1 - 1);
+    const double dz = a.ldlt ? (double)Pd[cz * (ld + 1)] : 1.0;
+    const double z = a.z[f + cz];
+    if (c0 + tid < c1) zk[tid] = z * dz;
+    __syncthreads();
+    double v = 0.0;
+    for (int c = cb; c < ce; c += 16) {
+        if (c != cb) {
 #pragma unroll
-        for (int j = 0; j < NR; ++j) v[j] = 0.0;
-        for (int c = cb; c < ce; c += 16) {
-            if (c != cb) {
-#pragma unroll
-                for (int u = 0; u < 16; ++u) l[u] = Lr[(int64_t)min(c + u, ce - 1) * ld];
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const double lv = c + u < ce ? (double)l[u] : 0.0;
-                const double* zc = zk + (min(c + u, ce - 1) - c0) * NR;
-#pragma unroll
-                for (int j = 0; j < NR; ++j) v[j] += lv * zc[j];
-            }
+            for (int u = 0; u < 16; ++u) l[u] = Lr[(int64_t)min(c + u, ce - 1) * ld];
         }
 #pragma unroll
-        for (int j = 0; j < NR; ++j) part[(wave * 64 + lane) * NR + j] = v[j];
-        __syncthreads();
-        if (wave == 0 && lane < nr) {
-            for (int j = 0; j < nv; ++j) {
-                const double sum = (part[lane * NR + j] + part[(64 + lane) * NR + j]) +
-                                   (part[(128 + lane) * NR + j] + part[(192 + lane) * NR + j]);
-                unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + gi, -sum);
-            }
-        }
-        __syncthreads();
+        for (int u = 0; u < 16; ++u) v += (c + u < ce ? (double)l[u] : 0.0) * zk[min(c + u, ce - 1) - c0];
     }
+    part[wave * 64 + lane] = v;
+    __syncthreads();
+    if (wave == 0 && lane < nr)
+        unsafeAtomicAdd(a.y + gi, -((part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane])));
 }
 
-// ---- backward, off-diagonal rows: tacc[f + c] += sum_r L[r, c] x[g(r)].
-// One workgroup per item: up to 16 LANES panel rows from row0 by the
-// columns c0 .. c1 - 1, 256 / LANES columns at a time; LANES lanes per
-// column, lane q takes the rows q, q + LANES, ... with all sixteen loads in
-// flight (the first block's before the staging barrier).  LANES = 4: 64-row
-// items, the forward kernel's (wide levels: many blocks, few rows each);
-// LANES = 16: 256-row items of 16 columns (narrow levels with one
-// right-hand side; their blocks have thousands of rows: a column of tacc
-// then takes one atomic add per 256 rows instead of per 64, and each load
-// instruction covers 16 consecutive rows of four columns instead of four
-// rows of sixteen).
-template <class T, int LANES, int NR>
+// ---- backward, off-diagonal rows, one right-hand side: tacc[f + c] +=
+// sum_r L[r, c] x[g(r)].  One workgroup per item: up to 16 LANES panel rows
+// from row0 by the columns c0 .. c1 - 1, 256 / LANES columns at a time; LANES
+// lanes per column, lane q takes the rows q, q + LANES, ... with all sixteen
+// loads in flight (the first block's before the staging barrier).  LANES = 4:
+// 64-row items, the forward kernel's (wide levels: many blocks, few rows
+// each); LANES = 16: 256-row items of 16 columns (narrow levels; their blocks
+// have thousands of rows: a column of tacc then takes one atomic add per 256
+// rows instead of per 64, and each load instruction covers 16 consecutive
+// rows of four columns instead of four rows of sixteen).
+template <class T, int LANES>
 __global__ void __launch_bounds__(256) bwd_off(SweepArgs a, const OffItem* items)
 {
-    constexpr int COLS = 256 / LANES, ROWS = 16 * LANES, NST = (ROWS * NR + 255) / 256;
-    __shared__ double xr[ROWS * NR];
+    __shared__ double xr[16 * LANES];
     const OffItem it = items[blockIdx.x];
+    constexpr int COLS = 256 / LANES;
     const int f = it.f, c0 = it.cnr & 511, c1 = (it.cnr >> 9) & 511, nr = it.cnr >> 18;
     const int64_t ld = it.ld;
-    const int32_t* g = a.rowg + it.gofs;
     const int tid = threadIdx.x, q = tid % LANES, cl = tid / LANES;
     const T* L = static_cast<const T*>(a.panels_b) + it.pofs;
-    // global rows of the thread's staged entries (staged entry idx = tid +
-    // 256 i holds row idx / NR), loaded ahead of the panel: the gather then
-    // waits for them only, not for the panel loads issued after them
-    int gv[NST];
+    // global row of the thread's staged entry, loaded ahead of the panel: the
+    // gather then waits for it only, not for the panel loads issued after it
+    const int gv = a.rowg[it.gofs + min(tid, nr - 1)];
+    T l[16];
+    {
+        const T* Lc = L + (int64_t)min(c0 + cl, c1 - 1) * ld;
 #pragma unroll
-    for (int i = 0; i < NST; ++i) gv[i] = g[min((tid + 256 * i) / NR, nr - 1)];
-    {   // the grid row's block of right-hand sides
-        const int rb = blockIdx.y * NR;
-        const int nv = min(NR, a.nrhs - rb);
-        T l[16];
-        {
-            const T* Lc = L + (int64_t)min(c0 + cl, c1 - 1) * ld;
+        for (int u = 0; u < 16; ++u) l[u] = Lc[min(q + LANES * u, nr - 1)];
+    }
+    if (tid < nr) xr[tid] = a.x[gv];
+    __syncthreads();
+    for (int cb = c0; cb < c1; cb += COLS) {
+        const int c = min(cb + cl, c1 - 1);
+        if (cb != c0) {
+            const T* Lc = L + (int64_t)c * ld;
 #pragma unroll
             for (int u = 0; u < 16; ++u) l[u] = Lc[min(q + LANES * u, nr - 1)];
         }
+        double v = 0.0;
 #pragma unroll
-        for (int i = 0; i < NST; ++i) {
-            const int idx = tid + 256 * i, j = idx % NR;
-            if (idx < nr * NR) xr[idx] = j < nv ? a.x[(int64_t)(rb + j) * a.n + gv[i]] : 0.0;
-        }
-        __syncthreads();
-        for (int cb = c0; cb < c1; cb += COLS) {
-            const int c = min(cb + cl, c1 - 1);
-            if (cb != c0) {
-                const T* Lc = L + (int64_t)c * ld;
-#pragma unroll
-                for (int u = 0; u < 16; ++u) l[u] = Lc[min(q + LANES * u, nr - 1)];
-            }
-            double v[NR];
-#pragma unroll
-            for (int j = 0; j < NR; ++j) v[j] = 0.0;
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const double lv = q + LANES * u < nr ? (double)l[u] : 0.0;
-                const double* xp = xr + min(q + LANES * u, nr - 1) * NR;
-#pragma unroll
-                for (int j = 0; j < NR; ++j) v[j] += lv * xp[j];
-            }
-#pragma unroll
-            for (int j = 0; j < NR; ++j) v[j] = group_sum<LANES>(v[j]);
-            if (cb + cl < c1 && q == 0)
-                for (int j = 0; j < nv; ++j) unsafeAtomicAdd(a.tacc + (int64_t)(rb + j) * a.n + f + c, v[j]);
-        }
-        __syncthreads();
+        for (int u = 0; u < 16; ++u) v += (q + LANES * u < nr ? (double)l[u] : 0.0) * xr[min(q + LANES * u, nr - 1)];
+        v = group_sum<LANES>(v);
+        if (cb + cl < c1 && q == 0) unsafeAtomicAdd(a.tacc + f + c, v);
     }
 }
 
@@ -259,42 +234,57 @@ typedef double sw_d4 __attribute__((ext_vector_type(4)));
 
 // forward: y[g(r)] -= (L z)[r] over the item's 64 rows and columns c0..c1.
 // Wave v takes a quarter of the columns, all four 16-row tiles (A = panel
-// rows, B = the staged z, right-hand sides past NR zero); the four waves'
-// partial sums meet in LDS.
+// rows, B = the staged z, right-hand sides past NR zero), the first sixteen
+// columns before the staging barrier; the four waves' partial sums meet in
+// LDS.
 template <class T, int NR>
 __global__ void __launch_bounds__(256) fwd_off_mm(SweepArgs a, const OffItem* items)
 {
-    __shared__ double zk[256 * NR];
-    __shared__ double part[4 * 64 * NR];
+    __shared__ double zk[256 * NR], part[4 * 64 * NR];
     const OffItem it = items[blockIdx.x];
+    const int rb = blockIdx.y * NR;
     const int f = it.f, c0 = it.cnr & 511, c1 = (it.cnr >> 9) & 511, nr = it.cnr >> 18;
     const int64_t ld = it.ld;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
-    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int nv = min(NR, a.nrhs - rb);
     const int qw = (((c1 - c0 + 3) >> 2) + 3) & ~3;   // a wave's columns, a multiple of 4
     const int cb = c0 + wave * qw, ce = min(c1, cb + qw);
     const T* L = static_cast<const T*>(a.panels) + it.pofs;
     const T* Pd = static_cast<const T*>(a.panels) + (it.pofs - it.row0);   // d_c at c * (ld + 1) (L D L^T)
-    for (int idx = tid; idx < (c1 - c0) * NR; idx += 256) {
-        const int c = c0 + idx / NR, j = idx % NR;
-        zk[idx] = j < nv ? a.z[(int64_t)(rb + j) * a.n + f + c] * (a.ldlt ? (double)Pd[c * (ld + 1)] : 1.0) : 0.0;
-    }
+    constexpr int NG = NR / 4;   // rows of y per thread
+    int gr[NG];
+#pragma unroll
+    for (int i = 0; i < NG; ++i) gr[i] = a.rowg[it.gofs + min((tid + 256 * i) / NR, nr - 1)];
+    // (columns past ce read a clamped column and meet B = 0; rows past nr
+    // read a clamped row whose results are not stored)
+    T al[4][4];
+    auto load = [&](int k0) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                al[t][s] = L[min(16 * t + li, nr - 1) + (int64_t)min(k0 + 4 * s + lk, c1 - 1) * ld];
+    };
+    load(cb);
+    const int n0 = (c1 - c0) * NR;
+    double dz[NR];
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+        dz[i] = a.ldlt && 256 * i < n0 ? (double)Pd[min(c0 + (tid + 256 * i) / NR, c1 - 1) * (ld + 1)] : 1.0;
+    stage<NR>(zk, n0, [&](int idx) {
+        return a.z[(int64_t)(rb + min(idx % NR, nv - 1)) * a.n + f + c0 + idx / NR];
+    }, [&](int i, double v) { return tid % NR < nv ? v * dz[i] : 0.0; });
     __syncthreads();
     sw_d4 acc[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) acc[t] = sw_d4{0, 0, 0, 0};
-    // (columns past ce read a clamped column and meet B = 0; rows past nr
-    // read a clamped row whose results are not stored)
     for (int k0 = cb; k0 < ce; k0 += 16) {
-        T al[4][4];
+        if (k0 != cb) load(k0);
         double bz[4];
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const int c = k0 + 4 * s + lk;
-            const int cc = min(c, ce - 1);
-            bz[s] = (c < ce && li < NR) ? zk[(cc - c0) * NR + li] : 0.0;
-#pragma unroll
-            for (int t = 0; t < 4; ++t) al[t][s] = L[min(16 * t + li, nr - 1) + (int64_t)cc * ld];
+            bz[s] = (c < ce && li < NR) ? zk[(min(c, ce - 1) - c0) * NR + li] : 0.0;
         }
 #pragma unroll
         for (int s = 0; s < 4; ++s)
@@ -308,12 +298,13 @@ __global__ void __launch_bounds__(256) fwd_off_mm(SweepArgs a, const OffItem* it
 #pragma unroll
             for (int v = 0; v < 4; ++v) part[(wave * 64 + 16 * t + 4 * v + lk) * NR + li] = acc[t][v];
     __syncthreads();
-    for (int idx = tid; idx < nr * NR; idx += 256) {
-        const int r = idx / NR, j = idx % NR;
-        if (j < nv) {
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        const int idx = tid + 256 * i, r = idx / NR, j = idx % NR;
+        if (r < nr && j < nv) {
             const double sum = (part[r * NR + j] + part[(64 + r) * NR + j]) +
                                (part[(128 + r) * NR + j] + part[(192 + r) * NR + j]);
-            unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + a.rowg[it.gofs + r], -sum);
+            unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + gr[i], -sum);
         }
     }
 }
@@ -326,25 +317,37 @@ __global__ void __launch_bounds__(256) bwd_off_mm(SweepArgs a, const OffItem* it
 {
     __shared__ double xr[kChunk * NR];
     const OffItem it = items[blockIdx.x];
+    const int rb = blockIdx.y * NR;
     const int f = it.f, c0 = it.cnr & 511, c1 = (it.cnr >> 9) & 511, nr = it.cnr >> 18;
     const int64_t ld = it.ld;
-    const int32_t* g = a.rowg + it.gofs;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, li = lane & 15, lk = lane >> 4;
-    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int nv = min(NR, a.nrhs - rb);
     const T* L = static_cast<const T*>(a.panels_b) + it.pofs;
-    for (int idx = tid; idx < kChunk * NR; idx += 256) {
-        const int r = idx / NR, j = idx % NR;
-        xr[idx] = (r < nr && j < nv) ? a.x[(int64_t)(rb + j) * a.n + g[r]] : 0.0;
+    constexpr int NG = kChunk * NR / 256;
+    int gr[NG];
+#pragma unroll
+    for (int i = 0; i < NG; ++i) gr[i] = a.rowg[it.gofs + min((tid + 256 * i) / NR, nr - 1)];
+    T bl[16];
+    auto load = [&](int cb) {
+        const T* Lc = L + (int64_t)min(cb + li, c1 - 1) * ld;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) bl[s] = Lc[min(4 * s + lk, nr - 1)];
+    };
+    load(c0 + 16 * wave);
+    double xg[NG];
+#pragma unroll
+    for (int i = 0; i < NG; ++i) xg[i] = a.x[(int64_t)(rb + min((tid + 256 * i) % NR, nv - 1)) * a.n + gr[i]];
+#pragma unroll
+    for (int i = 0; i < NG; ++i) {
+        const int idx = tid + 256 * i;
+        xr[idx] = idx / NR < nr && idx % NR < nv ? xg[i] : 0.0;
     }
     __syncthreads();
     double ax[16];   // A[rhs = li][row = 4 s + lk]
 #pragma unroll
     for (int s = 0; s < 16; ++s) ax[s] = li < NR ? xr[(4 * s + lk) * NR + li] : 0.0;
     for (int cb = c0 + 16 * wave; cb < c1; cb += 64) {
-        const T* Lc = L + (int64_t)min(cb + li, c1 - 1) * ld;
-        T bl[16];
-#pragma unroll
-        for (int s = 0; s < 16; ++s) bl[s] = Lc[min(4 * s + lk, nr - 1)];
+        if (cb != c0 + 16 * wave) load(cb);
         sw_d4 acc = {0, 0, 0, 0};
 #pragma unroll
         for (int s = 0; s < 16; ++s) acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ax[s], (double)bl[s], acc, 0, 0, 0);
@@ -358,12 +361,10 @@ __global__ void __launch_bounds__(256) bwd_off_mm(SweepArgs a, const OffItem* it
 // ---- backward, diagonal block: x_k = D^T (z_k - t_k); LANES lanes per
 // column c of D, lane q takes the rows p = c+q, c+q+LANES, ... (p >= w
 // clamped and multiplied by zero); the forward kernel's items, columns
-// r0 .. r0 + 256/LANES - 1
+// r0 .. r0 + 256/LANES - 1.  zs: kMaxPairWidth * NR
 template <class T, int LANES, int NR>
-__global__ void __launch_bounds__(256) bwd_diag(SweepArgs a, const DiagItem* items)
+__device__ __forceinline__ void bwd_diag_step(const SweepArgs& a, const DiagItem& it, int rb, double* zs)
 {
-    __shared__ double zs[kMaxPairWidth * NR];
-    const DiagItem it = items[blockIdx.x];
     const int f = it.f, w = it.w, c0 = it.r0;
     const T* D = static_cast<const T*>(a.dinv_b) + it.dofs;
     const int tid = threadIdx.x, q = tid % LANES, col = min(c0 + tid / LANES, w - 1);
@@ -371,42 +372,52 @@ __global__ void __launch_bounds__(256) bwd_diag(SweepArgs a, const DiagItem* ite
     const T* Pd2 = static_cast<const T*>(a.panels) + it.pofs2;  // and c >= w1 at (c - w1) * (ld2 + 1)
     const int64_t ld = it.ld, ld2 = it.ld2;
     const int w1 = it.w1;
-    {   // the grid row's block of right-hand sides
-        const int rb = blockIdx.y * NR;
-        const int nv = min(NR, a.nrhs - rb);
-        T d[16];   // the first sixteen loads are issued before the staging barrier
+    const int nv = min(NR, a.nrhs - rb);
+    T d[16];   // the first sixteen loads are issued before the staging barrier
 #pragma unroll
-        for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(col * w + min(col + q + LANES * u, w - 1))];
-        for (int idx = tid; idx < w * NR; idx += 256) {
-            const int c = idx / NR, j = idx - c * NR;
-            const int64_t o = (int64_t)(rb + j) * a.n + f + c;
-            const double dc = !a.ldlt ? 1.0 : (double)(c < w1 ? Pd[c * (ld + 1)] : Pd2[(c - w1) * (ld2 + 1)]);
-            zs[idx] = j < nv ? (a.z[o] - a.tacc[o]) * dc : 0.0;
+    for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(col * w + min(col + q + LANES * u, w - 1))];
+    double zr[2 * NR], dz[2 * NR];   // z and d of the thread's staged entries
+#pragma unroll
+    for (int i = 0; i < 2 * NR; ++i) {
+        zr[i] = 0.0;
+        dz[i] = 1.0;
+        if (256 * i < w * NR) {
+            const int idx = tid + 256 * i, c = min(idx / NR, w - 1);
+            zr[i] = a.z[(int64_t)(rb + min(idx % NR, nv - 1)) * a.n + f + c];
+            if (a.ldlt) dz[i] = (double)(c < w1 ? Pd[c * (ld + 1)] : Pd2[(c - w1) * (ld2 + 1)]);
         }
-        __syncthreads();
-        double v[NR];
-#pragma unroll
-        for (int j = 0; j < NR; ++j) v[j] = 0.0;
-        for (int pb = col; pb < w; pb += 16 * LANES) {
-            if (pb != col) {
-#pragma unroll
-                for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(col * w + min(pb + q + LANES * u, w - 1))];
-            }
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int p = pb + q + LANES * u;
-                const double dv = p < w ? (double)d[u] : 0.0;
-                const double* zp = zs + min(p, w - 1) * NR;
-#pragma unroll
-                for (int j = 0; j < NR; ++j) v[j] += dv * zp[j];
-            }
-        }
-#pragma unroll
-        for (int j = 0; j < NR; ++j) v[j] = group_sum<LANES>(v[j]);
-        if (c0 + tid / LANES < w && q == 0)
-            for (int j = 0; j < nv; ++j) a.x[(int64_t)(rb + j) * a.n + f + col] = v[j];
-        __syncthreads();
     }
+    stage<2 * NR>(zs, w * NR, [&](int idx) {
+        return a.tacc[(int64_t)(rb + min(idx % NR, nv - 1)) * a.n + f + idx / NR];
+    }, [&](int i, double v) { return tid % NR < nv ? (zr[i] - v) * dz[i] : 0.0; });
+    __syncthreads();
+    double v[NR];
+#pragma unroll
+    for (int j = 0; j < NR; ++j) v[j] = 0.0;
+    for (int pb = col; pb < w; pb += 16 * LANES) {
+        if (pb != col) {
+#pragma unroll
+            for (int u = 0; u < 16; ++u) d[u] = D[(uint32_t)(col * w + min(pb + q + LANES * u, w - 1))];
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const int p = pb + q + LANES * u;
+            const double dv = p < w ? (double)d[u] : 0.0;
+            const double* zp = zs + min(p, w - 1) * NR;
+#pragma unroll
+            for (int j = 0; j < NR; ++j) v[j] += dv * zp[j];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < NR; ++j) v[j] = group_sum<LANES>(v[j]);
+    if (c0 + tid / LANES < w && q == 0)
+        for (int j = 0; j < nv; ++j) a.x[(int64_t)(rb + j) * a.n + f + col] = v[j];
+}
+template <class T, int LANES, int NR>
+__global__ void __launch_bounds__(256) bwd_diag(SweepArgs a, const DiagItem* items)
+{
+    __shared__ double zs[kMaxPairWidth * NR];
+    bwd_diag_step<T, LANES, NR>(a, items[blockIdx.x], blockIdx.y * NR, zs);
 }
 
 // ---- small blocks (width <= 32, at most 128 panel rows), both halves of a
@@ -429,12 +440,12 @@ constexpr int kSGroups = 256 / kSG;        // tiny blocks per workgroup
 
 // forward, tiny block: z_k = D y_k, then y[g(r)] -= L[r, :] z_k
 template <class T, int NR>
-__device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it, bool on)
+__device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it, bool on, int rb)
 {
     const int l = threadIdx.x % kSG, w = it.w(), ld = it.ld(), f = it.f;
     const T* D = static_cast<const T*>(a.dinv) + it.dofs;
     const T* L = static_cast<const T*>(a.panels) + it.pofs;
-    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int nv = min(NR, a.nrhs - rb);
     const int lw = min(l, w - 1);
     T d[8], lv[2][8];
     int g[2];
@@ -449,9 +460,9 @@ __device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it
         for (int c = 0; c < 8; ++c) lv[i][c] = L[min(w + l + kSG * i, ld - 1) + min(c, w - 1) * ld];
 #pragma unroll
     for (int i = 0; i < 2; ++i) g[i] = ld > w ? a.rowg[it.gofs + min(l + kSG * i, ld - w - 1)] : 0;
+    const double s = a.ldlt ? (double)L[lw * (ld + 1)] : 1.0;
 #pragma unroll
     for (int j = 0; j < NR; ++j) y[j] = a.y[(int64_t)(rb + min(j, nv - 1)) * a.n + f + lw];
-    const double s = a.ldlt ? (double)L[lw * (ld + 1)] : 1.0;
     double z[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
@@ -476,12 +487,13 @@ __device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it
 // forward, a wave: lane = row and half of the columns of D, then lane = row
 // below (two of them)
 template <class T, int NR>
-__device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it, bool on, double* ys, double* zs)
+__device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it, bool on, int rb, double* ys,
+                                         double* zs)
 {
     const int lane = threadIdx.x & 63, w = it.w(), ld = it.ld(), f = it.f, R = ld - w;
     const T* D = static_cast<const T*>(a.dinv) + it.dofs;
     const T* L = static_cast<const T*>(a.panels) + it.pofs;
-    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int nv = min(NR, a.nrhs - rb);
     const int r = lane & 31, half = lane >> 5, rw = min(r, w - 1);
     T d[16], lv[2][8];
     int g[2];
@@ -493,9 +505,20 @@ __device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it
         for (int c = 0; c < 8; ++c) lv[i][c] = L[min(w + lane + 64 * i, ld - 1) + min(c, w - 1) * ld];
 #pragma unroll
     for (int i = 0; i < 2; ++i) g[i] = R > 0 ? a.rowg[it.gofs + min(lane + 64 * i, R - 1)] : 0;
-    for (int idx = lane; idx < 32 * NR; idx += 64) {
-        const int c = idx / NR, j = idx % NR;
-        ys[idx] = c < w && j < nv ? a.y[(int64_t)(rb + j) * a.n + f + c] : 0.0;
+    const double s = a.ldlt ? (double)L[rw * (ld + 1)] : 1.0;
+    {
+        constexpr int NY = (32 * NR + 63) / 64;
+        double yv[NY];
+#pragma unroll
+        for (int i = 0; i < NY; ++i) {
+            const int idx = lane + 64 * i;
+            yv[i] = a.y[(int64_t)(rb + min(idx % NR, nv - 1)) * a.n + f + min(idx / NR, w - 1)];
+        }
+#pragma unroll
+        for (int i = 0; i < NY; ++i) {
+            const int idx = lane + 64 * i;
+            if (idx < 32 * NR) ys[idx] = idx / NR < w && idx % NR < nv ? yv[i] : 0.0;
+        }
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
     double z[NR];
@@ -507,7 +530,6 @@ __device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it
 #pragma unroll
         for (int j = 0; j < NR; ++j) z[j] += dv * ys[(2 * i + half) * NR + j];
     }
-    const double s = a.ldlt ? (double)L[rw * (ld + 1)] : 1.0;
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         z[j] += __shfl_xor(z[j], 32);
@@ -547,32 +569,38 @@ __device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it
             for (int j = 0; j < nv; ++j) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + g[i], -v[i][j]);
 }
 
-// grid: ceil(ntiny / 16) workgroups of tiny blocks, then ceil((count -
-// ntiny) / 4) of the others
+// workgroup b of a level's small blocks: ceil(ntiny / 16) of tiny ones, then
+// ceil((count - ntiny) / 4) of the others.  sm: 4 * 2 * 32 * NR
+template <class T, int NR>
+__device__ __forceinline__ void fwd_small_step(const SweepArgs& a, const SmallItem* items, int count, int ntiny, int b,
+                                               int rb, double* sm)
+{
+    const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
+    if (b < nt) {
+        const int idx = b * kSGroups + tid / kSG;
+        const SmallItem it = items[min(idx, ntiny - 1)];
+        fwd_tiny<T, NR> (a, it, idx < ntiny, rb);
+    } else {
+        const int wave = tid >> 6, idx = ntiny + (b - nt) * 4 + wave;
+        const SmallItem it = items[min(idx, count - 1)];
+        fwd_wave<T, NR> (a, it, idx < count, rb, sm + wave * 64 * NR, sm + wave * 64 * NR + 32 * NR);
+    }
+}
 template <class T, int NR>
 __global__ void __launch_bounds__(256) fwd_small(SweepArgs a, const SmallItem* items, int count, int ntiny)
 {
-    __shared__ double sm[4][2][32 * NR];
-    const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
-    if ((int)blockIdx.x < nt) {
-        const int idx = blockIdx.x * kSGroups + tid / kSG;
-        const SmallItem it = items[min(idx, ntiny - 1)];
-        fwd_tiny<T, NR>(a, it, idx < ntiny);
-    } else {
-        const int wave = tid >> 6, idx = ntiny + ((int)blockIdx.x - nt) * 4 + wave;
-        const SmallItem it = items[min(idx, count - 1)];
-        fwd_wave<T, NR>(a, it, idx < count, sm[wave][0], sm[wave][1]);
-    }
+    __shared__ double sm[4 * 64 * NR];
+    fwd_small_step<T, NR>(a, items, count, ntiny, blockIdx.x, blockIdx.y * NR, sm);
 }
 
 // backward, tiny block: t = L_off^T x[g(rows below)], x_k = D^T (z_k - t)
 template <class T, int NR>
-__device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it, bool on)
+__device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it, bool on, int rb)
 {
     const int l = threadIdx.x % kSG, w = it.w(), ld = it.ld(), f = it.f;
     const T* D = static_cast<const T*>(a.dinv_b) + it.dofs;
     const T* L = static_cast<const T*>(a.panels_b) + it.pofs;
-    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int nv = min(NR, a.nrhs - rb);
     // after the sums below lane l holds column (l >> 1) & 7; lane c of the
     // first eight takes column c of D^T
     const int cs = (l >> 1) & 7, cw = min(cs, w - 1), lw = min(l, w - 1);
@@ -589,12 +617,15 @@ __device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it
     const double s = a.ldlt ? (double)L[cw * (ld + 1)] : 1.0;
     double zc[NR], x[2][NR];
 #pragma unroll
-    for (int j = 0; j < NR; ++j) {
-        const int64_t o = (int64_t)(rb + min(j, nv - 1)) * a.n;
-        zc[j] = a.z[o + f + cw];
+    for (int j = 0; j < NR; ++j) zc[j] = a.z[(int64_t)(rb + min(j, nv - 1)) * a.n + f + cw];
 #pragma unroll
-        for (int i = 0; i < 2; ++i) x[i][j] = w + l + kSG * i < ld ? a.x[o + g[i]] : 0.0;
-    }
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i][j] = a.x[(int64_t)(rb + min(j, nv - 1)) * a.n + g[i]];
+#pragma unroll
+    for (int j = 0; j < NR; ++j)
+#pragma unroll
+        for (int i = 0; i < 2; ++i) x[i][j] = w + l + kSG * i < ld ? x[i][j] : 0.0;
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         double t[8];
@@ -628,12 +659,13 @@ __device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it
 // backward, a wave: lane = column and half of the rows below, then of the
 // rows of D
 template <class T, int NR>
-__device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it, bool on, double* xs, double* us)
+__device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it, bool on, int rb, double* xs,
+                                         double* us)
 {
     const int lane = threadIdx.x & 63, w = it.w(), ld = it.ld(), f = it.f, R = ld - w;
     const T* D = static_cast<const T*>(a.dinv_b) + it.dofs;
     const T* L = static_cast<const T*>(a.panels_b) + it.pofs;
-    const int rb = blockIdx.y * NR, nv = min(NR, a.nrhs - rb);
+    const int nv = min(NR, a.nrhs - rb);
     const int c = lane & 31, half = lane >> 5, cw = min(c, w - 1);
     int g[2];
 #pragma unroll
@@ -649,11 +681,17 @@ __device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it
     double zc[NR];
 #pragma unroll
     for (int j = 0; j < NR; ++j) zc[j] = a.z[(int64_t)(rb + min(j, nv - 1)) * a.n + f + cw];
+    {
+        double xv[2][NR];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+        for (int i = 0; i < 2; ++i)
 #pragma unroll
-        for (int j = 0; j < NR; ++j)
-            xs[(lane + 64 * i) * NR + j] = lane + 64 * i < R && j < nv ? a.x[(int64_t)(rb + j) * a.n + g[i]] : 0.0;
+            for (int j = 0; j < NR; ++j) xv[i][j] = a.x[(int64_t)(rb + min(j, nv - 1)) * a.n + g[i]];
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < NR; ++j) xs[(lane + 64 * i) * NR + j] = lane + 64 * i < R && j < nv ? xv[i][j] : 0.0;
+    }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
     double t[NR];
 #pragma unroll
@@ -696,43 +734,76 @@ __device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it
     }
 }
 
+// sm: 4 * 160 * NR
+template <class T, int NR>
+__device__ __forceinline__ void bwd_small_step(const SweepArgs& a, const SmallItem* items, int count, int ntiny, int b,
+                                               int rb, double* sm)
+{
+    const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
+    if (b < nt) {
+        const int idx = b * kSGroups + tid / kSG;
+        const SmallItem it = items[min(idx, ntiny - 1)];
+        bwd_tiny<T, NR> (a, it, idx < ntiny, rb);
+    } else {
+        const int wave = tid >> 6, idx = ntiny + (b - nt) * 4 + wave;
+        const SmallItem it = items[min(idx, count - 1)];
+        bwd_wave<T, NR> (a, it, idx < count, rb, sm + wave * 160 * NR, sm + wave * 160 * NR + 128 * NR);
+    }
+}
 template <class T, int NR>
 __global__ void __launch_bounds__(256) bwd_small(SweepArgs a, const SmallItem* items, int count, int ntiny)
 {
-    __shared__ double xs[4][128 * NR];
-    __shared__ double us[4][32 * NR];
-    const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
-    if ((int)blockIdx.x < nt) {
-        const int idx = blockIdx.x * kSGroups + tid / kSG;
-        const SmallItem it = items[min(idx, ntiny - 1)];
-        bwd_tiny<T, NR>(a, it, idx < ntiny);
-    } else {
-        const int wave = tid >> 6, idx = ntiny + ((int)blockIdx.x - nt) * 4 + wave;
-        const SmallItem it = items[min(idx, count - 1)];
-        bwd_wave<T, NR>(a, it, idx < count, xs[wave], us[wave]);
-    }
+    __shared__ double sm[4 * 160 * NR];
+    bwd_small_step<T, NR>(a, items, count, ntiny, blockIdx.x, blockIdx.y * NR, sm);
+}
+
+// ---- both kinds of a level in one launch, one right-hand side: nd diagonal
+// items, then the small blocks (a launch of the graph takes about 4.5 us
+// however little it does; with 4 or 8 right-hand sides the small blocks need
+// 256 registers, which would halve the diagonal items' waves: two launches)
+template <class T, int LANES>
+__global__ void __launch_bounds__(256) fwd_level(SweepArgs a, const DiagItem* ditems, int nd, const SmallItem* items,
+                                                 int count, int ntiny)
+{
+    __shared__ double sm[kMaxPairWidth];
+    const int b = blockIdx.x;
+    if (b < nd) fwd_diag_step<T, LANES, 1>(a, ditems[b], 0, sm);
+    else fwd_small_step<T, 1>(a, items, count, ntiny, b - nd, 0, sm);
+}
+template <class T, int LANES>
+__global__ void __launch_bounds__(256) bwd_level(SweepArgs a, const DiagItem* ditems, int nd, const SmallItem* items,
+                                                 int count, int ntiny)
+{
+    __shared__ double sm[4 * 160];
+    const int b = blockIdx.x;
+    if (b < nd) bwd_diag_step<T, LANES, 1>(a, ditems[b], 0, sm);
+    else bwd_small_step<T, 1>(a, items, count, ntiny, b - nd, 0, sm);
 }
 
 // ---- vector kernels
-__global__ void permute_in(double* y, const double* b, int64_t ldb, const int32_t* perm, int32_t n, int32_t nrhs)
+// y = the permuted right-hand sides, t = 0 (the backward partial sums)
+__global__ void permute_in(double* y, double* t, const double* b, int64_t ldb, const int32_t* perm, int32_t n,
+                           int32_t nrhs)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t p = perm[i];
-        for (int32_t c = blockIdx.y; c < nrhs; c += gridDim.y) y[(int64_t)c * n + i] = b[c * ldb + p];
+        for (int32_t c = blockIdx.y; c < nrhs; c += gridDim.y) {
+            y[(int64_t)c * n + i] = b[c * ldb + p];
+            t[(int64_t)c * n + i] = 0.0;
+        }
     }
 }
 
-__global__ void permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs)
+// the solution in the user's order; the statistics of the residual that
+// follows cleared
+__global__ void permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs,
+                            unsigned long long* stats)
 {
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x < 5) stats[threadIdx.x * kStatStride] = 0ull;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
         const int32_t p = perm[i];
         for (int32_t c = blockIdx.y; c < nrhs; c += gridDim.y) x[c * ldx + p] = y[(int64_t)c * n + i];
     }
-}
-
-__global__ void zero_u64(unsigned long long* p, int n)
-{
-    for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = 0ull;
 }
 
 __global__ void axpy_kernel(double* x, const double* d, int64_t n)
@@ -773,49 +844,66 @@ __device__ __forceinline__ unsigned long long block_max(unsigned long long v)
 // (stats[q] at word q * kStatStride: every block adds its maxima by atomics,
 // one cache line per statistic; a fixed grid of kResidualBlocks blocks)
 // A thread takes a row and NR right-hand sides at a time (grid rows): its
-// entries are read once for all of them, with no division per element.
+// entries are read once for all of them, kRU entries and their x at a time
+// (bound by the round trips to memory).
 template <int NR>
 __global__ void __launch_bounds__(256) residual_kernel(const int64_t* rptr, const int32_t* rcol, const double* rv,
                                                        const double* x, const double* b,
                                                        int64_t ldb, double* r, int32_t n, int32_t nrhs,
                                                        unsigned long long* stats)
 {
+    constexpr int kRU = NR == 1 ? 8 : 4;
     unsigned long long m0 = 0, m1 = 0, m2 = 0, m3 = 0, m4 = 0;
     auto up = [](unsigned long long& m, double v) {
         const unsigned long long k = key_of(v);
         m = k > m ? k : m;
     };
-    const int c0 = blockIdx.y * NR, nv = min(NR, nrhs - c0);
-    const double* xc = x + (int64_t)c0 * n;
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        double acc[NR], den[NR], arow = 0.0;
-#pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            const double bi = b[(c0 + min(j, nv - 1)) * ldb + i];
-            acc[j] = bi;
-            den[j] = fabs(bi);
-            up(m3, fabs(bi));
-        }
-        for (int64_t q = rptr[i]; q < rptr[i + 1]; ++q) {
-            const double av = rv[q];
-            const int32_t col = rcol[q];
+    for (int c0 = blockIdx.y * NR; c0 < nrhs; c0 += gridDim.y * NR) {
+        const int nv = min(NR, nrhs - c0);
+        const double* xc = x + (int64_t)c0 * n;
+        for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+            double acc[NR], den[NR], arow = 0.0;
 #pragma unroll
             for (int j = 0; j < NR; ++j) {
-                const double xv = xc[(int64_t)min(j, nv - 1) * n + col];
-                acc[j] -= av * xv;
-                den[j] += fabs(av) * fabs(xv);
+                const double bi = b[(c0 + min(j, nv - 1)) * ldb + i];
+                acc[j] = bi;
+                den[j] = fabs(bi);
+                up(m3, fabs(bi));
             }
-            arow += fabs(av);
-        }
+            const int64_t qe = rptr[i + 1];
+            for (int64_t q = rptr[i]; q < qe; q += kRU) {
+                double av[kRU], xv[kRU][NR];
+                int32_t col[kRU];
 #pragma unroll
-        for (int j = 0; j < NR; ++j) {
-            if (j < nv) r[(int64_t)(c0 + j) * n + i] = acc[j];
-            const double ar = fabs(acc[j]);
-            up(m0, ar == 0.0 ? 0.0 : (den[j] == 0.0 ? __builtin_inf() : ar / den[j]));
-            up(m1, ar);
-            up(m2, fabs(xc[(int64_t)min(j, nv - 1) * n + i]));
+                for (int u = 0; u < kRU; ++u) {
+                    av[u] = rv[min(q + u, qe - 1)];
+                    col[u] = rcol[min(q + u, qe - 1)];
+                }
+#pragma unroll
+                for (int u = 0; u < kRU; ++u)
+#pragma unroll
+                    for (int j = 0; j < NR; ++j) xv[u][j] = xc[(int64_t)min(j, nv - 1) * n + col[u]];
+#pragma unroll
+                for (int u = 0; u < kRU; ++u)
+                    if (q + u < qe) {
+#pragma unroll
+                        for (int j = 0; j < NR; ++j) {
+                            acc[j] -= av[u] * xv[u][j];
+                            den[j] += fabs(av[u]) * fabs(xv[u][j]);
+                        }
+                        arow += fabs(av[u]);
+                    }
+            }
+#pragma unroll
+            for (int j = 0; j < NR; ++j) {
+                if (j < nv) r[(int64_t)(c0 + j) * n + i] = acc[j];
+                const double ar = fabs(acc[j]);
+                up(m0, ar == 0.0 ? 0.0 : (den[j] == 0.0 ? __builtin_inf() : ar / den[j]));
+                up(m1, ar);
+                up(m2, fabs(xc[(int64_t)min(j, nv - 1) * n + i]));
+            }
+            up(m4, arow);
         }
-        up(m4, arow);
     }
     m0 = block_max(m0);
     m1 = block_max(m1);
@@ -987,19 +1075,6 @@ static int nr_block(int nrhs) { return nrhs <= 1 ? 1 : (nrhs <= 4 ? 4 : 8); }
         else { constexpr int NR = 8; CALL; } \
     } while (0)
 
-hipError_t launch_fwd_diag(const SweepArgs& a, const DiagItem* items, int count, int lanes, hipStream_t s)
-{
-    if (count <= 0) return hipSuccess;
-    const int nrv = nr_block(a.nrhs);
-    const dim3 grid(count, (a.nrhs + nrv - 1) / nrv);
-#define SPX_FD(L) SPX_NR_DISPATCH(nrv, (a.f32 ? fwd_diag<float, L, NR><<<grid, 256, 0, s>>>(a, items) \
-                                               : fwd_diag<double, L, NR><<<grid, 256, 0, s>>>(a, items)))
-    if (lanes == 32) SPX_FD(32);
-    else if (lanes == 16) SPX_FD(16);
-    else SPX_FD(4);
-#undef SPX_FD
-    return hipGetLastError();
-}
 hipError_t launch_fwd_off(const SweepArgs& a, const OffItem* items, int count, hipStream_t s)
 {
     if (count <= 0) return hipSuccess;
@@ -1014,8 +1089,8 @@ hipError_t launch_fwd_off(const SweepArgs& a, const OffItem* items, int count, h
         }
         return hipGetLastError();
     }
-    SPX_NR_DISPATCH(nr_block(a.nrhs), (a.f32 ? fwd_off<float, NR><<<dim3(count, (a.nrhs + NR - 1) / NR), 256, 0, s>>>(a, items)
-                                             : fwd_off<double, NR><<<dim3(count, (a.nrhs + NR - 1) / NR), 256, 0, s>>>(a, items)));
+    if (a.f32) fwd_off<float><<<count, 256, 0, s>>>(a, items);
+    else fwd_off<double><<<count, 256, 0, s>>>(a, items);
     return hipGetLastError();
 }
 hipError_t launch_bwd_off(const SweepArgs& a, const OffItem* items, int count, bool tall, hipStream_t s)
@@ -1033,25 +1108,67 @@ hipError_t launch_bwd_off(const SweepArgs& a, const OffItem* items, int count, b
         return hipGetLastError();
     }
     if (tall) {
-        SPX_NR_DISPATCH(nr_block(a.nrhs), (a.f32 ? bwd_off<float, 16, NR><<<dim3(count, (a.nrhs + NR - 1) / NR), 256, 0, s>>>(a, items)
-                                                 : bwd_off<double, 16, NR><<<dim3(count, (a.nrhs + NR - 1) / NR), 256, 0, s>>>(a, items)));
+        if (a.f32) bwd_off<float, 16><<<count, 256, 0, s>>>(a, items);
+        else bwd_off<double, 16><<<count, 256, 0, s>>>(a, items);
     } else {
-        SPX_NR_DISPATCH(nr_block(a.nrhs), (a.f32 ? bwd_off<float, 4, NR><<<dim3(count, (a.nrhs + NR - 1) / NR), 256, 0, s>>>(a, items)
-                                                 : bwd_off<double, 4, NR><<<dim3(count, (a.nrhs + NR - 1) / NR), 256, 0, s>>>(a, items)));
+        if (a.f32) bwd_off<float, 4><<<count, 256, 0, s>>>(a, items);
+        else bwd_off<double, 4><<<count, 256, 0, s>>>(a, items);
     }
     return hipGetLastError();
 }
-hipError_t launch_bwd_diag(const SweepArgs& a, const DiagItem* items, int count, int lanes, hipStream_t s)
+// the diagonal items and the small blocks of a level
+hipError_t launch_fwd_level(const SweepArgs& a, const DiagItem* ditems, int nd, int lanes, const SmallItem* items,
+                            int count, int ntiny, hipStream_t s)
 {
-    if (count <= 0) return hipSuccess;
-    const int nrv = nr_block(a.nrhs);
-    const dim3 grid(count, (a.nrhs + nrv - 1) / nrv);
-#define SPX_BD(L) SPX_NR_DISPATCH(nrv, (a.f32 ? bwd_diag<float, L, NR><<<grid, 256, 0, s>>>(a, items) \
-                                               : bwd_diag<double, L, NR><<<grid, 256, 0, s>>>(a, items)))
-    if (lanes == 32) SPX_BD(32);
-    else if (lanes == 16) SPX_BD(16);
-    else SPX_BD(4);
-#undef SPX_BD
+    const int ns = (ntiny + kSGroups - 1) / kSGroups + (count - ntiny + 3) / 4;
+    const int nrv = nr_block(a.nrhs), rows = (a.nrhs + nrv - 1) / nrv;
+    if (nd > 0 && ns > 0 && nrv == 1) {
+#define SPX_LEVEL(L) (a.f32 ? fwd_level<float, L><<<nd + ns, 256, 0, s>>>(a, ditems, nd, items, count, ntiny) \
+                            : fwd_level<double, L><<<nd + ns, 256, 0, s>>>(a, ditems, nd, items, count, ntiny))
+        if (lanes == 32) SPX_LEVEL(32);
+        else if (lanes == 16) SPX_LEVEL(16);
+        else SPX_LEVEL(4);
+#undef SPX_LEVEL
+        return hipGetLastError();
+    }
+    if (nd > 0) {
+#define SPX_DIAG(L) SPX_NR_DISPATCH(nrv, (a.f32 ? fwd_diag<float, L, NR><<<dim3(nd, rows), 256, 0, s>>>(a, ditems) \
+                                                 : fwd_diag<double, L, NR><<<dim3(nd, rows), 256, 0, s>>>(a, ditems)))
+        if (lanes == 32) SPX_DIAG(32);
+        else if (lanes == 16) SPX_DIAG(16);
+        else SPX_DIAG(4);
+#undef SPX_DIAG
+    }
+    if (ns > 0)
+        SPX_NR_DISPATCH(nrv, (a.f32 ? fwd_small<float, NR><<<dim3(ns, rows), 256, 0, s>>>(a, items, count, ntiny)
+                                    : fwd_small<double, NR><<<dim3(ns, rows), 256, 0, s>>>(a, items, count, ntiny)));
+    return hipGetLastError();
+}
+hipError_t launch_bwd_level(const SweepArgs& a, const DiagItem* ditems, int nd, int lanes, const SmallItem* items,
+                            int count, int ntiny, hipStream_t s)
+{
+    const int ns = (ntiny + kSGroups - 1) / kSGroups + (count - ntiny + 3) / 4;
+    const int nrv = nr_block(a.nrhs), rows = (a.nrhs + nrv - 1) / nrv;
+    if (nd > 0 && ns > 0 && nrv == 1) {
+#define SPX_LEVEL(L) (a.f32 ? bwd_level<float, L><<<nd + ns, 256, 0, s>>>(a, ditems, nd, items, count, ntiny) \
+                            : bwd_level<double, L><<<nd + ns, 256, 0, s>>>(a, ditems, nd, items, count, ntiny))
+        if (lanes == 32) SPX_LEVEL(32);
+        else if (lanes == 16) SPX_LEVEL(16);
+        else SPX_LEVEL(4);
+#undef SPX_LEVEL
+        return hipGetLastError();
+    }
+    if (nd > 0) {
+#define SPX_DIAG(L) SPX_NR_DISPATCH(nrv, (a.f32 ? bwd_diag<float, L, NR><<<dim3(nd, rows), 256, 0, s>>>(a, ditems) \
+                                                 : bwd_diag<double, L, NR><<<dim3(nd, rows), 256, 0, s>>>(a, ditems)))
+        if (lanes == 32) SPX_DIAG(32);
+        else if (lanes == 16) SPX_DIAG(16);
+        else SPX_DIAG(4);
+#undef SPX_DIAG
+    }
+    if (ns > 0)
+        SPX_NR_DISPATCH(nrv, (a.f32 ? bwd_small<float, NR><<<dim3(ns, rows), 256, 0, s>>>(a, items, count, ntiny)
+                                    : bwd_small<double, NR><<<dim3(ns, rows), 256, 0, s>>>(a, items, count, ntiny)));
     return hipGetLastError();
 }
 hipError_t launch_pair_inv(const void* panels, void* dinv, bool f32, bool ldlt, const PairItem* items, int count,
@@ -1067,44 +1184,18 @@ hipError_t launch_pair_inv(const void* panels, void* dinv, bool f32, bool ldlt, 
                                               ldlt ? 1 : 0);
     return hipGetLastError();
 }
-hipError_t launch_permute_in(double* y, const double* b, int64_t ldb, const int32_t* perm, int32_t n, int32_t nrhs,
-                             hipStream_t s)
+hipError_t launch_permute_in(double* y, double* t, const double* b, int64_t ldb, const int32_t* perm, int32_t n,
+                             int32_t nrhs, hipStream_t s)
 {
-    permute_in<<<dim3(grid_for(n), std::min(nrhs, 64)), 256, 0, s>>>(y, b, ldb, perm, n, nrhs);
+    permute_in<<<dim3(grid_for(n), std::min(nrhs, 64)), 256, 0, s>>>(y, t, b, ldb, perm, n, nrhs);
     return hipGetLastError();
 }
 hipError_t launch_permute_out(double* x, int64_t ldx, const double* y, const int32_t* perm, int32_t n, int32_t nrhs,
-                              hipStream_t s)
+                              unsigned long long* stats, hipStream_t s)
 {
-    permute_out<<<dim3(grid_for(n), std::min(nrhs, 64)), 256, 0, s>>>(x, ldx, y, perm, n, nrhs);
+    permute_out<<<dim3(grid_for(n), std::min(nrhs, 64)), 256, 0, s>>>(x, ldx, y, perm, n, nrhs, stats);
     return hipGetLastError();
 }
-hipError_t launch_zero_u64(unsigned long long* p, int n, hipStream_t s)
-{
-    zero_u64<<<1, 256, 0, s>>>(p, n);
-    return hipGetLastError();
-}
-
-hipError_t launch_fwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s)
-{
-    if (count <= 0) return hipSuccess;
-    const int nrv = nr_block(a.nrhs);
-    const dim3 grid((ntiny + kSGroups - 1) / kSGroups + (count - ntiny + 3) / 4, (a.nrhs + nrv - 1) / nrv);
-    SPX_NR_DISPATCH(nrv, (a.f32 ? fwd_small<float, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)
-                                : fwd_small<double, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)));
-    return hipGetLastError();
-}
-
-hipError_t launch_bwd_small(const SweepArgs& a, const SmallItem* items, int count, int ntiny, hipStream_t s)
-{
-    if (count <= 0) return hipSuccess;
-    const int nrv = nr_block(a.nrhs);
-    const dim3 grid((ntiny + kSGroups - 1) / kSGroups + (count - ntiny + 3) / 4, (a.nrhs + nrv - 1) / nrv);
-    SPX_NR_DISPATCH(nrv, (a.f32 ? bwd_small<float, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)
-                                : bwd_small<double, NR><<<grid, 256, 0, s>>>(a, items, count, ntiny)));
-    return hipGetLastError();
-}
-
 hipError_t launch_axpy(double* x, const double* d, int64_t n, hipStream_t s)
 {
     axpy_kernel<<<grid_for(n), 256, 0, s>>>(x, d, n);
@@ -1115,8 +1206,8 @@ hipError_t launch_residual(const int64_t* rptr, const int32_t* rcol, const doubl
                            unsigned long long* stats, hipStream_t s)
 {
     const int nr = nrhs <= 1 ? 1 : 4;
-    const int rows = (nrhs + nr - 1) / nr;
-    const int blocks = (int)std::min<int64_t>(std::max(1, kResidualBlocks / rows), std::max<int64_t>(1, ((int64_t)n + 255) / 256));
+    const int rows = std::min((nrhs + nr - 1) / nr, 64);
+    const int blocks = (int)std::min<int64_t>(std::max(64, kResidualBlocks / rows), std::max<int64_t>(1, ((int64_t)n + 255) / 256));
     if (nr == 1) residual_kernel<1><<<dim3(blocks, rows), 256, 0, s>>>(rptr, rcol, rv, x, b, ldb, r, n, nrhs, stats);
     else residual_kernel<4><<<dim3(blocks, rows), 256, 0, s>>>(rptr, rcol, rv, x, b, ldb, r, n, nrhs, stats);
     return hipGetLastError();

@@ -32,16 +32,12 @@ def _system(w, r, rng, sym):
     return A
 
 
-@pytest.mark.parametrize("nrhs", [1, 2, 4, 5, 8, 13])
-@pytest.mark.parametrize("method,precision", [("llt", "fp64"), ("ldlt", "fp64"), ("lu", "fp64"), ("llt", "fp32_ir"),
-                                              ("ldlt", "fp32_ir"), ("lu", "fp32_ir")])
-def test_shapes(method, precision, nrhs):
+def _check(shapes, method, precision, nrhs, m0):
     import torch
     from paper_1405_2636_amd import Solver
     rng = np.random.default_rng(nrhs)
     mats = [_system(w, r, rng, method != "lu") * (-1 if method == "ldlt" and q % 2 else 1)
-            for q, (w, r) in enumerate(SHAPES)]
-    print("small sweeps", method, precision, nrhs, flush=True)
+            for q, (w, r) in enumerate(shapes)]
     A = sp.csc_matrix(sp.block_diag(mats))
     A.sort_indices()
     n = A.shape[0]
@@ -53,8 +49,29 @@ def test_shapes(method, precision, nrhs):
     x = x.cpu().numpy()
     u = 2.0 ** -53 if precision == "fp64" else 2.0 ** -24
     o = 0
-    for (w, r), M in zip(SHAPES, mats):
+    for (w, r), M in zip(shapes, mats):
         m = len(M)
         ref = np.linalg.solve(M, b[:, o:o + m].T).T
-        assert np.max(np.abs(x[:, o:o + m] - ref)) <= 64 * 160 * u * np.max(np.abs(ref)), (w, r)
+        assert np.max(np.abs(x[:, o:o + m] - ref)) <= 64 * max(m0, m) * u * np.max(np.abs(ref)), (w, r)
         o += m
+
+
+MODES = pytest.mark.parametrize("method,precision", [("llt", "fp64"), ("ldlt", "fp64"), ("lu", "fp64"), ("llt", "fp32_ir"),
+                                                     ("ldlt", "fp32_ir"), ("lu", "fp32_ir")])
+
+
+@pytest.mark.parametrize("nrhs", [1, 2, 4, 5, 8, 13, 17])
+@MODES
+def test_shapes(method, precision, nrhs):
+    print("small sweeps", method, precision, nrhs, flush=True)
+    _check(SHAPES, method, precision, nrhs, 160)
+
+
+@pytest.mark.parametrize("many", [0, 1])
+@pytest.mark.parametrize("nrhs", [1, 3, 8, 17])
+@MODES
+def test_wide(method, precision, nrhs, many):
+    """Wider blocks, next to multiples of 16 and 64: the diagonal and
+    off-diagonal steps, on levels of few blocks and of many."""
+    print("wide blocks", method, precision, nrhs, many, flush=True)
+    _check([(47, 33), (64, 65), (65, 200), (130, 65)] + [(33, 40)] * (64 * many), method, precision, nrhs, 0)

@@ -339,6 +339,28 @@ void build_tasks(spx_handle* h)
     std::vector<char> inv(nc, 0);
     for (int32_t k = 0; k < nc; ++k)
         inv[k] = hp[k] && per_level[lvl[k]] <= kInvLevel && solves[lvl[k]] <= kInvSolves && P.lcol[k] - P.fcol[k] + 1 >= 128;
+    // All updates of a level take thin tiles if these are at most kFineTiles
+    // in FP64, kFineTiles32 in FP32 (L U: both sides in one item): with 256 x
+    // 64 tiles such a level is one or two rounds of the workgroups, a tile
+    // takes 60 us alone and twice that beside another on its CU, and the
+    // factorization above waits for the last one; sixteen rounds of a quarter
+    // of the time end together.  More of them lose to the larger tiles, which
+    // load and claim less per product.  Scheduler kernel, ms, with at most 0,
+    // 1024, 4096, 8192, 16384 tiles: 41x37x43 3.09, 2.74, 2.70, 2.70, 2.71;
+    // 48^3 5.3, 5.0, 4.52, 4.48, 4.47; 50x47x49 L U 11.2, 10.9, 9.9, 9.4, 9.4;
+    // 18x20x19 elasticity L D L^T 3.70, 3.51, 3.35, 3.39, 3.33; 36x35x34 2.20,
+    // 1.92, 1.93, 1.91, 1.92; 72x70x69 18.4, -, 18.2, 18.0, 18.8; 100^3 86.0, -,
+    // 85.5, 85.6, 87.1; FP32, whose tiles take half the time: 63x65x61 8.41,
+    // 8.34, 8.41, 8.88, 8.80; 80^3 split BF16 15.9, 16.0, 16.3, 16.8, 20.4.
+    constexpr double kFineTiles = 8192, kFineTiles32 = 1024;
+    std::vector<double> tiles(static_cast<size_t>(nc) + 1, 0.0);   // thin tiles of a level's updates
+    for (int32_t k = 0; k < nc; ++k) {
+        const double r = P.stride[k] - (P.lcol[k] - P.fcol[k] + 1);
+        tiles[lvl[k]] += r * r / (64.0 * 64.0) * (h->lu() ? 1.0 : 0.5);
+    }
+    std::vector<char> fine(nc, 0);
+    for (int32_t k = 0; k < nc; ++k)
+        fine[k] = tiles[lvl[k]] <= (h->f32() ? kFineTiles32 : kFineTiles) && P.lcol[k] - P.fcol[k] + 1 >= 32;
     // update tiles of source k into target group [b, b2) (blocks facing one
     // cblk), tr x tcl each
     auto for_tiles = [&](int32_t k, int32_t b, int32_t b2, int32_t tr, int32_t tcl, auto&& fn) {
@@ -533,7 +555,7 @@ void build_tasks(spx_handle* h)
                 rmap.push_back(pos);
             }
             const int32_t mbase = static_cast<int32_t>(moff - rs);
-            const bool thin = chain[k] && first_pair && !small[k];
+            const bool thin = ((chain[k] && first_pair) || fine[k]) && !small[k];
             const int32_t ttr = thin ? 64 : h->tile_rows, ttc = thin ? 64 : h->tile_cols;
             const int32_t pfirst = id;
             for_tiles(k, b, b2, ttr, ttc, [&](int32_t r0, int32_t mr, int32_t c0, int32_t ncl) {

@@ -165,7 +165,7 @@ constexpr int kSmallMaxUpd = 64;
 constexpr int kSmallMap = 2048;
 // and those of at most kTinyW columns and kTinyRows panel rows, with at most
 // kTinyTiles update tiles and kTinyMap row-map entries, as groups
-constexpr int kTinyW = 16, kTinyRows = 32, kTinyTiles = 8, kTinyMap = 256;
+constexpr int kTinyW = 16, kTinyRows = 64, kTinyTiles = 16, kTinyMap = 512;
 
 // Residual statistics: one 256-byte line per statistic (five of them),
 // filled by a fixed grid of blocks.

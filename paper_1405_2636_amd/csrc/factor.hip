@@ -1875,7 +1875,7 @@ __device__ __noinline__ void task_small(const SchedArgs& a, Geo g, const int4 d1
 }
 
 // ---------------------------------------------------------------- tiny blocks
-// Column blocks of at most 16 columns and 32 panel rows, a wave each, up to
+// Column blocks of at most 16 columns and 64 panel rows, a wave each, up to
 // kTinyGroup blocks of one dependency level per item (no block of a level
 // depends on another one).  At the bottom of a 2-D problem or of a batch
 // nearly all blocks are a few columns wide; as an item of a whole workgroup
@@ -1884,18 +1884,26 @@ __device__ __noinline__ void task_small(const SchedArgs& a, Geo g, const int4 d1
 // operands and of the counters are shared by the group, and the whole panel
 // goes through the tile factorization: its rows below the block are more
 // rows of the tile (l_rc = (a_rc - sum) / l_cc, stepped with the block's own
-// columns), so that L comes out in one pass.  The update tiles are formed
-// from LDS, row by lane, two columns at a time, and scattered by atomics.
+// columns), so that L comes out in one pass; rows past 32 (TALL) become
+// A_off D^T, row by lane, from the inverse in LDS.  The update tiles are
+// formed from LDS, row by lane (up to 32 rows: two columns at a time), and
+// scattered by atomics.
 // LDS per wave: rows of L (stride NC + 2), the row map, the target of every
-// facing row, the broadcast buffer.
-constexpr int kTinyLds = 1024;   // doubles per wave
-static_assert(kTinyRows * (kTinyW + 2) + kTinyMap / 2 + 2 * kTinyRows + 64 + kTinyW + 4 * kTinyTiles <= kTinyLds, "LDS of a tiny block");
+// facing row, the tiles, the broadcast buffer, the inverse.
+// 701x503, where half the time of the small blocks went into blocks of 33 to
+// 64 panel rows as items of a workgroup: 2.20 -> 1.90 ms; 256 grids of side 16
+// to 96: 1.60 -> 1.49.
+constexpr int kTinyLds = 2112;   // doubles per wave
+static_assert(kTinyRows * (kTinyW + 2) + kTinyMap / 2 + 2 * kTinyRows + 4 * kTinyTiles + 64 + kTinyW + kTinyW * kTinyW <= kTinyLds,
+              "LDS of a tiny block");
+static_assert(kTinyTiles <= 64 && kTinyRows <= 64, "a lane each");
 static_assert((kThreads / 64) * kTinyLds <= kTiles * kTSz, "LDS of a group of tiny blocks");
 
-template <class T, int NC, bool LDL>
+// TALL: more than 32 panel rows, 8 tiles or 256 row-map entries
+template <class T, int NC, bool LDL, bool TALL>
 __device__ __forceinline__ void tiny_block(const SchedArgs& a, const int4 q0, const int4 q1, int tfirst, double thr, double* ws)
 {
-    constexpr int LS = NC + 2;
+    constexpr int LS = NC + 2, NM = TALL ? kTinyMap / 64 : 4;
     const int f = uni(q0.x), w = uni(q0.y) & 255, ld = (uni(q0.y) >> 8) & 255, nupd = uni(q0.y) >> 16, mstart = uni(q0.z),
               mlen = uni(q0.w);
     T* A = static_cast<T*>(a.panels) + words64(uni(q1.x), uni(q1.y));
@@ -1906,13 +1914,18 @@ __device__ __forceinline__ void tiny_block(const SchedArgs& a, const int4 q0, co
     auto tab = smap + kTinyMap;             // facing row r: map base, stride and panel offset of its target
     auto dt = tab + 4 * kTinyRows;          // tile u: gate, first and last + 1 facing row, map base, stride, offset
     double* bc = ws + kTinyRows * (kTinyW + 2) + (kTinyMap + 4 * kTinyRows + 8 * kTinyTiles) / 2;
+    auto M = lds(bc + 64 + kTinyW);         // TALL: the inverse, row by row
     const GOp gA = make_gop(A, (int64_t)ld * w, 0, 1, ld);
     T av[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) av[c] = gload<T>(gA, c < w && r < ld ? r * gA.si + c * gA.sk : kOffNone);
-    int mv[kTinyMap / 64];
+    T bv[TALL ? NC : 1];   // row 32 + r
+    if constexpr (TALL)
 #pragma unroll
-    for (int q = 0; q < kTinyMap / 64; ++q) mv[q] = a.rmap[mlen > 0 ? mstart + min(lane + 64 * q, mlen - 1) : 0];
+        for (int c = 0; c < NC; ++c) bv[c] = gload<T>(gA, c < w && r + 32 < ld ? (r + 32) * gA.si + c * gA.sk : kOffNone);
+    int mv[NM];
+#pragma unroll
+    for (int q = 0; q < NM; ++q) mv[q] = a.rmap[mlen > 0 ? mstart + min(lane + 64 * q, mlen - 1) : 0];
     int4 u0 = {0, 0, 0, 0}, u1 = u0, u2 = u0;
     if (lane < nupd) {
         const int4* ft = a.ftab + 3 * (int64_t)(tfirst + lane);
@@ -1941,8 +1954,24 @@ __device__ __forceinline__ void tiny_block(const SchedArgs& a, const int4 q0, co
 #pragma unroll
         for (int c = 0; c < NC; ++c) S[r * LS + c] = c < w ? (double)(T)tc.v[c] : 0.0;
     }
+    if constexpr (TALL) {
 #pragma unroll
-    for (int q = 0; q < kTinyMap / 64; ++q) smap[lane + 64 * q] = mv[q];
+        for (int c = 0; c < NC; ++c)
+            if (lane >= 32 && r < NC) M[c * NC + r] = r <= c && c < w ? tc.v[c] : 0.0;
+        __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) {
+            double x = 0.0;
+#pragma unroll
+            for (int t = 0; t <= c; ++t) x += (double)bv[t] * M[c * NC + t];
+            if (lane < 32) {
+                if (c < w && r + 32 < ld) oA[r + 32 + c * ld] = (T)x;
+                S[(r + 32) * LS + c] = (double)(T)x;
+            }
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < NM; ++q) smap[lane + 64 * q] = mv[q];
     if (lane < nupd) {
         auto e = dt + 8 * lane;
         e[0] = u0.w;               // first facing row
@@ -1955,29 +1984,31 @@ __device__ __forceinline__ void tiny_block(const SchedArgs& a, const int4 q0, co
     __atomic_signal_fence(__ATOMIC_SEQ_CST);   // (LDS operations of a wave complete in order)
     for (int u = 0; u < nupd; ++u) {
         const int b = dt[8 * u], e = dt[8 * u + 1];
-        if (lane < 32 && r >= b && r < e) {
+        if (lane < kTinyRows && lane >= b && lane < e) {
 #pragma unroll
-            for (int i = 0; i < 4; ++i) tab[4 * r + i] = dt[8 * u + 2 + i];
+            for (int i = 0; i < 4; ++i) tab[4 * lane + i] = dt[8 * u + 2 + i];
         }
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
-    // C_j[rmap(r), rmap(c)] -= L_r . L_c (L D L^T: L_r D L_c), r >= c; the
-    // halves of the wave take the facing rows c alternately
+    // C_j[rmap(r), rmap(c)] -= L_r . L_c (L D L^T: L_r D L_c), r >= c; up to 32
+    // rows: the halves of the wave take the facing rows c alternately
+    constexpr int half = TALL ? 1 : 2;
+    const int ro = TALL ? lane : r;
     double own[NC];
 #pragma unroll
     for (int t = 0; t < NC; ++t) {
-        const double s = S[min(r, ld - 1) * LS + t];
+        const double s = S[min(ro, ld - 1) * LS + t];
         own[t] = !LDL ? s : t < w ? s * lds(bc)[64 + t] : 0.0;   // (pivots past w are undefined)
     }
     if (nupd > 0)
-        for (int c = w + (lane >> 5); c < ld; c += 2) {
+        for (int c = w + (TALL ? 0 : lane >> 5); c < ld; c += half) {
             double acc = 0.0;
 #pragma unroll
             for (int t = 0; t < NC; ++t) acc += own[t] * S[c * LS + t];
             const int mb = tab[4 * c], ldj = tab[4 * c + 1];
             auto Cg = glob(static_cast<T*>(a.panels) + words64(tab[4 * c + 2], tab[4 * c + 3]));
-            if (r >= c && r < ld)
-                __hip_atomic_fetch_add(Cg + (int64_t)smap[mb + c] * ldj + smap[mb + r], (T)(-acc), __ATOMIC_RELAXED, AGENT);
+            if (ro >= c && ro < ld)
+                __hip_atomic_fetch_add(Cg + (int64_t)smap[mb + c] * ldj + smap[mb + ro], (T)(-acc), __ATOMIC_RELAXED, AGENT);
         }
     __builtin_amdgcn_s_waitcnt(0);   // the block's atomics have completed
     if (lane < nupd) finish_update(a, u0.x);
@@ -1991,8 +2022,16 @@ __device__ __noinline__ void task_tiny(const SchedArgs& a, int first, int count,
         const int4* t = a.tiny + 3 * (int64_t)(first + q);
         const int4 q0 = t[0], q1 = t[1];
         const int tf = uni(t[2].x);
-        if ((uni(q0.y) & 255) <= 8) tiny_block<T, 8, LDL>(a, q0, q1, tf, thr, tiles + wave * kTinyLds);
-        else tiny_block<T, 16, LDL>(a, q0, q1, tf, thr, tiles + wave * kTinyLds);
+        const int w = uni(q0.y) & 255, ld = (uni(q0.y) >> 8) & 255, nupd = uni(q0.y) >> 16;
+        double* ws = tiles + wave * kTinyLds;
+        if (ld > 32 || nupd > 8 || uni(q0.w) > 256) {
+            if (w <= 8) tiny_block<T, 8, LDL, true>(a, q0, q1, tf, thr, ws);
+            else tiny_block<T, 16, LDL, true>(a, q0, q1, tf, thr, ws);
+        } else if (w <= 8) {
+            tiny_block<T, 8, LDL, false>(a, q0, q1, tf, thr, ws);
+        } else {
+            tiny_block<T, 16, LDL, false>(a, q0, q1, tf, thr, ws);
+        }
     }
 }
 

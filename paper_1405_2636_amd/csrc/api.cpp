@@ -191,7 +191,8 @@ struct spx_handle {
     hipGraph_t fgraph[2] = {nullptr, nullptr};
     hipGraphExec_t fgraph_exec[2] = {nullptr, nullptr};
     int device = 0;
-    int grid = 0;
+    int grid = 0, ncu = 0;     // workers of the scheduler kernel at most; compute units
+    bool one_per_cu = false;   // a worker per CU
     // the fixed work array of the allocation-free solve on this handle's
     // device (device address, from scratch_region at the plan upload)
     void* scratch = nullptr;
@@ -413,6 +414,36 @@ void build_tasks(spx_handle* h)
             if (tiny[k] && P.stride[k] > 32) ++ntall[lvl[k]];
         for (int32_t k = 0; k < nc; ++k)
             if (P.stride[k] > 32 && ntall[lvl[k]] < kTinyItems) tiny[k] = 0;
+    }
+    // Workers: one per CU where the elimination chain is longer than the work.
+    // A second workgroup on a CU hides the latency of the other and nearly
+    // doubles the rate of the products, but an item of the chain beside a long
+    // update takes up to twice its time.  The chain: the longest path of
+    // factorizations (0.28 us a column, L U 0.55) and links to the next block
+    // (panel solve, update, two queue passes: 50 us); the work: products at
+    // 52 TFLOP/s (FP32 105) and the small blocks over 512 workers.  Scheduler
+    // kernel, ms, with two and one workers per CU, and work / chain: 64^2 0.273,
+    // 0.251 (0.01); 36x35x34 1.93, 1.73 (0.09); 41x37x43 2.68, 2.33 (0.14);
+    // elasticity 18x20x19 4.0, 3.39 (0.20); 48^3 4.47, 4.03 (0.28); 701x503 1.90,
+    // 1.90 (0.27); 50x47x49 L U 9.4, 8.35 (0.39); 63x65x61 FP32 8.4, 7.7 (0.43);
+    // 80^3 split BF16 16.0, 17.4 (1.2); 72x70x69 18.0, 19.1 (1.4); 256 grids 1.49,
+    // 2.3 (2.3); 100^3 86, 106 (6.3).  (Two with the second one of a CU
+    // working behind a backlog only: no better than two.)
+    {
+        constexpr double kChainLonger = 0.75;
+        const double col = h->lu() ? 0.55 : 0.28, rate = h->f32() ? 105e6 : 52e6;   // us, FLOP / us
+        std::vector<double> at(nc, 0.0);
+        double chain_us = 0.0, work_us = 0.0;
+        for (int32_t k = 0; k < nc; ++k) {
+            const double w = P.lcol[k] - P.fcol[k] + 1, r = P.stride[k] - w;
+            at[k] += small[k] ? 25.0 : 10.0 + col * w;
+            chain_us = std::max(chain_us, at[k]);
+            for (int32_t q = P.uptr[k]; q < P.uptr[k + 1]; ++q)
+                at[P.utgt[q]] = std::max(at[P.utgt[q]], at[k] + (small[k] ? 0.0 : 50.0));
+            work_us += (w * w * w / 3.0 + w * w * r + w * r * r) * (h->lu() ? 2.0 : 1.0) / rate;
+            if (small[k]) work_us += (P.lcol[k] - P.fcol[k] + 1 <= kTinyW && P.stride[k] <= kTinyRows ? 4.0 : 25.0) / 512.0;
+        }
+        h->one_per_cu = work_us < kChainLonger * chain_us;
     }
     std::vector<int32_t> item(nc, -1), group;   // group: blocks of the tiny items, item by item
     std::vector<int32_t> gptr{0}, first_of;      // their ends; first block of every factoring item
@@ -946,6 +977,7 @@ void upload_plan(spx_handle* h)
     HIPCHK(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
     if (hipDeviceGetAttribute(&clk_khz, hipDeviceAttributeWallClockRate, h->device) != hipSuccess || clk_khz <= 0)
         clk_khz = 100000;
+    h->ncu = std::max(1, ncu);
     h->grid = std::max(1, ncu * sched_blocks_per_cu(h->f32(), h->ldlt(), h->lu()));
     h->timeout_ticks = static_cast<int64_t>(clk_khz) * 1000 * 20;   // 20 s per wait
     HIPCHK(scratch_region(&h->scratch, &h->scratch_bytes));
@@ -1024,7 +1056,7 @@ void factor_part(spx_handle* h, int part, hipStream_t s)
     const bool f32 = h->f32();
     const SchedArgs a = sched_args(h);
     if (part == 1) {
-        if (h->total > 0) HIPCHK(launch_sched(a, f32, h->lu(), h->grid, s));
+        if (h->total > 0) HIPCHK(launch_sched(a, f32, h->lu(), h->one_per_cu ? std::min(h->ncu, h->grid) : h->grid, s));
         return;
     }
     const int64_t nsym = P.rptr.empty() ? 0 : P.rptr.back();

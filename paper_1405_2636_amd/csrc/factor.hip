@@ -483,6 +483,16 @@ struct Geo {
 };
 __device__ __forceinline__ int64_t words64(int lo, int hi) { return (int64_t)(uint32_t)lo | ((int64_t)hi << 32); }
 
+// (L D L^T) the pivots of the diagonal block in work: one array for FACT and
+// INV items, which never run at once in a workgroup (an array each left LDS
+// for one workgroup per CU instead of two)
+template <bool LDL>
+__device__ __forceinline__ double* ldl_pivots()
+{
+    __shared__ double dd[LDL ? 256 : 1];
+    return dd;
+}
+
 // ---------------------------------------------------------------- FACT(k)
 // 1/d from the hardware estimate and two Newton-Raphson steps
 __device__ __forceinline__ double recip_nr(double d)
@@ -1166,7 +1176,7 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, Geo g, bool full, dou
     const int tid = threadIdx.x, wave = uni(tid >> 6), lane = tid & 63, li = lane & 15, lk = lane >> 4;
     double* bc = Lt + kNB * 33;
     __shared__ int s_x[8], s_d;      // blocks of row block i published (i + 1: D_ii too); tiles factored
-    __shared__ double dd[LDL ? 256 : 1];   // (L D L^T) the pivots
+    double* dd = ldl_pivots<LDL>();
     const int nb = (w + kNB - 1) / kNB;
     if (tid < 8) s_x[tid] = 0;
     if (tid == 8) s_d = 0;
@@ -1424,7 +1434,7 @@ __device__ __noinline__ void task_inv(const SchedArgs& a, Geo g)
     const GOp gA = make_gop(A, ld * w, 0, 1, ld);
     const int tid = threadIdx.x, wave = uni(tid >> 6), nb = (w + kNB - 1) / kNB;
     __shared__ int s_x[8], s_d;
-    __shared__ double dd[LDL ? 256 : 1];
+    double* dd = ldl_pivots<LDL>();
     if (tid < 8) s_x[tid] = 9;   // everything is there
     if (tid == 8) s_d = 9;
     if (LDL && tid < w) dd[tid] = (double)A[tid * (ld + 1)];

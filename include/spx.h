@@ -147,12 +147,13 @@ typedef struct spx_info {
     double logdet;            /* log det A after a factorization (SPX_LDLT, SPX_LU: log |det A|) */
     double factor_kernel_ms;  /* last factorization: scheduler kernel time (HIP events) */
     double assemble_ms;       /* last factorization: assembly kernel time */
-    int32_t tile_rows;        /* update tile in use: 256 x 64 or 128 x 128 */
+    int32_t tile_rows;        /* update tile in use: 256 x 64 or 128 x 128 (levels with
+                               * little work take 64 x 64 in both) */
     int32_t tile_cols;
     int32_t hp_policy;        /* 0: every elimination chain first; 1: only the upper levels */
     int32_t nsys;             /* independent systems of the handle (spx_analyze_batch), 1 otherwise */
     int64_t nfused_tiles;     /* update tiles carried out inside fused items (not in ntasks) */
-    int32_t nsmall;           /* column blocks handled as one fused item (fuse_small) */
+    int32_t nsmall;           /* column blocks handled in fused items (fuse_small) */
     int32_t nneg;             /* SPX_LDLT: negative pivots (the inertia's negative count;
                                * sign det A = (-1)^nneg); SPX_LU: negative u_jj (sign det
                                * A = (-1)^nneg); 0 for SPX_LLT */
@@ -288,8 +289,8 @@ int spx_copy_factor(spx_handle* h, double* dst, int32_t dst_on_device, void* hip
 /* Task trace of the last factorization (trace option on): 4 int64 per work
  * item in dst {claimed, started, finished: device wall-clock ticks; hardware
  * id register of the executing wave}, and, if kinds is not NULL, 4 int32 per
- * item {kind 0 factor / 1 triangular solve / 2 update / 3 fused small block /
- * 4 off-diagonal tiles of a chain block's inverse,
+ * item {kind 0 factor / 1 triangular solve / 2 update / 3 fused small block, or
+ * a group of up to 8 of them (source: the first) / 4 off-diagonal tiles of a chain block's inverse,
  * source cblk, target cblk, rows*cols of an update tile or rows of a solve
  * tile}.  cap = number of items dst can hold (info.ntasks).  Returns the
  * item count, or a negative status. */

@@ -283,13 +283,14 @@ int guarded(spx_handle* h, F&& f)
     }
 }
 
-// Work items of the device scheduler, in id order: FACT(k) = k, then per cblk
-// its TRSM row tiles (64 rows), then per cblk its UPDATE tiles.  The update
-// tiles of a pair (k, j) are 256 rows by 64 facing columns; tiles entirely
-// in the strict upper
-// triangle of j's diagonal block are not generated.  The tiles into the
-// first facing cblk (the next block of an elimination chain) come first and
-// go to the high-priority queue, like FACT and TRSM items.
+// Work items of the device scheduler, in id order: the items that factor
+// blocks (FACT or a fused small block each, or a group of tiny ones), then per
+// cblk its TRSM row tiles, then per cblk its UPDATE tiles, then the INV items.
+// The update tiles of a pair (k, j) are 256 rows by 64 facing columns (thin:
+// 64 by 64); tiles entirely in the strict upper triangle of j's diagonal block
+// are not generated.  The tiles into the first facing cblk (the next block of
+// an elimination chain) come first and go to the high-priority queue, like
+// FACT and TRSM items.
 // rmap holds, per update pair, the row inside panel j of every panel row of
 // k from the first facing row on (checked against the target structure).
 void build_tasks(spx_handle* h)

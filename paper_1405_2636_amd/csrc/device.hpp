@@ -22,7 +22,7 @@ struct DevPlan {
 
 // Work-item kinds of the device scheduler (low byte of the first word; an
 // update keeps its merged piece count - 1 in bits 8..11; bit 12 marks a thin
-// TRSM or update item of an elimination chain: 16-row wave tiles).
+// TRSM item of an elimination chain or a thin update: 16-row wave tiles).
 enum ItemKind : int32_t { kFact = 0, kTrsm = 1, kUpdate = 2, kSmall = 3, kInv = 4, kTiny = 5 };
 constexpr int32_t kThinItem = 1 << 12;
 constexpr int32_t kSubstItem = 1 << 13;   // TRSM of a chain block: substitution with the diagonal tiles of D (16 rows)

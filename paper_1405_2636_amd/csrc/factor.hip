@@ -11,14 +11,16 @@
 // work items from device-side ready queues:
 //   FACT(k)          Cholesky of the diagonal block and its inverse L_kk^{-1}
 //   TRSM(k, rows)    64, 128 or 256 off-diagonal rows of panel k times
-//                    L_kk^{-T}
-//   UPDATE(k,j,r,c)  a 256x64 (or 128x128) tile of the outer product of panel
-//                    k, subtracted into panel j with atomics; for a group of
-//                    pieces of a split supernode, the sum of their products
+//                    L_kk^{-T}; chain blocks: 16 rows by block substitution
+//   INV(k)           the rest of L_kk^{-1} of a chain block, beside the chain
+//   UPDATE(k,j,r,c)  a 256x64 (or 128x128; 64x64 on levels with little work)
+//                    tile of the outer product of panel k, subtracted into
+//                    panel j with atomics; for a group of pieces of a split
+//                    supernode, the sum of their products
 //   SMALL(k)         a narrow column block (width <= 32, <= 128 rows): all
 //                    three steps and every update tile of the block at once
 //   TINY(k, ...)     the same for a group of blocks of width <= 16 with at most
-//                    32 rows, a wave each
+//                    64 rows, a wave each
 // Dependencies are counters: FACT(j) becomes ready when every UPDATE tile
 // into j is done, the TRSM tiles of k when FACT(k) is done, the UPDATE tiles
 // of k when its last TRSM tile is done.  FACT, TRSM and the updates into the
@@ -1139,7 +1141,7 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
 // a forward substitution against the finished row blocks above it,
 //   L_iJ = (A_iJ - sum_{K<J} L_iK L_JK^T) D_JJ^T,   J = 0 .. i-1,
 // then its diagonal tile A_ii - sum_K L_iK L_iK^T is factored and inverted
-// (tile_chol_inv).  Nothing is updated in memory: a block is read once,
+// (TileChol).  Nothing is updated in memory: a block is read once,
 // collected on the matrix cores and written once.  The waves run as a
 // pipeline without barriers: row block i takes L_J* as soon as row block J
 // has published it (s_x) and D_JJ as soon as tile J is factored (s_d), so a
@@ -1629,7 +1631,7 @@ __device__ __noinline__ void task_trsm_chain(const SchedArgs& a, Geo g, int row0
 // W_L = L_k[rows] U^T_k[cols]^T goes to j's L panel (its square diagonal
 // block included), and, for rows below j's diagonal block, W_U =
 // U^T_k[rows] L_k[cols]^T to j's U^T panel.
-// RB = 1: a thin tile of an elimination chain, at most 64 x 64, each wave
+// RB = 1: a thin tile (levels with little work), at most 64 x 64, each wave
 // 16 rows of it (a quarter of the work of a 64-row wave tile).
 template <class T, bool LDL = false, bool LU = false, int RB = 4>
 __device__ __noinline__ void task_update(const SchedArgs& a, const int4 d0, const int4 d1, const int4 d2, const int4 d3,
@@ -1755,7 +1757,7 @@ __device__ __forceinline__ void finish_update(const SchedArgs& a, int j)
 // ---------------------------------------------------------------- fused small block
 // A column block of width w <= 32 with at most 128 panel rows as one item:
 // the panel is read into LDS once; the diagonal block is factored and
-// inverted (tile_chol_inv); the rows below become A_off D^T; every update
+// inverted (TileChol); the rows below become A_off D^T; every update
 // tile of the block (fused-tile table) is formed from the LDS copy and
 // scattered with the atomics of the update items; then the item counts its
 // targets down.  Blocks at the bottom of the elimination

@@ -140,7 +140,6 @@ struct spx_handle {
     DevBuf<int32_t> rcol;
     DevBuf<int32_t> erow, ecol;   // row and column of every stored entry (-1: above the diagonal)
     DevBuf<int32_t> rowg;
-    DevBuf<int64_t> rowg_off;
     // scheduler tables
     int32_t total = 0, nready = 0, nready_hp = 0, hp_total = 0, total_normal = 0;
     int32_t nsmall = 0, nfused_tiles = 0;   // fused small blocks and their update tiles
@@ -955,7 +954,6 @@ void upload_plan(spx_handle* h)
     }
     rgo[P.ncblk] = static_cast<int64_t>(rg.size());
     h->rowg.upload(rg);
-    h->rowg_off.upload(rgo);
     {
         // coordinates of the entries read by the factorization, from the
         // symmetric row lists of the residual (each lower entry appears in
@@ -1004,7 +1002,6 @@ void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
         return;
     }
     SweepArgs a;
-    a.pl = h->devplan();
     a.panels = h->panel_ptr();
     a.dinv = h->dinv_ptr();
     {
@@ -1016,7 +1013,6 @@ void sweeps(spx_handle* h, const SweepBufs& w, int32_t nrhs, hipStream_t s)
     a.f32 = h->f32() ? 1 : 0;
     a.ldlt = h->ldlt() ? 1 : 0;
     a.rowg = h->rowg.p;
-    a.rowg_off = h->rowg_off.p;
     a.y = w.y;
     a.z = w.z;
     a.x = w.x;

@@ -91,7 +91,6 @@ struct SchedArgs {
 
 // Arguments of the triangular sweeps.
 struct SweepArgs {
-    DevPlan pl;
     const void* panels;       // double, or float in the FP32 refinement mode
     const void* dinv;
     const void* panels_b;     // backward sweep: L U's U^T panels and U_kk^{-T} (else the same as forward)
@@ -99,7 +98,6 @@ struct SweepArgs {
     int32_t f32;              // 1: panels and inverses are float
     int32_t ldlt;             // 1: L D L^T factor (D on the panel diagonals, inverses D^{-1} L^{-1})
     const int32_t* rowg;      // global row of every off-diagonal panel row
-    const int64_t* rowg_off;  // [ncblk] start of cblk k's rows in rowg
     double* y;                // permuted right-hand side, accumulates the forward updates (n x nrhs, ld n)
     double* z;                // forward sweep result L^{-1} P b
     double* x;                // backward sweep result L^{-T} z

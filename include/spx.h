@@ -102,7 +102,10 @@ typedef struct spx_options {
     int32_t tune;             /* 1: on the first factorization, time one run per work
                                * decomposition (update tile shape, priority policy) and
                                * keep the fastest (0: 256x64 tiles, every chain first) */
-    int32_t tile;             /* update tile shape without tuning: 0 = 256 x 64, 1 = 128 x 128 (0) */
+    int32_t tile;             /* update tile shape without tuning (0): 0 = 256 x 64, and 64 x 64
+                               * for the updates of levels with little work; 1 = 128 x 128 on
+                               * every level (both: 64 x 64 towards the next block of an
+                               * elimination chain) */
     int32_t fuse_small;       /* 1: a column block of width <= 32 with at most 128 panel rows
                                * (and at most 64 update tiles) is factored, solved and
                                * scattered as one work item (1) */
@@ -148,7 +151,8 @@ typedef struct spx_info {
     double factor_kernel_ms;  /* last factorization: scheduler kernel time (HIP events) */
     double assemble_ms;       /* last factorization: assembly kernel time */
     int32_t tile_rows;        /* update tile in use: 256 x 64 or 128 x 128 (levels with
-                               * little work take 64 x 64 in both) */
+                               * little work take 64 x 64 in both, unless tile = 1 was
+                               * asked for) */
     int32_t tile_cols;
     int32_t hp_policy;        /* 0: every elimination chain first; 1: only the upper levels */
     int32_t nsys;             /* independent systems of the handle (spx_analyze_batch), 1 otherwise */

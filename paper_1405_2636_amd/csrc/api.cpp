@@ -353,6 +353,8 @@ void build_tasks(spx_handle* h)
     // 1.92, 1.93, 1.91, 1.92; 72x70x69 18.4, -, 18.2, 18.0, 18.8; 100^3 86.0, -,
     // 85.5, 85.6, 87.1; FP32, whose tiles take half the time: 63x65x61 8.41,
     // 8.34, 8.41, 8.88, 8.80; 80^3 split BF16 15.9, 16.0, 16.3, 16.8, 20.4.
+    // A caller who asks for the 128 x 128 shape (tile = 1, no tuning) gets it
+    // on every level.
     constexpr double kFineTiles = 8192, kFineTiles32 = 1024;
     std::vector<double> tiles(static_cast<size_t>(nc) + 1, 0.0);   // thin tiles of a level's updates
     for (int32_t k = 0; k < nc; ++k) {
@@ -360,8 +362,9 @@ void build_tasks(spx_handle* h)
         tiles[lvl[k]] += r * r / (64.0 * 64.0) * (h->lu() ? 1.0 : 0.5);
     }
     std::vector<char> fine(nc, 0);
+    const bool any_shape = h->opt.tile == 0 || h->opt.tune;
     for (int32_t k = 0; k < nc; ++k)
-        fine[k] = tiles[lvl[k]] <= (h->f32() ? kFineTiles32 : kFineTiles) && P.lcol[k] - P.fcol[k] + 1 >= 32;
+        fine[k] = any_shape && tiles[lvl[k]] <= (h->f32() ? kFineTiles32 : kFineTiles) && P.lcol[k] - P.fcol[k] + 1 >= 32;
     // update tiles of source k into target group [b, b2) (blocks facing one
     // cblk), tr x tcl each
     auto for_tiles = [&](int32_t k, int32_t b, int32_t b2, int32_t tr, int32_t tcl, auto&& fn) {

@@ -1,6 +1,7 @@
-"""Update tiles larger than 64 x 64 (64-row wave tiles) with inner
+"""Update tiles larger than 64 x 64 (128 x 128 and 256 x 64) with inner
 dimensions of 32 and more, of single and of merged pieces, in every method
-and storage precision: 128 x 128 asked for (tile = 1: every level takes it).
+and storage precision: 128 x 128 asked for (tile = 1: every level takes it),
+and 256 x 64 on levels with too much work for 64 x 64 tiles.
 
 Matrices: arrows, A = L0 U0 (L0 L0^T, L0 D0 L0^T), with leaves of w dense
 columns, uncoupled to each other, and a dense root of r.  L0's and U0^T's
@@ -150,3 +151,24 @@ def test_asked_for(method, precision, opts):
         s, _, k, wide = _factor(torch, a, method, precision, tile=1, split_width=split, **opts)
         assert wide.any()
         assert a.error(torch, s, precision) <= 1.0
+
+
+# (leaves, columns of a leaf, root): more than 8192 tiles of 64 x 64 (FP32: 1024) on the leaves' two levels
+@pytest.mark.parametrize("method,precision,leaves,w,r,two_per_cu", [
+    ("llt", "fp64", 40, 512, 1300, True), ("ldlt", "fp64", 40, 300, 1310, False), ("lu", "fp64", 20, 300, 1310, False),
+    ("llt", "fp32_ir", 12, 300, 933, False), ("llt", "bf16x3_ir", 12, 300, 933, False),
+    ("ldlt", "fp32_ir", 12, 300, 933, False), ("ldlt", "bf16x3_ir", 12, 300, 933, False),
+    ("lu", "fp32_ir", 12, 300, 933, False)])
+def test_default_shape(method, precision, leaves, w, r, two_per_cu):
+    """256 x 64 on levels with many tiles, merged pieces among them; work
+    enough for two workers on a CU in the first case."""
+    import torch
+    a = Arrow(torch, leaves, w, r, method, r)
+    s, t, k, wide = _factor(torch, a, method, precision)
+    assert k[wide, 3].max() == 256 * 64
+    if two_per_cu:   # items in work at once
+        at = np.concatenate([t[:, 1], t[:, 2]])
+        step = np.concatenate([np.ones(len(t), int), -np.ones(len(t), int)])
+        order = np.lexsort((step, at))
+        assert np.cumsum(step[order]).max() > torch.cuda.get_device_properties(0).multi_processor_count
+    assert a.error(torch, s, precision) <= 1.0

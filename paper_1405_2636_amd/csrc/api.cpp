@@ -418,36 +418,6 @@ void build_tasks(spx_handle* h)
         for (int32_t k = 0; k < nc; ++k)
             if (P.stride[k] > 32 && ntall[lvl[k]] < kTinyItems) tiny[k] = 0;
     }
-    // Workers: one per CU where the elimination chain is longer than the work.
-    // A second workgroup on a CU hides the latency of the other and nearly
-    // doubles the rate of the products, but an item of the chain beside a long
-    // update takes up to twice its time.  The chain: the longest path of
-    // factorizations (0.28 us a column, L U 0.55) and links to the next block
-    // (panel solve, update, two queue passes: 50 us); the work: products at
-    // 52 TFLOP/s (FP32 105) and the small blocks over 512 workers.  Scheduler
-    // kernel, ms, with two and one workers per CU, and work / chain: 64^2 0.273,
-    // 0.251 (0.01); 36x35x34 1.93, 1.73 (0.09); 41x37x43 2.68, 2.33 (0.14);
-    // elasticity 18x20x19 4.0, 3.39 (0.20); 48^3 4.47, 4.03 (0.28); 701x503 1.90,
-    // 1.90 (0.27); 50x47x49 L U 9.4, 8.35 (0.39); 63x65x61 FP32 8.4, 7.7 (0.43);
-    // 80^3 split BF16 16.0, 17.4 (1.2); 72x70x69 18.0, 19.1 (1.4); 256 grids 1.49,
-    // 2.3 (2.3); 100^3 86, 106 (6.3).  (Two with the second one of a CU
-    // working behind a backlog only: no better than two.)
-    {
-        constexpr double kChainLonger = 0.75;
-        const double col = h->lu() ? 0.55 : 0.28, rate = h->f32() ? 105e6 : 52e6;   // us, FLOP / us
-        std::vector<double> at(nc, 0.0);
-        double chain_us = 0.0, work_us = 0.0;
-        for (int32_t k = 0; k < nc; ++k) {
-            const double w = P.lcol[k] - P.fcol[k] + 1, r = P.stride[k] - w;
-            at[k] += small[k] ? 25.0 : 10.0 + col * w;
-            chain_us = std::max(chain_us, at[k]);
-            for (int32_t q = P.uptr[k]; q < P.uptr[k + 1]; ++q)
-                at[P.utgt[q]] = std::max(at[P.utgt[q]], at[k] + (small[k] ? 0.0 : 50.0));
-            work_us += (w * w * w / 3.0 + w * w * r + w * r * r) * (h->lu() ? 2.0 : 1.0) / rate;
-            if (small[k]) work_us += (P.lcol[k] - P.fcol[k] + 1 <= kTinyW && P.stride[k] <= kTinyRows ? 4.0 : 25.0) / 512.0;
-        }
-        h->one_per_cu = work_us < kChainLonger * chain_us;
-    }
     std::vector<int32_t> item(nc, -1), group;   // group: blocks of the tiny items, item by item
     std::vector<int32_t> gptr{0}, first_of;      // their ends; first block of every factoring item
     {
@@ -661,6 +631,43 @@ void build_tasks(spx_handle* h)
         desc[4 * static_cast<size_t>(item[k]) + 1] = int4{tf[k], tc[k], inv_item[k], hp[k]};
         for (int32_t i = 0; i < tc[k]; ++i)
             desc[4 * static_cast<size_t>(tf[k] + i) + 1] = int4{uf[k], uh[k], ucnt[k], 0};
+    }
+    // Workers: one per CU where the elimination chain is longer than the work.
+    // A second workgroup on a CU hides the latency of the other and nearly
+    // doubles the rate of the products, but an item of the chain beside a long
+    // update takes up to twice its time.  The chain: the longest path of
+    // factorizations (0.28 us a column, L U 0.55) and links to the next block
+    // (panel solve, update, two queue passes: 50 us); the work: products at
+    // 52 TFLOP/s (FP32 105) and the small blocks over 512 workers.  Scheduler
+    // kernel, ms, with two and one workers per CU, and work / chain: 64^2 0.273,
+    // 0.251 (0.01); 36x35x34 1.93, 1.73 (0.09); 41x37x43 2.68, 2.33 (0.14);
+    // elasticity 18x20x19 4.0, 3.39 (0.20); 48^3 4.47, 4.03 (0.28); 701x503 1.90,
+    // 1.90 (0.27); 50x47x49 L U 9.4, 8.35 (0.39); 63x65x61 FP32 8.4, 7.7 (0.43);
+    // 80^3 split BF16 16.0, 17.4 (1.2); 72x70x69 18.0, 19.1 (1.4); 256 grids 1.49,
+    // 2.3 (2.3); 100^3 86, 106 (6.3).  (Two with the second one of a CU
+    // working behind a backlog only: no better than two.)
+    // Small blocks of L U, which are never fused, add 12 us an item: 9 to 11 in
+    // work, 2 or 3 in the queues.  L U, two and one: 256 grids of side 16 to 96
+    // 39.3, 43.1 (15); 2000 of side 4 to 24 21.3, 22.6 (9.9); 600x590 13.7, 14.6
+    // (2.3); 300x300 4.32, 4.65 (0.88); 100x100 1.00, 1.00 (0.16).  (L L^T without
+    // fusing: 6 to 8 us an item, which one worker per CU takes as fast as the
+    // queues give them out, 25 a us: 33.0, 33.8 and 18.9, 18.1.)
+    {
+        constexpr double kChainLonger = 0.75;
+        const double col = h->lu() ? 0.55 : 0.28, rate = h->f32() ? 105e6 : 52e6;   // us, FLOP / us
+        std::vector<double> at(nc, 0.0);
+        double chain_us = 0.0, work_us = 0.0;
+        for (int32_t k = 0; k < nc; ++k) {
+            const double w = P.lcol[k] - P.fcol[k] + 1, r = P.stride[k] - w;
+            at[k] += small[k] ? 25.0 : 10.0 + col * w;
+            chain_us = std::max(chain_us, at[k]);
+            for (int32_t q = P.uptr[k]; q < P.uptr[k + 1]; ++q)
+                at[P.utgt[q]] = std::max(at[P.utgt[q]], at[k] + (small[k] ? 0.0 : 50.0));
+            work_us += (w * w * w / 3.0 + w * w * r + w * r * r) * (h->lu() ? 2.0 : 1.0) / rate;
+            if (small[k]) work_us += (P.lcol[k] - P.fcol[k] + 1 <= kTinyW && P.stride[k] <= kTinyRows ? 4.0 : 25.0) / 512.0;
+            else if (h->lu() && w <= kNB && P.stride[k] <= kSmallRows) work_us += 12.0 * (1 + tc[k] + ucnt[k]) / 512.0;
+        }
+        h->one_per_cu = work_us < kChainLonger * chain_us;
     }
     h->total = id;
     h->npair = static_cast<int32_t>(pairs.size());

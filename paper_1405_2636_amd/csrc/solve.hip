@@ -435,12 +435,16 @@ __global__ void __launch_bounds__(256) bwd_diag(SweepArgs a, const DiagItem* ite
 // lanes for every block, four or eight columns per round trip); 48^3 with 13
 // right-hand sides, 3 levels: 358 -> 48 and 506 -> 58 us (the blocks of
 // right-hand sides were a loop of two at a time inside the kernels).
+// Lanes without a block leave at once: a chain has one block per level, and
+// the other lanes repeating its loads made a level of it 2.8 us instead of
+// 2.2 (band of 3 in natural order, 1558 levels, one right-hand side 8.78 ->
+// 6.91 ms, two 12.28 -> 9.85).
 constexpr int kSG = 16;                    // lanes per tiny block
 constexpr int kSGroups = 256 / kSG;        // tiny blocks per workgroup
 
 // forward, tiny block: z_k = D y_k, then y[g(r)] -= L[r, :] z_k
 template <class T, int NR>
-__device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it, bool on, int rb)
+__device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it, int rb)
 {
     const int l = threadIdx.x % kSG, w = it.w(), ld = it.ld(), f = it.f;
     const T* D = static_cast<const T*>(a.dinv) + it.dofs;
@@ -469,7 +473,7 @@ __device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it
         z[j] = 0.0;
 #pragma unroll
         for (int p = 0; p < 8; ++p) z[j] += (p <= lw ? (double)d[p] : 0.0) * __shfl(y[j], p, kSG);
-        if (on && l < w && j < nv) a.z[(int64_t)(rb + j) * a.n + f + l] = z[j];
+        if (l < w && j < nv) a.z[(int64_t)(rb + j) * a.n + f + l] = z[j];
         z[j] *= s;
         double v[2] = {0.0, 0.0};
 #pragma unroll
@@ -480,14 +484,14 @@ __device__ __forceinline__ void fwd_tiny(const SweepArgs& a, const SmallItem& it
         }
 #pragma unroll
         for (int i = 0; i < 2; ++i)
-            if (on && w + l + kSG * i < ld && j < nv) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + g[i], -v[i]);
+            if (w + l + kSG * i < ld && j < nv) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + g[i], -v[i]);
     }
 }
 
 // forward, a wave: lane = row and half of the columns of D, then lane = row
 // below (two of them)
 template <class T, int NR>
-__device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it, bool on, int rb, double* ys,
+__device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it, int rb, double* ys,
                                          double* zs)
 {
     const int lane = threadIdx.x & 63, w = it.w(), ld = it.ld(), f = it.f, R = ld - w;
@@ -534,7 +538,7 @@ __device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it
     for (int j = 0; j < NR; ++j) {
         z[j] += __shfl_xor(z[j], 32);
         if (half == 0) zs[r * NR + j] = r < w ? z[j] * s : 0.0;
-        if (on && half == 0 && r < w && j < nv) a.z[(int64_t)(rb + j) * a.n + f + r] = z[j];
+        if (half == 0 && r < w && j < nv) a.z[(int64_t)(rb + j) * a.n + f + r] = z[j];
     }
     __atomic_signal_fence(__ATOMIC_SEQ_CST);
     if (R <= 0) return;
@@ -565,7 +569,7 @@ __device__ __forceinline__ void fwd_wave(const SweepArgs& a, const SmallItem& it
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
-        if (on && lane + 64 * i < R)
+        if (lane + 64 * i < R)
             for (int j = 0; j < nv; ++j) unsafeAtomicAdd(a.y + (int64_t)(rb + j) * a.n + g[i], -v[i][j]);
 }
 
@@ -578,12 +582,14 @@ __device__ __forceinline__ void fwd_small_step(const SweepArgs& a, const SmallIt
     const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
     if (b < nt) {
         const int idx = b * kSGroups + tid / kSG;
-        const SmallItem it = items[min(idx, ntiny - 1)];
-        fwd_tiny<T, NR> (a, it, idx < ntiny, rb);
+        if (idx >= ntiny) return;
+        const SmallItem it = items[idx];
+        fwd_tiny<T, NR>(a, it, rb);
     } else {
         const int wave = tid >> 6, idx = ntiny + (b - nt) * 4 + wave;
-        const SmallItem it = items[min(idx, count - 1)];
-        fwd_wave<T, NR> (a, it, idx < count, rb, sm + wave * 64 * NR, sm + wave * 64 * NR + 32 * NR);
+        if (idx >= count) return;
+        const SmallItem it = items[idx];
+        fwd_wave<T, NR>(a, it, rb, sm + wave * 64 * NR, sm + wave * 64 * NR + 32 * NR);
     }
 }
 template <class T, int NR>
@@ -595,7 +601,7 @@ __global__ void __launch_bounds__(256) fwd_small(SweepArgs a, const SmallItem* i
 
 // backward, tiny block: t = L_off^T x[g(rows below)], x_k = D^T (z_k - t)
 template <class T, int NR>
-__device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it, bool on, int rb)
+__device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it, int rb)
 {
     const int l = threadIdx.x % kSG, w = it.w(), ld = it.ld(), f = it.f;
     const T* D = static_cast<const T*>(a.dinv_b) + it.dofs;
@@ -652,14 +658,14 @@ __device__ __forceinline__ void bwd_tiny(const SweepArgs& a, const SmallItem& it
             const double up = __shfl(u, 2 * p, kSG);
             v += (p >= l && p < w ? (double)d[p] : 0.0) * (p < w ? up : 0.0);
         }
-        if (on && l < w && j < nv) a.x[(int64_t)(rb + j) * a.n + f + l] = v;
+        if (l < w && j < nv) a.x[(int64_t)(rb + j) * a.n + f + l] = v;
     }
 }
 
 // backward, a wave: lane = column and half of the rows below, then of the
 // rows of D
 template <class T, int NR>
-__device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it, bool on, int rb, double* xs,
+__device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it, int rb, double* xs,
                                          double* us)
 {
     const int lane = threadIdx.x & 63, w = it.w(), ld = it.ld(), f = it.f, R = ld - w;
@@ -730,7 +736,7 @@ __device__ __forceinline__ void bwd_wave(const SweepArgs& a, const SmallItem& it
 #pragma unroll
     for (int j = 0; j < NR; ++j) {
         v[j] += __shfl_xor(v[j], 32);
-        if (on && half == 0 && c < w && j < nv) a.x[(int64_t)(rb + j) * a.n + f + c] = v[j];
+        if (half == 0 && c < w && j < nv) a.x[(int64_t)(rb + j) * a.n + f + c] = v[j];
     }
 }
 
@@ -742,12 +748,14 @@ __device__ __forceinline__ void bwd_small_step(const SweepArgs& a, const SmallIt
     const int nt = (ntiny + kSGroups - 1) / kSGroups, tid = threadIdx.x;
     if (b < nt) {
         const int idx = b * kSGroups + tid / kSG;
-        const SmallItem it = items[min(idx, ntiny - 1)];
-        bwd_tiny<T, NR> (a, it, idx < ntiny, rb);
+        if (idx >= ntiny) return;
+        const SmallItem it = items[idx];
+        bwd_tiny<T, NR>(a, it, rb);
     } else {
         const int wave = tid >> 6, idx = ntiny + (b - nt) * 4 + wave;
-        const SmallItem it = items[min(idx, count - 1)];
-        bwd_wave<T, NR> (a, it, idx < count, rb, sm + wave * 160 * NR, sm + wave * 160 * NR + 128 * NR);
+        if (idx >= count) return;
+        const SmallItem it = items[idx];
+        bwd_wave<T, NR>(a, it, rb, sm + wave * 160 * NR, sm + wave * 160 * NR + 128 * NR);
     }
 }
 template <class T, int NR>

@@ -850,17 +850,19 @@ __device__ __forceinline__ unsigned long long block_max(unsigned long long v)
 // stats[0] = max_i |r_i| / (|A||x| + |b|)_i   (0/0 = 0, p/0 = inf)
 // stats[1] = max |r_i|, stats[2] = max |x_i|, stats[3] = max |b_i|, stats[4] = max_i sum_j |a_ij|
 // (stats[q] at word q * kStatStride: every block adds its maxima by atomics,
-// one cache line per statistic; a fixed grid of kResidualBlocks blocks)
+// one cache line per statistic)
 // A thread takes a row and NR right-hand sides at a time (grid rows): its
 // entries are read once for all of them, kRU entries and their x at a time
-// (bound by the round trips to memory).
+// (bound by the round trips to memory; four entries at a time took dense rows
+// of 1500 and four right-hand sides 761 us, longer than a thread per row and
+// right-hand side, 684; eight: solve 867 -> 684 us).
 template <int NR>
 __global__ void __launch_bounds__(256) residual_kernel(const int64_t* rptr, const int32_t* rcol, const double* rv,
                                                        const double* x, const double* b,
                                                        int64_t ldb, double* r, int32_t n, int32_t nrhs,
                                                        unsigned long long* stats)
 {
-    constexpr int kRU = NR == 1 ? 8 : 4;
+    constexpr int kRU = 8;
     unsigned long long m0 = 0, m1 = 0, m2 = 0, m3 = 0, m4 = 0;
     auto up = [](unsigned long long& m, double v) {
         const unsigned long long k = key_of(v);

@@ -22,7 +22,6 @@ namespace spx {
 
 hipError_t launch_fill_f64(double* p, int64_t n, double v, hipStream_t s);
 hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t s);
-hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s);
 hipError_t launch_assemble(void* panels, bool f32, const int64_t* amap, const double* values, int64_t nnz,
                            hipStream_t s);
 hipError_t launch_widen(double* dst, const float* src, int64_t n, hipStream_t s);
@@ -32,7 +31,7 @@ hipError_t launch_sched_init(const SchedArgs& a, const int32_t* ready, int32_t n
 int sched_blocks_per_cu(bool f32, bool ldlt, bool lu);
 hipError_t launch_sched(const SchedArgs& a, bool f32, bool lu, int grid, hipStream_t s);
 hipError_t launch_update_bench(const SchedArgs& a, bool f32, bool ldl, const int4* tiles, int ntiles, int mbase,
-                               int copies, hipStream_t s);
+                               int4 tgt, int4 src, int copies, hipStream_t s);
 hipError_t launch_fwd_level(const SweepArgs& a, const DiagItem* ditems, int nd, int lanes, const SmallItem* items,
                             int count, int ntiny, hipStream_t s);
 hipError_t launch_bwd_level(const SweepArgs& a, const DiagItem* ditems, int nd, int lanes, const SmallItem* items,
@@ -133,8 +132,7 @@ struct spx_handle {
     int32_t n = 0;
     int64_t nnz = 0;
     // device plan
-    DevBuf<int32_t> fcol, lcol, stride, bptr, frow, lrow, coefind, perm;
-    DevBuf<int64_t> panel_off, dinv_off;
+    DevBuf<int32_t> fcol, lcol, perm;
     DevBuf<int64_t> diag_off;   // panel offset of the diagonal entry of every column
     DevBuf<int64_t> amap, rptr, rval;
     DevBuf<int32_t> rcol;
@@ -234,22 +232,6 @@ struct spx_handle {
     int64_t dinv_count() const { return dinv_size * (lu() ? 2 : 1); }
     void* panel_ptr() { return f32() ? static_cast<void*>(panels_f.p) : static_cast<void*>(panels.p); }
     void* dinv_ptr() { return f32() ? static_cast<void*>(dinv_f.p) : static_cast<void*>(dinv.p); }
-
-    DevPlan devplan() const
-    {
-        DevPlan d;
-        d.ncblk = plan.ncblk;
-        d.fcol = fcol.p;
-        d.lcol = lcol.p;
-        d.stride = stride.p;
-        d.panel_off = panel_off.p;
-        d.bptr = bptr.p;
-        d.frow = frow.p;
-        d.lrow = lrow.p;
-        d.coefind = coefind.p;
-        d.dinv_off = dinv_off.p;
-        return d;
-    }
 };
 
 namespace {
@@ -929,20 +911,13 @@ void upload_plan(spx_handle* h)
     HIPCHK(hipGetDevice(&h->device));
     h->fcol.upload(P.fcol);
     h->lcol.upload(P.lcol);
-    h->stride.upload(P.stride);
-    h->bptr.upload(P.bptr);
-    h->frow.upload(P.frow);
-    h->lrow.upload(P.lrow);
-    h->coefind.upload(P.coefind);
     h->perm.upload(P.perm);
-    h->panel_off.upload(P.panel_off);
     std::vector<int64_t> doff(static_cast<size_t>(P.ncblk) + 1, 0);
     for (int32_t k = 0; k < P.ncblk; ++k) {
         const int64_t w = P.lcol[k] - P.fcol[k] + 1;
         doff[k + 1] = doff[k] + w * w;
     }
     h->dinv_size = doff[P.ncblk];
-    h->dinv_off.upload(doff);
     {
         std::vector<int64_t> dg(static_cast<size_t>(P.n));
         for (int32_t k = 0; k < P.ncblk; ++k)
@@ -1078,7 +1053,7 @@ void factor_part(spx_handle* h, int part, hipStream_t s)
 SchedArgs sched_args(spx_handle* h)
 {
     SchedArgs a;
-    a.pl = h->devplan();
+    a.pl = DevPlan{h->fcol.p, h->lcol.p};
     a.panels = h->panel_ptr();
     a.dinv = h->dinv_ptr();
     a.split = h->opt.precision == SPX_BF16X3_IR ? 1 : 0;
@@ -1429,7 +1404,6 @@ int spx_solve(spx_handle* h, int32_t nrhs, double* b, int64_t ldb, int32_t b_on_
         if (nrhs == 0 || h->n == 0) return SPX_OK;
         hipStream_t s = static_cast<hipStream_t>(hip_stream);
         const int32_t n = h->n;
-        const size_t tot = static_cast<size_t>(n) * nrhs;
         if (nrhs > h->nrhs_cap) {
             // new buffers: a graph captured on the old ones is stale
             h->drop_graph();
@@ -1717,25 +1691,16 @@ int spx_update_bench(int32_t precision, int32_t method, int32_t n_inner, int32_t
                 if (r0 + mr - 1 < c0) continue;   // strictly above the target's diagonal
                 tiles.push_back(int4{r0, mr, c0, std::min(tc, n_inner + k - c0)});
             }
-        DevBuf<int32_t> fcol, lcol, stride;
-        DevBuf<int64_t> poff;
         DevBuf<int4> dt;
-        fcol.upload(std::vector<int32_t>{0, n_inner});
-        lcol.upload(std::vector<int32_t>{n_inner - 1, n_inner + k - 1});
-        stride.upload(std::vector<int32_t>{n_inner + m, ldc});
-        poff.upload(std::vector<int64_t>{0, static_cast<int64_t>(n_inner + m) * n_inner});
         dt.upload(tiles);
         SchedArgs a{};
-        a.pl.ncblk = 2;
-        a.pl.fcol = fcol.p;
-        a.pl.lcol = lcol.p;
-        a.pl.stride = stride.p;
-        a.pl.panel_off = poff.p;
         a.panels = panels;
         a.rmap = rmap;
         a.split = precision == SPX_BF16X3_IR ? 1 : 0;
         a.ldlt = method == SPX_LDLT ? 1 : 0;
         const int nt = static_cast<int>(tiles.size());
+        const int64_t po = static_cast<int64_t>(n_inner + m) * n_inner;   // the target panel
+        const int4 tgt{1, ldc, static_cast<int32_t>(po), 0}, src{n_inner, n_inner + m, 0, 0};
         const int ns = std::max(1, nstreams);
         for (int i = 0; i < ns; ++i) {
             hipStream_t q;
@@ -1751,10 +1716,10 @@ int spx_update_bench(int32_t precision, int32_t method, int32_t n_inner, int32_t
         HIPCHK(hipEventRecord(ev[0], st[0]));
         for (int i = 1; i < ns; ++i) HIPCHK(hipStreamWaitEvent(st[i], ev[0], 0));
         if (nstreams == 0) {   // all calls as one grid
-            HIPCHK(launch_update_bench(a, f32, method == SPX_LDLT, dt.p, nt, -n_inner, calls, st[0]));
+            HIPCHK(launch_update_bench(a, f32, method == SPX_LDLT, dt.p, nt, -n_inner, tgt, src, calls, st[0]));
         } else {               // one grid per call, round-robin over the streams
             for (int c = 0; c < calls; ++c)
-                HIPCHK(launch_update_bench(a, f32, method == SPX_LDLT, dt.p, nt, -n_inner, 1, st[c % ns]));
+                HIPCHK(launch_update_bench(a, f32, method == SPX_LDLT, dt.p, nt, -n_inner, tgt, src, 1, st[c % ns]));
         }
         for (int i = 1; i < ns; ++i) {
             HIPCHK(hipEventRecord(ev[2 + i], st[i]));

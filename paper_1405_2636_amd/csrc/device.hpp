@@ -6,18 +6,11 @@
 
 namespace spx {
 
-// Column-block geometry on the device (all arrays indexed by cblk or block).
+// First and last column of every column block, on the device (everything
+// else of the geometry is in the work items).
 struct DevPlan {
-    int32_t ncblk;
     const int32_t* fcol;
     const int32_t* lcol;
-    const int32_t* stride;
-    const int64_t* panel_off;
-    const int32_t* bptr;
-    const int32_t* frow;
-    const int32_t* lrow;
-    const int32_t* coefind;
-    const int64_t* dinv_off;   // offset of the inverted diagonal tiles of each cblk
 };
 
 // Work-item kinds of the device scheduler (low byte of the first word; an
@@ -174,7 +167,6 @@ constexpr int kResidualBlocks = 1024;
 constexpr size_t kScratchBytes = size_t(64) << 20;
 
 constexpr int kThreads = 256;   // 4 waves of 64
-constexpr int kTile = 64;       // rows/cols of update, triangular-solve tiles
 constexpr int kNB = 32;         // diagonal tile (inverted explicitly)
 
 }  // namespace spx

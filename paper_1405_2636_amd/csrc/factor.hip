@@ -496,14 +496,6 @@ __device__ __forceinline__ double* ldl_pivots()
 }
 
 // ---------------------------------------------------------------- FACT(k)
-// 1/d from the hardware estimate and two Newton-Raphson steps
-__device__ __forceinline__ double recip_nr(double d)
-{
-    double y = __builtin_amdgcn_rcp(d);
-    y = y * __builtin_fma(-d, y, 2.0);
-    return y * __builtin_fma(-d, y, 2.0);
-}
-
 // The static pivoting threshold eps * max |a_ij| (0: off) sits in LDS after
 // the 64-entry broadcast buffer bc and the 32-entry pivot buffer of the
 // fused small items, written once by each worker at its start: a global
@@ -2247,36 +2239,28 @@ __global__ void __launch_bounds__(kThreads, 2) sched_kernel(SchedArgs a)
 // mbase).  Several calls of the grid, or one grid of several calls, measure
 // the update kernel alone (the paper's update-kernel study).
 template <class T, bool LDL>
-__global__ void __launch_bounds__(kThreads, 2) update_bench_kernel(SchedArgs a, const int4* tiles, int ntiles, int mbase)
+__global__ void __launch_bounds__(kThreads, 2) update_bench_kernel(SchedArgs a, const int4* tiles, int ntiles, int mbase,
+                                                                  int4 tgt, int4 src)
 {
     __shared__ int rpos[256], cpos[128];
     const int4 t = tiles[blockIdx.x % ntiles];
-    const DevPlan& pl = a.pl;
-    const int64_t po = pl.panel_off[1];
-    task_update<T, LDL, false>(a, int4{kUpdate, 0, 1, t.x}, int4{t.y, t.z, t.w, mbase},
-                               int4{1, pl.stride[1], (int)(po & 0xffffffff), (int)(po >> 32)},
-                               int4{pl.lcol[0] - pl.fcol[0] + 1, pl.stride[0], 0, 0}, rpos, cpos);
+    task_update<T, LDL, false>(a, int4{kUpdate, 0, 1, t.x}, int4{t.y, t.z, t.w, mbase}, tgt, src, rpos, cpos);
 }
 
 hipError_t launch_update_bench(const SchedArgs& a, bool f32, bool ldl, const int4* tiles, int ntiles, int mbase,
-                               int copies, hipStream_t s)
+                               int4 tgt, int4 src, int copies, hipStream_t s)
 {
     const int grid = ntiles * copies;
-    if (f32 && ldl) update_bench_kernel<float, true><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase);
-    else if (f32) update_bench_kernel<float, false><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase);
-    else if (ldl) update_bench_kernel<double, true><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase);
-    else update_bench_kernel<double, false><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase);
+    if (f32 && ldl) update_bench_kernel<float, true><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase, tgt, src);
+    else if (f32) update_bench_kernel<float, false><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase, tgt, src);
+    else if (ldl) update_bench_kernel<double, true><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase, tgt, src);
+    else update_bench_kernel<double, false><<<grid, kThreads, 0, s>>>(a, tiles, ntiles, mbase, tgt, src);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------- set-up kernels
 template <class T>
 __global__ void fill_kernel(T* p, int64_t n, T v)
-{
-    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
-}
-
-__global__ void fill_i32(int32_t* p, int64_t n, int32_t v)
 {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) p[i] = v;
 }
@@ -2370,14 +2354,6 @@ hipError_t launch_fill_f32(float* p, int64_t n, float v, hipStream_t s)
     if (n <= 0) return hipSuccess;
     const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
     fill_kernel<float><<<blocks, 256, 0, s>>>(p, n, v);
-    return hipGetLastError();
-}
-
-hipError_t launch_fill_i32(int32_t* p, int64_t n, int32_t v, hipStream_t s)
-{
-    if (n <= 0) return hipSuccess;
-    const int blocks = (int)std::min<int64_t>((n + 255) / 256, 8192);
-    fill_i32<<<blocks, 256, 0, s>>>(p, n, v);
     return hipGetLastError();
 }
 

@@ -307,8 +307,8 @@ void build_tasks(spx_handle* h)
     // an INV item in the normal queue forms the rest of the inverse (needed
     // by the triangular sweeps only): the chain runs through none of the
     // inverse's products.  A level is narrow if it has at most kInvLevel
-    // blocks and its solves fit two rounds of the workgroups that run at
-    // once: more of them wait for each other, and the product with the whole
+    // blocks and its solves fit two rounds of two workgroups per CU, four of
+    // one: more of them wait for each other, and the product with the whole
     // inverse is the shorter way.  Scheduler kernel with at most 128, 256,
     // 512, 1024 solves: 100^3 90.1, 89.6, 89.5, 89.5 ms (92.1 without the
     // limit), 50x47x49 L U 12.4, 12.0, 12.0, 11.4, 72x70x69 19.6, 19.3, 19.3,
@@ -781,7 +781,7 @@ void build_levels(spx_handle* h, const std::vector<int64_t>& doff, const std::ve
         if (unit[k] == k) ++L.cptr[lvl[k] + 1];
     for (int32_t l = 0; l < nl; ++l) L.cptr[l + 1] += L.cptr[l];
     L.cblk.resize(L.cptr[nl]);
-    // small blocks (one 16-lane group each in the sweeps) first in their level
+    // small blocks (16 lanes or a wave each in the sweeps) first in their level
     L.nsmall.assign(nl, 0);
     std::vector<int32_t> pos(L.cptr.begin(), L.cptr.end() - 1);
     for (int32_t k = 0; k < nc; ++k)

@@ -158,9 +158,9 @@ constexpr int kSmallMap = 2048;
 // kTinyTiles update tiles and kTinyMap row-map entries, as groups
 constexpr int kTinyW = 16, kTinyRows = 64, kTinyTiles = 16, kTinyMap = 512;
 
-// Residual statistics: one 256-byte line per statistic (five of them),
-// filled by a fixed grid of blocks.
+// Residual statistics: one 256-byte line per statistic (five of them).
 constexpr int kStatStride = 32;   // u64 words between statistics
+// The residual's blocks, over all of its grid rows (64 per row at least)
 constexpr int kResidualBlocks = 1024;
 
 // Fixed work memory of the allocation-free solve, per device (bytes).

@@ -159,7 +159,7 @@ __device__ __forceinline__ void gstore_s(const GOp& g, int voff, int soff, float
 }
 
 // One wave accumulates a 64 x (16*NB) tile: acc += X Y^T, X(r, p) r < 64,
-// Y(c, p) c < 16*NB, p < K (K rounded up to 8 reads zeros or is exact).  The
+// Y(c, p) c < 16*NB, p < K (K rounded up to 4 reads zeros or is exact).  The
 // whole tile is always computed (no per-block predicates); rows and columns
 // beyond the caller's bounds produce results that are not stored.
 // Y feeds operand A and X operand B (lane layout in MM), so
@@ -505,8 +505,8 @@ constexpr int kThrSlot = 3 * kNB;   // offset from bc
 
 // acc[i] += m * (lane i's value of b within each row of 16 lanes), i = I0 ..
 // I0 + N - 1: FP64 multiply-adds that take one operand from a fixed lane
-// (DPP row_newbcast; 4.5 cycles each, measured, where a readlane pair and
-// a multiply-add took 23 and a broadcast read of LDS 10 plus the
+// (DPP row_newbcast; 4.5 cycles each in a row of their own, where a readlane
+// pair and a multiply-add took 23 and a broadcast read of LDS 10 plus the
 // multiply-add).  b comes from LDS, not from a vector instruction; the
 // s_nop keeps the distance a DPP read needs even if a register copy
 // precedes it.
@@ -542,16 +542,19 @@ __device__ __forceinline__ void fmac_rows(double (&acc)[NV], int at, double b, d
 // diagonal), of lane 32 + q it is x_cq (zero for q > c), columns 0 .. jb - 1;
 // NC (8, 16 or 32, >= jb) bounds them.
 //
-// What bounds it is the chain from one pivot to the next, 94 cycles a column
-// (readlane, multiply-add, readlane, estimate, one third-order step,
-// scaling), and the issue of the multiply-adds.  The next column is updated
-// by a readlane of l_{c+1,c}, so that its pivot does not wait for the LDS
-// round trip of the others, and the updates of the columns after it are put,
-// four at a time, into the gaps of the next column's chain (column() below
-// is in the order of issue, held by scheduling barriers: the compiler puts
-// them behind the chain).  A tile alone on the chip takes 10,300 cycles,
-// 12,000 with the updates behind the chain; a form that read l_ic from LDS
-// for every update and branched around each load of Lt took 38,400.
+// What bounds it is the chain from one pivot to the next (readlane,
+// multiply-add, readlane, estimate, one third-order step, scaling) and the
+// issue of the multiply-adds: about 145 cycles a column and 8.4 a
+// multiply-add (8, 16, 24 and 32 columns of the pass take 2980, 5500, 7470
+// and 8750).  The next column is updated by a readlane of l_{c+1,c}, so that
+// its pivot does not wait for the LDS round trip of the others, and the
+// updates of the columns after it are put, four at a time, into the gaps of
+// the next column's chain (column() below is in the order of issue, held by
+// scheduling barriers: the compiler puts them behind the chain).  A tile alone
+// on the chip, its loads from LDS and the inverse's stores included, takes
+// 10,000 cycles, 4.2 us (L D L^T 10,430), the first time 11,200; 12,000 with
+// the updates behind the chain; a form that read l_ic from LDS for every
+// update and branched around each load of Lt took 38,400.
 //
 // LDL = true: the L D L^T form of the same pass (unit L): the pivot d is
 // not square-rooted (a breakdown is a zero or non-finite d), a row keeps the
@@ -746,8 +749,9 @@ struct TileChol {
 // reads them.  Out: out(c, lane, x, z) with x = l_rc (rows r > c) or u_cq
 // (columns q >= c) and z = X(c, r) or Y(c, q), columns 0 .. jb - 1 rounded up
 // to a multiple of 8.  Static pivoting and breakdown as in L D L^T.
-// Bound: the multiply-adds (992 of 4.5 cycles) beside the chain of pivots
-// (about 100 cycles a column, the next pivot formed by readlanes).  The form
+// Bound: the multiply-adds (992) beside the chain of pivots (the next one
+// formed by readlanes): FACT of 32 columns takes 31,200 cycles, 18,400 in
+// L L^T, whose pass has 496.  The form
 // before it (two passes, a broadcast LDS read per multiply-add, the code
 // unrolled with a branch for each replaced pivot's retry) is part of the
 // 490 us of a 256-wide FACT below.
@@ -1150,7 +1154,9 @@ __device__ __forceinline__ void inv_column(const GOp& gL, const GOp& gD, T* D, i
 // written in memory at every 32-column step, two barriers per step) took
 // 294 us at w = 256 in FP64 and 252 us without the inverse's off-diagonal
 // blocks, in a kernel of its own on an idle MI355X; this one 109 and 71 us
-// (FP32 233 and 206 us before, 89 and 57 us now).  With a wave's second row
+// (FP32 233 and 206 us before, 89 and 57 us now); the eight tiles are 34 of
+// the 71 us.  A further row block of 32 costs 17,000 cycles up to 128 columns
+// and 25,500 beyond, where a wave owns two.  With a wave's second row
 // block begun after its first was finished it took 123 and 83 us: the sums
 // of the last row blocks came late.
 //
@@ -1287,8 +1293,9 @@ __device__ __noinline__ void task_fact(const SchedArgs& a, Geo g, bool full, dou
 // row block J+4 overwrites tile J's after row block J+3 is factored, so only
 // the row blocks up to J+3 take it from LDS.  At w = 256 in FP64 the
 // right-looking form before it took 490 us in a kernel of its own (FP32
-// 410), this one 248 us (215), 145 us on the chain without the inverses'
-// off-diagonal blocks.
+// 410), this one 246 to 257 us (216 to 224), and 147 to 157 (116 to 120)
+// without the inverses' off-diagonal blocks, as on the chain; with a panel
+// stride that is a multiple of 64, 291 and 167 (247, 129).
 template <class T>
 __device__ __noinline__ void task_fact_lu(const SchedArgs& a, Geo g, bool full, double* Lt, double* tiles)
 {

@@ -22,8 +22,8 @@
 // (fwd_small, bwd_small).
 // Every sweep step writes a different vector than it reads (y -> z -> x), so
 // a diagonal block can be spread over several workgroups.  Every dot product
-// is split over four lanes (interleaved inner indices) and combined by two
-// shuffles: the dependent load rounds per thread are a quarter of a
+// is split over 4, 16 or 32 lanes (interleaved inner indices) and combined by
+// shuffles: that many times fewer dependent load rounds per thread than a
 // one-lane loop.  The sweeps stream the panels once each: they are bound by
 // HBM bandwidth and, on the narrow top levels, by load latency.
 // The factor is read in its storage type T (double, or float in the FP32

@@ -146,8 +146,8 @@ class Solver:
     split-BF16 products, FP64 refinement).  ir_max_iter None: the library's
     default for the precision (2 for fp64, 10 otherwise).  method: "llt"
     (P A P^T = L L^T, A positive definite) or "ldlt" (L D L^T with static
-    pivoting, A symmetric with non-zero pivots, e.g. quasi-definite; fp64
-    only; info()["logdet"] is then log |det A| and info()["nneg"] the number
+    pivoting, A symmetric with non-zero pivots, e.g. quasi-definite;
+    info()["logdet"] is then log |det A| and info()["nneg"] the number
     of negative pivots), or "lu" (P A P^T = L U with static pivoting, A
     unsymmetric, values of both triangles read; all precisions; the factor
     is the L panels followed by the U^T panels; no value gradient).
